@@ -32,7 +32,7 @@ BOYS_FLOPS_TAYLOR = 3 * 7 + 4  # 8-term Taylor at the nearest grid point
 # readings stored under profiles/ apply only while these are unchanged
 KERNEL_SOURCES = ["paper_1708_00033_amd/csrc/eri_impl.h", "paper_1708_00033_amd/csrc/hfx_internal.h",
                   "paper_1708_00033_amd/csrc/gen_eri.py", "paper_1708_00033_amd/csrc/hfx_api.cpp",
-                  "paper_1708_00033_amd/csrc/eri_dispatch.hip"]
+                  "paper_1708_00033_amd/csrc/eri_dispatch.hip", "paper_1708_00033_amd/csrc/eri_rys.h"]
 
 
 def class_flop_model():
@@ -593,6 +593,8 @@ def main():
         if p["persistent"] in (3, 4):
             return f"k_class_kr<Eval{p['cls']}{alt}, {mode}, {p['ket_nprim']}, {p['bras_per_task']}> " \
                    f"grid {p['blocks'] * p['wgs']}"
+        if p["cls"] in gen_eri.RYS_CLASSES:
+            return f"k_class_rys<Eval{p['cls']}, {mode}, 0, false> grid {p['blocks'] * p['wgs']}"
         form = {0: "k_class", 1: "k_class_persist", 2: "k_class_wave"}[p["persistent"]]
         return f"{form}<Eval{p['cls']}{alt}, {mode}, 0, {p['dstage']}> grid {p['blocks'] * p['wgs']}"
 

@@ -291,7 +291,9 @@ hfx_status hfx_configure(hfx_ctx *ctx, const hfx_options *opt);
  * eight per-XCD queues through atomic counters, the dynamic load balancing
  * of algorithms 1-3's ddi_dlbnext; 2: persistent with one task per wave,
  * each wave with its own LDS bra rows, for short tasks; falls back to 1 when
- * the workgroup's rows do not fit in LDS; 3: persistent and register-tiled:
+ * the workgroup's rows do not fit in LDS, and for the classes (dp|dp),
+ * (dd|pp), (dd|ds), (dd|dp) and (dd|dd), where a workgroup shares each
+ * quartet and tasks are at most 48 of its ket batches; 3: persistent and register-tiled:
  * a ket's primitives (1, 3 or 9 per pair) are read into registers once and
  * serve a block of two Q-adjacent bras (one when their LDS rows do not
  * fit), FP64 only -- a mixed build evaluates such a class in FP64; classes

@@ -44,7 +44,7 @@ def sources() -> list:
     # largest classes first so the pool finishes early
     gen = sorted(gen, key=lambda s: -int(os.path.basename(s)[10:12]))
     own = [os.path.join(CSRC, f) for f in ("eri_dispatch.hip", "misc_kernels.hip", "guess.hip", "noalloc.hip", "batch_scf.hip", "hfx_api.cpp",
-                                            "scf.cpp", "boys_table.cpp")]
+                                            "scf.cpp", "boys_table.cpp", "rys_table.cpp")]
     return gen + own
 
 

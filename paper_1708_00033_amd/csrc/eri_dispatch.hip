@@ -18,7 +18,82 @@ static const void* (*const kClassLookup[21])(int) = {HFX_FOR_EACH_CID(HFX_KPTR)}
 static const void* (*const kClassLookupKr[21])(int) = {HFX_FOR_EACH_CID(HFX_RPTR)};
 static const void* (*const kSchwarzLookup[21])(void) = {HFX_FOR_EACH_CID(HFX_SPTR)};
 
+// Classes of the cooperative Rys kernels (eri_rys.h).
+#define HFX_RYS_DECL(cid)                                      \
+    extern "C" const void* hfx_class_kernel_rys_##cid(int);    \
+    extern "C" int hfx_class_rys_lds_##cid(int, int);          \
+    extern "C" int hfx_class_rys_kets_##cid(void);
+HFX_FOR_EACH_RYS(HFX_RYS_DECL)
+
+// Kernel variant mode + 2 mixed + 4 multi of a cooperative class.
+static const void* rys_kernel(int cid, int mode, int mixed, int multi) {
+    const int v = mode + 2 * mixed + 4 * multi;
+#define HFX_RYS_CASE(c) \
+    case c: return hfx_class_kernel_rys_##c(v);
+    switch (cid) {
+        HFX_FOR_EACH_RYS(HFX_RYS_CASE)
+        default: return nullptr;
+    }
+#undef HFX_RYS_CASE
+}
+
+extern "C" int hfx_class_is_rys(int cid) { return kEriClassInfo[cid].rys; }
+
+// LDS bytes of a cooperative kernel without its rows of W.
+extern "C" int hfx_class_rys_lds(int cid, int mode, int ndens) {
+#define HFX_RYS_CASE(c) \
+    case c: return hfx_class_rys_lds_##c(mode, ndens);
+    switch (cid) {
+        HFX_FOR_EACH_RYS(HFX_RYS_CASE)
+        default: return 0;
+    }
+#undef HFX_RYS_CASE
+}
+
+// Kets of one batch of a cooperative kernel.
+extern "C" int hfx_class_rys_kets(int cid) {
+#define HFX_RYS_CASE(c) \
+    case c: return hfx_class_rys_kets_##c();
+    switch (cid) {
+        HFX_FOR_EACH_RYS(HFX_RYS_CASE)
+        default: return 0;
+    }
+#undef HFX_RYS_CASE
+}
+
 extern "C" int hfx_class_wgs(int cid, int alt);
+
+static hipError_t set_lds(const void* fn, size_t lds_bytes) {
+    if (lds_bytes <= 64 * 1024) return hipSuccess;
+    return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+}
+
+// Workgroups of fn that fit on the device at once (0: a query failed).
+static int resident_blocks(const void* fn, int wgs, size_t lds_bytes) {
+    if (!fn || set_lds(fn, lds_bytes) != hipSuccess) return 0;
+    int per_cu = 0, dev = 0, ncu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, wgs, lds_bytes) != hipSuccess) return 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 0;
+    return per_cu * ncu;
+}
+
+// nblocks workgroups: the tasks of a static launch, or (args->work set) the resident grid.
+extern "C" hipError_t hfx_launch_class_rys(int cid, int mode, int mixed, int multi, int nblocks, size_t lds_bytes,
+                                           hipStream_t stream, const ClassArgs* args) {
+    if (nblocks <= 0) return hipSuccess;
+    const void* fn = rys_kernel(cid, mode, mixed, multi);
+    if (!fn || !args->rys) return hipErrorInvalidValue;
+    const hipError_t e = set_lds(fn, lds_bytes);
+    if (e != hipSuccess) return e;
+    void* kargs[] = {(void*)args};
+    return hipLaunchKernel(fn, dim3(nblocks), dim3(hfx_class_wgs(cid, 0)), kargs, lds_bytes, stream);
+}
+
+extern "C" int hfx_class_resident_blocks_rys(int cid, int mode, int mixed, size_t lds_bytes) {
+    return resident_blocks(rys_kernel(cid, mode, mixed, 0), hfx_class_wgs(cid, 0), lds_bytes);
+}
 
 // Register-tiled kernels: variant index of (digestion mode, ket primitive
 // count, bras per block), or -1 when the class has none for that count.
@@ -37,10 +112,8 @@ extern "C" hipError_t hfx_launch_class_kr(int cid, int mode, int kp, int nbl, in
     const int v = kr_variant(cid, mode, kp, nbl);
     if (v < 0 || !args->work) return hipErrorInvalidValue;
     const void* fn = kClassLookupKr[cid](v);
-    if (lds_bytes > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-        if (e != hipSuccess) return e;
-    }
+    const hipError_t e = set_lds(fn, lds_bytes);
+    if (e != hipSuccess) return e;
     void* kargs[] = {(void*)args};
     return hipLaunchKernel(fn, dim3(nblocks), dim3(hfx_class_wgs(cid, 1)), kargs, lds_bytes, stream);
 }
@@ -48,17 +121,7 @@ extern "C" hipError_t hfx_launch_class_kr(int cid, int mode, int kp, int nbl, in
 extern "C" int hfx_class_resident_blocks_kr(int cid, int mode, int kp, int nbl, size_t lds_bytes) {
     const int v = kr_variant(cid, mode, kp, nbl);
     if (v < 0) return 0;
-    const void* fn = kClassLookupKr[cid](v);
-    if (lds_bytes > 64 * 1024 &&
-        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess)
-        return 0;
-    int per_cu = 0, dev = 0, ncu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, hfx_class_wgs(cid, 1), lds_bytes) != hipSuccess)
-        return 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return 0;
-    return per_cu * ncu;
+    return resident_blocks(kClassLookupKr[cid](v), hfx_class_wgs(cid, 1), lds_bytes);
 }
 
 #define HFX_WG 256
@@ -82,10 +145,8 @@ extern "C" hipError_t hfx_launch_class(int cid, int alt, int wave, int mode, int
     if (args->dstage != 0 && args->dstage != 1 && args->dstage != 3) return hipErrorInvalidValue;
     const void* fn = kClassLookup[cid](class_variant(alt, args->work != nullptr, wave, mode, mixed, args->dstage));
     if (!fn) return hipErrorInvalidValue;
-    if (lds_bytes > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-        if (e != hipSuccess) return e;
-    }
+    const hipError_t e = set_lds(fn, lds_bytes);
+    if (e != hipSuccess) return e;
     void* kargs[] = {(void*)args};
     return hipLaunchKernel(fn, dim3(nblocks), dim3(hfx_class_wgs(cid, alt)), kargs, lds_bytes, stream);
 }
@@ -93,18 +154,8 @@ extern "C" hipError_t hfx_launch_class(int cid, int alt, int wave, int mode, int
 // Workgroups of one class kernel that fit on the device at once.
 extern "C" int hfx_class_resident_blocks(int cid, int alt, int wave, int mode, int mixed, int dstage,
                                          size_t lds_bytes) {
-    const void* fn = kClassLookup[cid](class_variant(alt, 1, wave, mode, mixed, dstage));
-    if (!fn) return 0;
-    if (lds_bytes > 64 * 1024 &&
-        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess)
-        return 0;
-    int per_cu = 0, dev = 0, ncu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, hfx_class_wgs(cid, alt), lds_bytes) != hipSuccess)
-        return 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return 0;
-    return per_cu * ncu;
+    return resident_blocks(kClassLookup[cid](class_variant(alt, 1, wave, mode, mixed, dstage)),
+                           hfx_class_wgs(cid, alt), lds_bytes);
 }
 
 
@@ -115,10 +166,9 @@ extern "C" hipError_t hfx_launch_class_multi(int cid, int mode, int nblocks, siz
     if (nblocks <= 0) return hipSuccess;
     if (!args->work) return hipErrorInvalidValue;
     const void* fn = kMultiLookup[cid](mode);
-    if (lds_bytes > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-        if (e != hipSuccess) return e;
-    }
+    if (!fn) return hipErrorInvalidValue;
+    const hipError_t e = set_lds(fn, lds_bytes);
+    if (e != hipSuccess) return e;
     void* kargs[] = {(void*)args};
     return hipLaunchKernel(fn, dim3(nblocks), dim3(kEriClassInfo[cid].wgs), kargs, lds_bytes, stream);
 }
@@ -130,10 +180,11 @@ extern "C" hipError_t hfx_launch_class_multi(int cid, int mode, int nblocks, siz
 extern "C" hipError_t hfx_class_kernel_resources(int cid, long long* scratch_bytes, int* regs) {
     long long sc = 0;
     int rg = 0;
-    for (int v = 0; v < 128 + 12 + 2; ++v) {
+    for (int v = 0; v < 128 + 12 + 2 + 6; ++v) {
         const void* fn = v < 128   ? kClassLookup[cid](v)
                          : v < 140 ? kClassLookupKr[cid](v - 128)
-                                   : kMultiLookup[cid](v - 140);
+                         : v < 142 ? kMultiLookup[cid](v - 140)
+                                   : rys_kernel(cid, (v - 142) & 1, ((v - 142) >> 1) & 1, (v - 142) >> 2);
         if (!fn) continue;
         hipFuncAttributes fa;
         const hipError_t e = hipFuncGetAttributes(&fa, fn);
@@ -147,9 +198,14 @@ extern "C" hipError_t hfx_class_kernel_resources(int cid, long long* scratch_byt
 }
 
 extern "C" hipError_t hfx_launch_schwarz(int cid, const PairInfo* pairs, int npairs, const PrimPair* prim,
-                                         const double* boys, double* Q, hipStream_t stream) {
+                                         const double* boys, const double* rys, double* Q, hipStream_t stream) {
     if (npairs <= 0) return hipSuccess;
     const void* fn = kSchwarzLookup[cid]();
+    if (!fn) return hipErrorInvalidValue;
+    if (kEriClassInfo[cid].rys) {   // one workgroup per pair
+        void* kargs[] = {(void*)&pairs, (void*)&prim, (void*)&rys, (void*)&Q};
+        return hipLaunchKernel(fn, dim3(npairs), dim3(kEriClassInfo[cid].wgs), kargs, 0, stream);
+    }
     void* kargs[] = {(void*)&pairs, (void*)&npairs, (void*)&prim, (void*)&boys, (void*)&Q};
     return hipLaunchKernel(fn, dim3((npairs + HFX_WG - 1) / HFX_WG), dim3(HFX_WG), kargs, 0, stream);
 }

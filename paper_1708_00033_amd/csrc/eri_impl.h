@@ -26,10 +26,6 @@
 #include "hfx_internal.h"
 
 #define HFX_WG 256
-// integral blocks at least this large are digested with rolled loops
-#define HFX_ROLLED_DIGEST_MIN 600
-
-
 
 // K update of W[grow][gcol]: MODE 0 into the task's LDS bra row at column
 // lcol (gcol less the column base of its window), MODE 1 straight into W.
@@ -265,148 +261,6 @@ __device__ __forceinline__ void digest_kr(const double* I, double g, double ck, 
     }
 }
 
-// Same updates with rolled loops, for classes whose integral block is too
-// large to keep in registers (the block then lives in scratch).
-template <int NA, int NB, int NC, int ND, int MODE>
-__device__ __forceinline__ void digest_rolled(const double* I, double g, const ClassArgs& a, const PairInfo& bra,
-                                              int fc, int fd, int spos, const double* dab, double* jab,
-                                              double* FI, double* FJ, const double* __restrict__ D,
-                                              double* W, int N, int RS, int cb, int db,
-                                              const double* __restrict__ dket, double* WK, double* wket) {
-    const int fa = bra.bfa, fb = bra.bfb;
-    const double cj2 = 2.0 * a.cj * g, ckg = -a.ck * g;
-    (void)wket;   // the ket block's J goes straight into W (rolled digestion)
-#pragma unroll 1
-    for (int mn = 0; mn < NA * NB; ++mn) {
-        double v = 0.0;
-#pragma unroll 1
-        for (int ls = 0; ls < NC * ND; ++ls) v += I[mn * NC * ND + ls] * dket[(size_t)ls * a.nket_list + spos];
-        jab[mn] += g * v;
-    }
-#pragma unroll 1
-    for (int ls = 0; ls < NC * ND; ++ls) {
-        double v = 0.0;
-#pragma unroll 1
-        for (int mn = 0; mn < NA * NB; ++mn) v += I[mn * NC * ND + ls] * dab[mn];
-        atomicAdd(W + (size_t)(fc + ls / ND) * N + fd + ls % ND, cj2 * v);
-    }
-#pragma unroll 1
-    for (int m = 0; m < NA; ++m)
-#pragma unroll 1
-        for (int l = 0; l < NC; ++l) {
-            double v1 = 0.0;
-#pragma unroll 1
-            for (int n = 0; n < NB; ++n)
-#pragma unroll 1
-                for (int s = 0; s < ND; ++s)
-                    v1 += I[((m * NB + n) * NC + l) * ND + s] * D[(size_t)(fb + n) * N + fd + s];
-            row_add<MODE>(FI + m * RS, WK, fa + m, fc + l, N, fc + l - cb, ckg * v1);
-        }
-#pragma unroll 1
-    for (int n = 0; n < NB; ++n)
-#pragma unroll 1
-        for (int s = 0; s < ND; ++s) {
-            double v2 = 0.0;
-#pragma unroll 1
-            for (int m = 0; m < NA; ++m)
-#pragma unroll 1
-                for (int l = 0; l < NC; ++l)
-                    v2 += I[((m * NB + n) * NC + l) * ND + s] * D[(size_t)(fa + m) * N + fc + l];
-            row_add<MODE>(FJ + n * RS, WK, fb + n, fd + s, N, fd + s - db, ckg * v2);
-        }
-#pragma unroll 1
-    for (int m = 0; m < NA; ++m)
-#pragma unroll 1
-        for (int s = 0; s < ND; ++s) {
-            double v3 = 0.0;
-#pragma unroll 1
-            for (int n = 0; n < NB; ++n)
-#pragma unroll 1
-                for (int l = 0; l < NC; ++l)
-                    v3 += I[((m * NB + n) * NC + l) * ND + s] * D[(size_t)(fb + n) * N + fc + l];
-            row_add<MODE>(FI + m * RS, WK, fa + m, fd + s, N, fd + s - db, ckg * v3);
-        }
-#pragma unroll 1
-    for (int n = 0; n < NB; ++n)
-#pragma unroll 1
-        for (int l = 0; l < NC; ++l) {
-            double v4 = 0.0;
-#pragma unroll 1
-            for (int m = 0; m < NA; ++m)
-#pragma unroll 1
-                for (int s = 0; s < ND; ++s)
-                    v4 += I[((m * NB + n) * NC + l) * ND + s] * D[(size_t)(fa + m) * N + fd + s];
-            row_add<MODE>(FJ + n * RS, WK, fb + n, fc + l, N, fc + l - cb, ckg * v4);
-        }
-}
-
-// Digestion of one pass of a large class: the integrals (a_k b | c d) of the
-// k-th Cartesian component of shell a, all b, c, d (I laid out [b][c][d]).
-// Same updates as digest(), restricted to mu = k; rolled loops (the block
-// lives in scratch, 8 NB NC ND bytes per lane).
-template <int NA, int NB, int NC, int ND, int MODE>
-__device__ __forceinline__ void digest_pass(int k, const double* I, double g, const ClassArgs& a,
-                                            const PairInfo& bra, int fc, int fd, int spos, const double* dab,
-                                            double* jab, double* FI, double* FJ, const double* __restrict__ D,
-                                            double* W, int N, int RS, int cb, int db,
-                                            const double* __restrict__ dket, double* WK, double* wket) {
-    const int fa = bra.bfa, fb = bra.bfb;
-    const double cj2 = 2.0 * a.cj * g, ckg = -a.ck * g;
-    constexpr int NCD = NC * ND;
-#pragma unroll 1
-    for (int n = 0; n < NB; ++n) {   // J, bra block (mu = k)
-        double v = 0.0;
-#pragma unroll 1
-        for (int ls = 0; ls < NCD; ++ls) v += I[n * NCD + ls] * dket[(size_t)ls * a.nket_list + spos];
-        jab[k * NB + n] += g * v;
-    }
-#pragma unroll 1
-    for (int ls = 0; ls < NCD; ++ls) {   // J, ket block
-        double v = 0.0;
-#pragma unroll 1
-        for (int n = 0; n < NB; ++n) v += I[n * NCD + ls] * dab[k * NB + n];
-        if constexpr (MODE == 0)
-            atomicAdd(wket + (size_t)ls * a.nket_list + spos, cj2 * v);
-        else
-            atomicAdd(W + (size_t)(fc + ls / ND) * N + fd + ls % ND, cj2 * v);
-    }
-#pragma unroll 1
-    for (int l = 0; l < NC; ++l) {   // K: (k, c_l) -= sum_{n s} I D_bd
-        double v = 0.0;
-#pragma unroll 1
-        for (int n = 0; n < NB; ++n)
-#pragma unroll 1
-            for (int s = 0; s < ND; ++s) v += I[(n * NC + l) * ND + s] * D[(size_t)(fb + n) * N + fd + s];
-        row_add<MODE>(FI + k * RS, WK, fa + k, fc + l, N, fc + l - cb, ckg * v);
-    }
-#pragma unroll 1
-    for (int s = 0; s < ND; ++s) {   // K: (k, d_s) -= sum_{n l} I D_bc
-        double v = 0.0;
-#pragma unroll 1
-        for (int n = 0; n < NB; ++n)
-#pragma unroll 1
-            for (int l = 0; l < NC; ++l) v += I[(n * NC + l) * ND + s] * D[(size_t)(fb + n) * N + fc + l];
-        row_add<MODE>(FI + k * RS, WK, fa + k, fd + s, N, fd + s - db, ckg * v);
-    }
-#pragma unroll 1
-    for (int n = 0; n < NB; ++n) {
-#pragma unroll 1
-        for (int s = 0; s < ND; ++s) {   // K: (b_n, d_s) -= sum_l I D_ac
-            double v = 0.0;
-#pragma unroll 1
-            for (int l = 0; l < NC; ++l) v += I[(n * NC + l) * ND + s] * D[(size_t)(fa + k) * N + fc + l];
-            row_add<MODE>(FJ + n * RS, WK, fb + n, fd + s, N, fd + s - db, ckg * v);
-        }
-#pragma unroll 1
-        for (int l = 0; l < NC; ++l) {   // K: (b_n, c_l) -= sum_s I D_ad
-            double v = 0.0;
-#pragma unroll 1
-            for (int s = 0; s < ND; ++s) v += I[(n * NC + l) * ND + s] * D[(size_t)(fa + k) * N + fd + s];
-            row_add<MODE>(FJ + n * RS, WK, fb + n, fc + l, N, fc + l - cb, ckg * v);
-        }
-    }
-}
-
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -474,7 +328,6 @@ __device__ __forceinline__ void task_sync() {
 template <class E, int MODE, int FP32, bool WAVE = false, int DST = 0>
 __device__ __forceinline__ void class_task(const ClassArgs& a, const int ti, const double* t64, unsigned& cnt64,
                                            unsigned& cnt32) {
-    static_assert(!(FP32 && E::PASSES), "classes evaluated in passes are FP64 only");
     constexpr int NA = hfx_ncart(E::LA), NB = hfx_ncart(E::LB), NC = hfx_ncart(E::LC), ND = hfx_ncart(E::LD);
     constexpr int NAB = NA * NB, NI = NA * NB * NC * ND;
     constexpr int NT = WAVE ? 64 : E::WGS;   // lanes of the task
@@ -506,7 +359,7 @@ __device__ __forceinline__ void class_task(const ClassArgs& a, const int ti, con
     }
     // LDS digestion with staged D' rows: DI, the bra's rows of shell a (DST
     // bit 0), then DJ, those of shell b (bit 1), after F_I and F_J
-    static_assert(DST == 0 || (MODE == 0 && NI <= HFX_STAGE_D_MAX_NI && !E::PASSES), "no staged D' rows");
+    static_assert(DST == 0 || (MODE == 0 && NI <= HFX_STAGE_D_MAX_NI), "no staged D' rows");
     constexpr int nda = (DST & 1) ? NA : 0, ndb = (DST & 2) ? NB : 0;
     // a wave's region is (NA + NB + nda + ndb) a.rs doubles (a.rs >= RS for every molecule of a batch)
     double* FI = lds + LdsLayout<E>::ROWS + (WAVE ? (int)(threadIdx.x >> 6) * (NA + NB + nda + ndb) * a.rs : 0);
@@ -537,24 +390,6 @@ __device__ __forceinline__ void class_task(const ClassArgs& a, const int ti, con
     const double sbra = bra.a != bra.b ? 2.0 : 1.0;
     const int kps = a.nket_list, kfs = a.nket_list * a.knprim;
     unsigned n64 = 0, n32 = 0;
-    if constexpr (E::PASSES) {
-        // one Cartesian component of shell a per pass, and the passes of a
-        // quartet on different lanes: work item it = k * nq + (s - s0), so a
-        // short task (few kets) still fills NA times as many lanes, and the
-        // lanes of a wave share k
-        const int nq = send - s0;
-        for (int it = tid; it < NA * nq; it += NT) {
-            const int k = it / nq, s = s0 + it % nq;
-            const int4 kb = a.kbf[s];
-            const double g = sbra * (kb.z != kb.w ? 2.0 : 1.0) * ((kb.z == bra.a && kb.w == bra.b) ? 1.0 : 2.0);
-            double Ik[NB * NC * ND];
-            E::template run_pass<double, BOYS_LROW64>(k, (const double*)(a.prim + bra.prim_off), bra.nprim,
-                                                      a.kprim + s, kfs, kps, a.knprim, bra.AB, a.ket[s].AB, t64, Ik);
-            digest_pass<NA, NB, NC, ND, MODE>(k, Ik, g, a, bra, kb.x, kb.y, s, dab, jab, FI, FJ, Dm, Wm, N, RS, cb,
-                                              db, a.dket, Wm, a.wket);
-            if (k == 0) ++n64;
-        }
-    }
     // The task's kets in slots of 64 consecutive kets, dealt to the task's
     // waves in turn (wave w takes slots w, w + nw, ...): the FP64 part
     // [s0, split) fills the first slots and the FP32 part [split, send) the
@@ -566,7 +401,7 @@ __device__ __forceinline__ void class_task(const ClassArgs& a, const int ti, con
     const int nw = NT / 64, wv = tid >> 6, ln = tid & 63;
     const int slots64 = (split - s0 + 63) >> 6;
     const int slots = slots64 + ((send - split + 63) >> 6);
-    for (int j = wv; j < slots && !E::PASSES; j += nw) {
+    for (int j = wv; j < slots; j += nw) {
         const bool lo = j < slots64;   // wave-uniform
         const int s = lo ? s0 + (j << 6) + ln : split + ((j - slots64) << 6) + ln;
         if (s >= (lo ? split : send)) continue;   // the part's last, partial slot
@@ -587,12 +422,8 @@ __device__ __forceinline__ void class_task(const ClassArgs& a, const int ti, con
         // the block (either precision) digested in FP64
         const int4 kb = a.kbf[s];   // ket's first basis functions and shells
         const double g = sbra * (kb.z != kb.w ? 2.0 : 1.0) * ((kb.z == bra.a && kb.w == bra.b) ? 1.0 : 2.0);
-        if constexpr (NI >= HFX_ROLLED_DIGEST_MIN)
-            digest_rolled<NA, NB, NC, ND, MODE>(I, g, a, bra, kb.x, kb.y, s, dab, jab, FI, FJ, Dm, Wm, N, RS, cb, db,
-                                                a.dket, Wm, a.wket);
-        else
-            digest<NA, NB, NC, ND, MODE, DST>(I, g, a, bra, kb.x, kb.y, s, dab, jab, FI, FJ, Dm, Wm, N, RS, cb, db,
-                                              a.dket, Wm, a.wket, DI, DJ);
+        digest<NA, NB, NC, ND, MODE, DST>(I, g, a, bra, kb.x, kb.y, s, dab, jab, FI, FJ, Dm, Wm, N, RS, cb, db, a.dket,
+                                          Wm, a.wket, DI, DJ);
     }
     // bra J block: wave reduction, one global add per wave (column bfb may lie
     // outside the task's windows)
@@ -811,7 +642,6 @@ __device__ __forceinline__ void class_task_multi(const ClassArgs& a, const int t
     if (task.x < 0) return;
     const int r0 = task.x & 0x0fffffff, nb = (task.x >> 28) + 1;
     const int s0 = task.y, nq = task.z - task.y;
-    const int nwork = E::PASSES ? NA * nq : nq;
     unsigned n64 = 0;
     for (int i = 0; i < nb; ++i) {
         const int r = r0 + i;
@@ -835,24 +665,19 @@ __device__ __forceinline__ void class_task_multi(const ClassArgs& a, const int t
             for (int x = tid; x < a.ndens * rowset; x += NT) F0[x] = 0.0;
             __syncthreads();
         }
-        for (int base = 0; base < nwork; base += NT) {
+        for (int base = 0; base < nq; base += NT) {
             const int it = base + tid;
-            bool valid = it < nwork;
-            const int k = E::PASSES ? (valid ? it / nq : 0) : 0;
-            const int s = s0 + (valid ? (E::PASSES ? it % nq : it) : 0);
+            bool valid = it < nq;
+            const int s = s0 + (valid ? it : 0);
             if (valid) valid = a.ketq[s] * bra.Q >= a.tau && !(a.same && a.kpos[s] > r);
             const int4 kb = a.kbf[s];
             const double g = sbra * (kb.z != kb.w ? 2.0 : 1.0) * ((kb.z == bra.a && kb.w == bra.b) ? 1.0 : 2.0);
-            double I[E::PASSES ? NB * NC * ND : NI];
+            double I[NI];
             if (valid) {
-                const double* bp = (const double*)(a.prim + bra.prim_off);
-                if constexpr (E::PASSES)
-                    E::template run_pass<double, BOYS_LROW64>(k, bp, bra.nprim, a.kprim + s, a.nket_list * a.knprim,
-                                                              a.nket_list, a.knprim, bra.AB, a.ket[s].AB, t64, I);
-                else
-                    E::template run<double, BOYS_LROW64>(bp, bra.nprim, a.kprim + s, a.nket_list * a.knprim,
-                                                         a.nket_list, a.knprim, bra.AB, a.ket[s].AB, t64, I);
-                if (k == 0) ++n64;
+                E::template run<double, BOYS_LROW64>((const double*)(a.prim + bra.prim_off), bra.nprim, a.kprim + s,
+                                                     a.nket_list * a.knprim, a.nket_list, a.knprim, bra.AB, a.ket[s].AB,
+                                                     t64, I);
+                ++n64;
             }
             for (int d = 0; d < a.ndens; ++d) {
                 const double* __restrict__ Dd = a.D + (size_t)d * a.dstride + moff;
@@ -867,17 +692,9 @@ __device__ __forceinline__ void class_task_multi(const ClassArgs& a, const int t
                     dab[mn] = Dd[(size_t)(bra.bfa + mn / NB) * N + bra.bfb + mn % NB];
                     jt[mn] = 0.0;
                 }
-                if (valid) {
-                    if constexpr (E::PASSES)
-                        digest_pass<NA, NB, NC, ND, MODE>(k, I, g, a, bra, kb.x, kb.y, s, dab, jt, FI, FI + NA * RS,
-                                                          Dd, WJ, N, RS, cb, db, dket, WKd, wket);
-                    else if constexpr (NI >= HFX_ROLLED_DIGEST_MIN)
-                        digest_rolled<NA, NB, NC, ND, MODE>(I, g, a, bra, kb.x, kb.y, s, dab, jt, FI, FI + NA * RS,
-                                                            Dd, WJ, N, RS, cb, db, dket, WKd, wket);
-                    else
-                        digest<NA, NB, NC, ND, MODE>(I, g, a, bra, kb.x, kb.y, s, dab, jt, FI, FI + NA * RS, Dd, WJ,
-                                                     N, RS, cb, db, dket, WKd, wket);
-                }
+                if (valid)
+                    digest<NA, NB, NC, ND, MODE>(I, g, a, bra, kb.x, kb.y, s, dab, jt, FI, FI + NA * RS, Dd, WJ, N, RS,
+                                                 cb, db, dket, WKd, wket);
 #pragma unroll
                 for (int mn = 0; mn < NAB; ++mn) {
                     const double v = wave_sum(jt[mn]);
@@ -1041,15 +858,10 @@ __global__ __launch_bounds__(HFX_WG) void k_schwarz(const PairInfo* __restrict__
 
 
 // Kernel variants of one class: launch form x digestion mode x precision.
-// Classes with integral blocks of HFX_ROLLED_DIGEST_MIN or more (d-d bra with
-// a d-d or d-p ket) exist only in FP64: their register allocation is the
-// build-time bottleneck and they carry a negligible share of the quartets,
-// so mixed builds evaluate them in FP64 (the more accurate choice).
 template <class E>
 struct ClassKernelsOne {
     static constexpr int NI = hfx_ncart(E::LA) * hfx_ncart(E::LB) * hfx_ncart(E::LC) * hfx_ncart(E::LD);
-    static constexpr bool kOnlyFp64Global = NI >= HFX_ROLLED_DIGEST_MIN;
-    static constexpr bool kStage = NI <= HFX_STAGE_D_MAX_NI && !E::PASSES;
+    static constexpr bool kStage = NI <= HFX_STAGE_D_MAX_NI;
     // LDS digestion with staged D' rows (DST 1: shell a's, 3: both shells'):
     // form 0 static, 1 persistent, 2 one task per wave
     template <int DST>
@@ -1073,25 +885,15 @@ struct ClassKernelsOne {
             }
         }
         if (variant & 16) {
-            if constexpr (kOnlyFp64Global) {
-                return (variant & 2) ? (const void*)k_class_wave<E, 1, 0> : (const void*)k_class_wave<E, 0, 0>;
-            } else {
-                static const void* w[4] = {(const void*)k_class_wave<E, 0, 0>, (const void*)k_class_wave<E, 0, 1>,
-                                           (const void*)k_class_wave<E, 1, 0>, (const void*)k_class_wave<E, 1, 1>};
-                return w[variant & 3];
-            }
+            static const void* w[4] = {(const void*)k_class_wave<E, 0, 0>, (const void*)k_class_wave<E, 0, 1>,
+                                       (const void*)k_class_wave<E, 1, 0>, (const void*)k_class_wave<E, 1, 1>};
+            return w[variant & 3];
         }
-        if constexpr (kOnlyFp64Global) {
-            static const void* t[4] = {(const void*)k_class<E, 0, 0>, (const void*)k_class<E, 1, 0>,
-                                       (const void*)k_class_persist<E, 0, 0>, (const void*)k_class_persist<E, 1, 0>};
-            return t[(variant >= 4 ? 2 : 0) + ((variant & 3) >= 2 ? 1 : 0)];
-        } else {
-            static const void* t[8] = {(const void*)k_class<E, 0, 0>,         (const void*)k_class<E, 0, 1>,
-                                       (const void*)k_class<E, 1, 0>,         (const void*)k_class<E, 1, 1>,
-                                       (const void*)k_class_persist<E, 0, 0>, (const void*)k_class_persist<E, 0, 1>,
-                                       (const void*)k_class_persist<E, 1, 0>, (const void*)k_class_persist<E, 1, 1>};
-            return t[variant];
-        }
+        static const void* t[8] = {(const void*)k_class<E, 0, 0>,         (const void*)k_class<E, 0, 1>,
+                                   (const void*)k_class<E, 1, 0>,         (const void*)k_class<E, 1, 1>,
+                                   (const void*)k_class_persist<E, 0, 0>, (const void*)k_class_persist<E, 0, 1>,
+                                   (const void*)k_class_persist<E, 1, 0>, (const void*)k_class_persist<E, 1, 1>};
+        return t[variant];
     }
 };
 
@@ -1136,7 +938,6 @@ struct ClassKernelsKr {
 #define HFX_CLASS_TU(cid, fname, la_, lb_, lc_, ld_, wgs_, wgs_alt_)                                               \
     struct Eval##cid {                                                                                 \
         static constexpr int LA = la_, LB = lb_, LC = lc_, LD = ld_, WGS = wgs_;                       \
-        static constexpr bool PASSES = false;                                                          \
         template <typename R, int BS = BOYS_ROW, typename SP = double, typename TT = R>                \
         __device__ __forceinline__ static void run(const SP* bp, int nbp, const SP* kq0, int kfs,      \
                                                    int kps, int nkp, const double* ab,                 \
@@ -1150,39 +951,6 @@ struct ClassKernelsKr {
                                                       const double* cd, const R* tab, R* out) {        \
             fname##_kr<R, BS, KP>(bp, nbp, kv, R(ab[0]), R(ab[1]), R(ab[2]), R(cd[0]), R(cd[1]),       \
                                   R(cd[2]), tab, out);                                                 \
-        }                                                                                              \
-    };                                                                                                 \
-    struct Eval##cid##A : Eval##cid {                                                                   \
-        static constexpr int WGS = wgs_alt_;                                                           \
-    };                                                                                                 \
-    extern "C" const void* hfx_class_kernel_##cid(int variant) {                                       \
-        return ClassKernels<Eval##cid, Eval##cid##A>::get(variant);                                    \
-    }                                                                                                  \
-    extern "C" const void* hfx_class_kernel_multi_##cid(int mode) {                                   \
-        return mode ? (const void*)k_class_multi<Eval##cid, 1> : (const void*)k_class_multi<Eval##cid, 0>; \
-    }                                                                                                  \
-    extern "C" const void* hfx_schwarz_kernel_##cid(void) { return (const void*)k_schwarz<Eval##cid>; }
-
-// Per-class translation unit of a large class: the full evaluator (Schwarz
-// bounds) plus the per-component passes used by the class kernels.
-#define HFX_CLASS_TU_PASSES(cid, fname, la_, lb_, lc_, ld_, wgs_, wgs_alt_)                                        \
-    struct Eval##cid {                                                                                 \
-        static constexpr int LA = la_, LB = lb_, LC = lc_, LD = ld_, WGS = wgs_;                       \
-        static constexpr bool PASSES = true;                                                           \
-        template <typename R, int BS = BOYS_ROW, typename SP = double, typename TT = R>                \
-        __device__ __forceinline__ static void run(const SP* bp, int nbp, const SP* kq0, int kfs,      \
-                                                   int kps, int nkp, const double* ab,                 \
-                                                   const double* cd, const TT* tab, R* out) {          \
-            fname<R, BS, SP, TT>(bp, nbp, kq0, kfs, kps, nkp, R(ab[0]), R(ab[1]), R(ab[2]), R(cd[0]),  \
-                                 R(cd[1]), R(cd[2]), tab, out);                                        \
-        }                                                                                              \
-        template <typename R, int BS = BOYS_ROW>                                                       \
-        __device__ __forceinline__ static void run_pass(int k, const double* bp, int nbp,              \
-                                                        const double* kq0, int kfs, int kps, int nkp,  \
-                                                        const double* ab, const double* cd,            \
-                                                        const R* tab, R* out) {                        \
-            fname##_pass<R, BS>(k, bp, nbp, kq0, kfs, kps, nkp, R(ab[0]), R(ab[1]), R(ab[2]),          \
-                                R(cd[0]), R(cd[1]), R(cd[2]), tab, out);                               \
         }                                                                                              \
     };                                                                                                 \
     struct Eval##cid##A : Eval##cid {                                                                   \

@@ -24,6 +24,9 @@ Head-Gordon & Pople, J. Chem. Phys. 89, 5777 (1988)):
                  + e_i/(2(p+q)) [e-1_i|f]^(m+1)
   [0|0]^(m)     = K_ab K_cd 2 pi^{5/2} / (p q sqrt(p+q)) F_m(rho |PQ|^2)
 
+The five largest classes get no evaluator: the lanes of a workgroup share
+their quartets (RYS_CLASSES, eri_rys.h).
+
 The functions are templated on the real type (double or float) so the same
 text yields the FP64 and FP32 evaluators.  The bra is built first (f = 0),
 then the ket; the recursion direction is the axis with the smallest
@@ -45,11 +48,20 @@ CLASSES = [(B, K) for B in range(6) for K in range(B + 1)]
 # SIMD), 512 where it fits in 256, 256 for the register-heavy classes.
 WG1024 = {1, 6}
 WG512 = {0, 2, 3, 4, 7, 9, 10}
+# Classes evaluated by the cooperative Rys-quadrature kernels (eri_rys.h), with
+# the kets of a batch: 16 where the one-dimensional integrals of 16 kets fit in
+# LDS beside the bra rows at 1,216 basis functions, else 8.
+RYS_CLASSES = {14: 16, 17: 16, 18: 16, 19: 8, 20: 8}
+# Classes that mixed builds evaluate in FP64 too (a d-d bra and a d-d or d-p ket).
+FP64_ONLY = {19, 20}
 # Classes whose bra primitive loop runs two primitives per trip.
 UNROLL2 = set()
 
 
 def wg_size(cid):
+    if cid in RYS_CLASSES:   # 9 units of 2 x 2 (d-d bra) or 5 of 4 (d-p) component pairs, 16 / kets per wave
+        units = 9 if CLASSES[cid][0] == 5 else 5
+        return 64 * -(-units * RYS_CLASSES[cid] // 16)
     return 1024 if cid in WG1024 else (512 if cid in WG512 else 256)
 
 
@@ -142,10 +154,8 @@ class ClassGen:
         return es, fs
 
     # ---- horizontal recurrences (after contraction) ----
-    def emit(self, fname, a_sel=None):
-        """Straight-line evaluator.  a_sel = k restricts the outputs to the
-        k-th Cartesian component of shell a (all b, c, d): a pass of a large
-        class, with only the recurrence nodes that this pass needs."""
+    def emit(self, fname):
+        """Straight-line evaluator."""
         acc_name = {}
         hnodes = {}
         hcode = []
@@ -194,8 +204,7 @@ class ClassGen:
 
         outs = []
         idx = 0
-        alist = cart(self.la) if a_sel is None else [cart(self.la)[a_sel]]
-        for a in alist:
+        for a in cart(self.la):
             for b in cart(self.lb):
                 for c in cart(self.lc):
                     for d in cart(self.ld):
@@ -282,43 +291,39 @@ class ClassGen:
         lines.extend(outs)
         lines.append("}")
         self.hrr_flops = hfl[0]
-        if a_sel is None:
-            # Register-tiled form: the ket's KP primitives (a compile-time count)
-            # are already in registers, kv[k] = {q, 1/2q, Q, Q - C, K}; the bra
-            # primitive loop is outermost (one set of scalar loads per bra
-            # primitive) and the KP ket primitives inside it are unrolled, so
-            # their independent Boys / recurrence chains interleave.
-            kr = [f"template <typename R, int BS, int KP>\n__device__ __forceinline__ void {fname}_kr(",
-                  "    const PrimPair* __restrict__ bp, int nbp, const R (&kv)[KP][9], const R AB0, const R AB1,",
-                  "    const R AB2, const R CD0, const R CD1, const R CD2, const R* __restrict__ boys_tab,",
-                  "    R* __restrict__ out) {"]
-            for a in acc_name.values():
-                kr.append(f"  R {a} = R(0);")
-            kr += ["#pragma unroll 1",
-                   "  for (int ib = 0; ib < nbp; ++ib) {",
-                   "    const HFX_CONST_AS double* B = (const HFX_CONST_AS double*)(bp + ib);",
-                   "    const R p = R(B[0]), i2p = R(B[1]), Kb = R(B[8]);",
-                   "    const R PA0 = R(B[5]), PA1 = R(B[6]), PA2 = R(B[7]);",
-                   "    const R P0 = R(B[2]), P1 = R(B[3]), P2 = R(B[4]);",
-                   "#pragma unroll",
-                   "    for (int ik = 0; ik < KP; ++ik) {",
-                   "      const R q = kv[ik][0], i2q = kv[ik][1], Kk = kv[ik][8];",
-                   "      const R Q0 = kv[ik][2], Q1 = kv[ik][3], Q2 = kv[ik][4];",
-                   "      const R QC0 = kv[ik][5], QC1 = kv[ik][6], QC2 = kv[ik][7];",
-                   "      const R PQ0 = P0 - Q0, PQ1 = P1 - Q1, PQ2 = P2 - Q2;"]
-            kr += ["      " + x for x in blk[4:]]
-            kr += ["    }", "  }", "  (void)AB0; (void)AB1; (void)AB2; (void)CD0; (void)CD1; (void)CD2;"]
-            kr.extend(hcode)
-            kr.extend(outs)
-            kr.append("}")
-            lines.append("")
-            lines.extend(kr)
+        # Register-tiled form: the ket's KP primitives (a compile-time count)
+        # are already in registers, kv[k] = {q, 1/2q, Q, Q - C, K}; the bra
+        # primitive loop is outermost (one set of scalar loads per bra
+        # primitive) and the KP ket primitives inside it are unrolled, so
+        # their independent Boys / recurrence chains interleave.
+        kr = [f"template <typename R, int BS, int KP>\n__device__ __forceinline__ void {fname}_kr(",
+              "    const PrimPair* __restrict__ bp, int nbp, const R (&kv)[KP][9], const R AB0, const R AB1,",
+              "    const R AB2, const R CD0, const R CD1, const R CD2, const R* __restrict__ boys_tab,",
+              "    R* __restrict__ out) {"]
+        for a in acc_name.values():
+            kr.append(f"  R {a} = R(0);")
+        kr += ["#pragma unroll 1",
+               "  for (int ib = 0; ib < nbp; ++ib) {",
+               "    const HFX_CONST_AS double* B = (const HFX_CONST_AS double*)(bp + ib);",
+               "    const R p = R(B[0]), i2p = R(B[1]), Kb = R(B[8]);",
+               "    const R PA0 = R(B[5]), PA1 = R(B[6]), PA2 = R(B[7]);",
+               "    const R P0 = R(B[2]), P1 = R(B[3]), P2 = R(B[4]);",
+               "#pragma unroll",
+               "    for (int ik = 0; ik < KP; ++ik) {",
+               "      const R q = kv[ik][0], i2q = kv[ik][1], Kk = kv[ik][8];",
+               "      const R Q0 = kv[ik][2], Q1 = kv[ik][3], Q2 = kv[ik][4];",
+               "      const R QC0 = kv[ik][5], QC1 = kv[ik][6], QC2 = kv[ik][7];",
+               "      const R PQ0 = P0 - Q0, PQ1 = P1 - Q1, PQ2 = P2 - Q2;"]
+        kr += ["      " + x for x in blk[4:]]
+        kr += ["    }", "  }", "  (void)AB0; (void)AB1; (void)AB2; (void)CD0; (void)CD1; (void)CD2;"]
+        kr.extend(hcode)
+        kr.extend(outs)
+        kr.append("}")
+        lines.append("")
+        lines.extend(kr)
         return "\n".join(lines)
 
 
-# Classes whose whole integral block is too large for registers are also
-# emitted as passes, one per Cartesian component of shell a.
-PASS_CLASSES = {19, 20}
 # Classes that also get the register-tiled kernels (ket primitives in
 # registers, blocks of bras): low total angular momentum, where the per-ket
 # loads and atomics weigh most against the arithmetic.
@@ -335,41 +340,34 @@ def main(out_dir):
         g = ClassGen(la, lb, lc, ld, cid in UNROLL2)
         fname = f"eri_{PAIR_NAMES[B]}_{PAIR_NAMES[K]}"
         body = g.emit(fname)
-        extra = []
-        if cid in PASS_CLASSES:
-            for k in range(ncart(la)):
-                extra.append(ClassGen(la, lb, lc, ld).emit(f"{fname}_p{k}", a_sel=k))
-            sw = ["template <typename R, int BS = BOYS_ROW, typename SP = double, typename TT = R>",
-                  f"__device__ __forceinline__ void {fname}_pass(int k, const SP* __restrict__ bp, int nbp,",
-                  "    const SP* __restrict__ kq0, int kfs, int kps, int nkp, const R AB0, const R AB1,",
-                  "    const R AB2, const R CD0, const R CD1, const R CD2, const TT* __restrict__ boys_tab,",
-                  "    R* __restrict__ out) {", "  switch (k) {"]
-            for k in range(ncart(la)):
-                sw.append(f"    case {k}: {fname}_p{k}<R, BS, SP, TT>(bp, nbp, kq0, kfs, kps, nkp, AB0, AB1, AB2, CD0, "
-                          "CD1, CD2, boys_tab, out); break;")
-            sw += ["    default: break;", "  }", "}"]
-            extra.append("\n".join(sw))
-        hdr = ["// Generated by gen_eri.py: Obara-Saika / Head-Gordon-Pople evaluator.",
-               f"// class {cid}: ({PAIR_NAMES[B]}|{PAIR_NAMES[K]}), L = {g.L}", "#pragma once",
-               '#include "../hfx_internal.h"', "", body, ""] + extra + [""]
-        with open(os.path.join(out_dir, f"eri_class_{cid:02d}.h"), "w") as fh:
-            fh.write("\n".join(hdr))
-        macro = "HFX_CLASS_TU_PASSES" if cid in PASS_CLASSES else "HFX_CLASS_TU"
-        tu = [f"// Generated by gen_eri.py: kernels of class {cid} ({PAIR_NAMES[B]}|{PAIR_NAMES[K]}).",
-              f'#include "eri_class_{cid:02d}.h"', '#include "../eri_impl.h"', "",
-              f"{macro}({cid}, {fname}, {la}, {lb}, {lc}, {ld}, {wg_size(cid)}, {wg_alt(cid)})",
-              f"HFX_CLASS_KR({cid})" if cid in KR_CLASSES else f"HFX_CLASS_NO_KR({cid})", ""]
+        head = f"// Generated by gen_eri.py: kernels of class {cid} ({PAIR_NAMES[B]}|{PAIR_NAMES[K]})."
+        dims = f"{cid}, {la}, {lb}, {lc}, {ld}, {wg_size(cid)}"
+        if cid in RYS_CLASSES:   # no evaluator of its own: FP64 only where FP64_ONLY says so
+            tu = [head, '#include "../eri_impl.h"', '#include "../eri_rys.h"', "",
+                  f"HFX_CLASS_TU_RYS({dims}, {RYS_CLASSES[cid]}, {'true' if cid in FP64_ONLY else 'false'})",
+                  f"HFX_SCHWARZ_RYS({cid})" if B == K else f"HFX_NO_SCHWARZ({cid})", ""]
+        else:
+            hdr = ["// Generated by gen_eri.py: Obara-Saika / Head-Gordon-Pople evaluator.",
+                   f"// class {cid}: ({PAIR_NAMES[B]}|{PAIR_NAMES[K]}), L = {g.L}", "#pragma once",
+                   '#include "../hfx_internal.h"', "", body, ""]
+            with open(os.path.join(out_dir, f"eri_class_{cid:02d}.h"), "w") as fh:
+                fh.write("\n".join(hdr))
+            tu = [head, f'#include "eri_class_{cid:02d}.h"', '#include "../eri_impl.h"', "",
+                  f"HFX_CLASS_TU({cid}, {fname}, {la}, {lb}, {lc}, {ld}, {wg_size(cid)}, {wg_alt(cid)})",
+                  f"HFX_CLASS_KR({cid})" if cid in KR_CLASSES else f"HFX_CLASS_NO_KR({cid})", ""]
         with open(os.path.join(out_dir, f"eri_class_{cid:02d}.hip"), "w") as fh:
             fh.write("\n".join(tu))
         table.append((cid, B, K, la, lb, lc, ld, g.flops, g.hrr_flops, fname))
     parts = ["// Generated by gen_eri.py: class table.", "#pragma once", "",
-             "struct EriClassInfo { int B, K, la, lb, lc, ld, vrr_flops_per_prim, hrr_flops, wgs, wgs_alt; };",
+             "struct EriClassInfo { int B, K, la, lb, lc, ld, vrr_flops_per_prim, hrr_flops, wgs, wgs_alt, rys; };",
              "static const EriClassInfo kEriClassInfo[21] = {"]
     for (cid, B, K, la, lb, lc, ld, fl, hfl, fname) in table:
-        parts.append(f"  {{{B}, {K}, {la}, {lb}, {lc}, {ld}, {fl}, {hfl}, {wg_size(cid)}, {wg_alt(cid)}}},  // {fname}")
+        parts.append(f"  {{{B}, {K}, {la}, {lb}, {lc}, {ld}, {fl}, {hfl}, {wg_size(cid)}, {wg_alt(cid)}, "
+                     f"{int(cid in RYS_CLASSES)}}},  // {fname}")
     parts.append("};")
     parts.append("")
     parts.append("#define HFX_FOR_EACH_CID(X) " + " ".join(f"X({cid})" for cid in range(21)))
+    parts.append("#define HFX_FOR_EACH_RYS(X) " + " ".join(f"X({cid})" for cid in sorted(RYS_CLASSES)))
     parts.append("")
     with open(os.path.join(out_dir, "eri_classes.h"), "w") as fh:
         fh.write("\n".join(parts))

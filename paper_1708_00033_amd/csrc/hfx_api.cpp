@@ -55,6 +55,16 @@ static const int kPairL[6][2] = {{0, 0}, {1, 0}, {1, 1}, {2, 0}, {2, 1}, {2, 2}}
 
 static hfx_status replan(hfx_ctx* c);
 
+// The quadrature table of a cooperative class (null for the others): L/2 + 1 points.
+static const double* rys_block_of(const hfx_ctx* c, int cid) {
+    if (!hfx_class_is_rys(cid)) return nullptr;
+    int B = 0;
+    while ((B + 1) * (B + 2) / 2 <= cid) ++B;
+    const int K = cid - B * (B + 1) / 2;
+    const int L = kPairL[B][0] + kPairL[B][1] + kPairL[K][0] + kPairL[K][1];
+    return c->d_rys + rys_block(L / 2 + 1);
+}
+
 constexpr int kXcds = 8;   // XCDs of an MI355X: private digestion keeps one copy of W per XCD
 
 // A captured build replays the launch arguments (plans, task buffers,
@@ -230,12 +240,18 @@ extern "C" hfx_status hfx_create(const hfx_options* opt, hfx_ctx** out) {
     }
     std::vector<double> tab((size_t)BOYS_TAB_ENTRIES);
     hfx_boys_table(tab.data());
-    if (dalloc(&c->d_boys64, tab.size()) != hipSuccess || dalloc(&c->d_dmax, 1) != hipSuccess ||
-        dalloc(&c->d_counters, HFX_CNT_WORDS + 1) != hipSuccess) {
+    static const std::vector<double> rys = [] {   // about 25 ms: once per process
+        std::vector<double> t((size_t)RYS_TAB_ENTRIES);
+        hfx_rys_table(t.data());
+        return t;
+    }();
+    if (dalloc(&c->d_boys64, tab.size()) != hipSuccess || dalloc(&c->d_rys, rys.size()) != hipSuccess ||
+        dalloc(&c->d_dmax, 1) != hipSuccess || dalloc(&c->d_counters, HFX_CNT_WORDS + 1) != hipSuccess) {
         hfx_destroy(c);
         return HFX_ERR_OOM;
     }
-    if (hipMemcpy(c->d_boys64, tab.data(), tab.size() * 8, hipMemcpyHostToDevice) != hipSuccess) {
+    if (hipMemcpy(c->d_boys64, tab.data(), tab.size() * 8, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(c->d_rys, rys.data(), rys.size() * 8, hipMemcpyHostToDevice) != hipSuccess) {
         hfx_destroy(c);
         return HFX_ERR_DEVICE;
     }
@@ -265,6 +281,7 @@ extern "C" void hfx_destroy(hfx_ctx* c) {
     (void)hipSetDevice(c->opt.device);
     release_system(c);
     dfree(c->d_boys64);
+    dfree(c->d_rys);
     dfree(c->d_dmax);
     dfree(c->d_counters);
     c->d_bad = nullptr;
@@ -318,8 +335,12 @@ static hfx_status plan_sub(hfx_ctx* c, int B, int li, const std::vector<PairInfo
     P.K = K;
     P.list = li;
     const double tau = c->opt.schwarz_tau;
-    const int TQ = c->tune_tq[P.cid] > 0 ? c->tune_tq[P.cid] : c->opt.task_quartets;
-    const bool stripe = c->tune_stripe[P.cid] >= 0 ? c->tune_stripe[P.cid] != 0 : true;
+    P.rys = hfx_class_is_rys(P.cid) != 0;
+    int TQ = c->tune_tq[P.cid] > 0 ? c->tune_tq[P.cid] : c->opt.task_quartets;
+    bool stripe = c->tune_stripe[P.cid] >= 0 ? c->tune_stripe[P.cid] != 0 : true;
+    if (P.rys) {
+        stripe = false;   // too few kets per bra
+    }
     // bra r (molecule m) meets the kets of its own molecule's groups; in
     // each group the kets with Q_s Q_r >= tau are a prefix (Q descending),
     // and for B == K so are the kets not after the bra in the class order
@@ -353,6 +374,15 @@ static hfx_status plan_sub(hfx_ctx* c, int B, int li, const std::vector<PairInfo
             P.prim += (long long)bras[r].nprim * (long long)KL.kp * (long long)n;
         }
     }
+    if (P.rys) {
+        // a cooperative workgroup spends microseconds on a batch of kets, and a
+        // molecule has few d-d and d-p bras: tasks of 4 to 48 batches, short
+        // enough that there are about eight per CU (a task also clears and
+        // flushes the bra's rows of W, which 4 batches outweigh)
+        const int nk = hfx_class_rys_kets(P.cid);
+        const long long batches = P.quartets / nk / (8 * 256);
+        TQ = std::min(TQ, nk * (int)std::min<long long>(48, std::max<long long>(4, batches)));
+    }
     const int nint = ncart(kPairL[B][0]) * ncart(kPairL[B][1]) * ncart(kPairL[K][0]) * ncart(kPairL[K][1]);
     P.integrals = P.quartets * nint;
     // Tasks, striped over the 8 XCDs (workgroup i runs on XCD i mod 8, each
@@ -362,14 +392,16 @@ static hfx_status plan_sub(hfx_ctx* c, int B, int li, const std::vector<PairInfo
     // Queues are interleaved (task 8k + j = queue j's k-th entry) and padded
     // with empty tasks (r = -1).
     P.lds_bytes = (size_t)(ncart(kPairL[B][0]) + ncart(kPairL[B][1])) * c->rs * sizeof(double);
-    P.fp64_only = nint >= 600;   // see ClassKernels in eri_impl.h
-    P.lds_tab = (size_t)boys_lds_bytes();   // FP64 rows (the mixed kernels' FP32 part reads them too)
+    P.fp64_only = nint >= 600;   // a d-d bra with a d-d or d-p ket: no FP32 kernels
+    // FP64 rows (the mixed kernels' FP32 part reads them too); the cooperative kernels read their table from memory
+    P.lds_tab = P.rys ? (size_t)hfx_class_rys_lds(P.cid, 0, 1) : (size_t)boys_lds_bytes();
     const int digest = c->tune_digest[P.cid] >= 0 ? c->tune_digest[P.cid] : c->opt.digest;
     // 160 KiB of LDS per workgroup, less room for the persistent kernel's static counter
     constexpr size_t kLdsBudget = 160 * 1024 - 256;
     const bool lds_digest = digest == HFX_DIGEST_LDS || digest == HFX_DIGEST_LDS_D;
     P.mode = (lds_digest && P.lds_bytes + P.lds_tab <= kLdsBudget) ? 0 : 1;
     P.priv = digest == HFX_DIGEST_PRIVATE;   // global-atomic kernels into the per-XCD copies
+    if (P.rys) P.lds_tab = (size_t)hfx_class_rys_lds(P.cid, P.mode, 1);
     // D' rows staged too: both shells' rows when they fit, else shell a's
     // (the larger set); only for classes with small integral blocks and
     // whole rows (with column windows a task covers one pair of windows, and
@@ -473,7 +505,7 @@ static hfx_status plan_sub(hfx_ctx* c, int B, int li, const std::vector<PairInfo
     P.persist = c->tune_persist[P.cid] > 0;
     // one task per wave: each wave of the workgroup needs its own bra rows
     P.wave = 0;
-    if (c->tune_persist[P.cid] == 2) {
+    if (c->tune_persist[P.cid] == 2 && !P.rys) {
         P.wave = WGS / 64;
         if (P.lds() > 160 * 1024 - 256) P.wave = 0;   // does not fit: one task per workgroup
     }
@@ -484,7 +516,8 @@ static hfx_status plan_sub(hfx_ctx* c, int B, int li, const std::vector<PairInfo
         P.nblocks[0] = P.nblocks[1] = ((nb + 7) / 8) * 8;
     }
     for (int mx = 0; mx < (P.kr ? 0 : (P.fp64_only ? 1 : 2)); ++mx) {
-        int nb = hfx_class_resident_blocks(P.cid, P.alt, P.wave > 0, P.mode, mx, P.dstage, P.lds());
+        int nb = P.rys ? hfx_class_resident_blocks_rys(P.cid, P.mode, mx, P.lds())
+                       : hfx_class_resident_blocks(P.cid, P.alt, P.wave > 0, P.mode, mx, P.dstage, P.lds());
         if (nb <= 0) return hfx_fail(c, HFX_ERR_DEVICE, "occupancy query of a class kernel failed");
         nb = std::min(nb, P.ntask);
         P.nblocks[mx] = ((nb + 7) / 8) * 8;   // whole rounds over the 8 XCDs
@@ -844,7 +877,8 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
         HIPCK(dalloc(&dp, L.size()));
         HIPCK(dalloc(&dq, L.size()));
         HIPCK(hipMemcpy(dp, L.data(), L.size() * sizeof(PairInfo), hipMemcpyHostToDevice));
-        HIPCK(hfx_launch_schwarz(class_id(B, B), dp, (int)L.size(), c->d_prim, c->d_boys64, dq, 0));
+        HIPCK(hfx_launch_schwarz(class_id(B, B), dp, (int)L.size(), c->d_prim, c->d_boys64,
+                                 rys_block_of(c, class_id(B, B)), dq, 0));
         std::vector<double> q(L.size());
         HIPCK(hipMemcpy(q.data(), dq, q.size() * sizeof(double), hipMemcpyDeviceToHost));
         dfree(dp);
@@ -1297,6 +1331,7 @@ hfx_status hfx_build_with(hfx_ctx* c, const BuildBufs& bufs, const double* dD, d
         a.moff = c->d_moff;
         a.tasks = P.d_tasks;
         a.boys64 = c->d_boys64;
+        a.rys = rys_block_of(c, cid);
         a.D = bufs.Dp;
         a.W = P.priv ? c->d_Wrep : bufs.W;
         a.wrep = P.priv ? (long long)nn : 0;
@@ -1324,12 +1359,14 @@ hfx_status hfx_build_with(hfx_ctx* c, const BuildBufs& bufs, const double* dD, d
         if (P.kr) {
             HIPCK(hfx_launch_class_kr(cid, P.mode, KL.kp, P.nbl, P.nblocks[0], P.lds(), ps, &a));
         } else if (P.persist) {
-            HIPCK(hfx_launch_class(cid, P.alt, P.wave > 0, P.mode, m, P.nblocks[m], P.lds(), ps, &a));
+            if (P.rys) HIPCK(hfx_launch_class_rys(cid, P.mode, m, 0, P.nblocks[m], P.lds(), ps, &a));
+            else HIPCK(hfx_launch_class(cid, P.alt, P.wave > 0, P.mode, m, P.nblocks[m], P.lds(), ps, &a));
         } else {
             for (int off = 0; off < P.ntask; off += kMaxGroups) {
                 a.task_off = off;
-                HIPCK(hfx_launch_class(cid, P.alt, 0, P.mode, m, std::min(kMaxGroups, P.ntask - off), P.lds(), ps,
-                                       &a));
+                const int nb = std::min(kMaxGroups, P.ntask - off);
+                if (P.rys) HIPCK(hfx_launch_class_rys(cid, P.mode, m, 0, nb, P.lds(), ps, &a));
+                else HIPCK(hfx_launch_class(cid, P.alt, 0, P.mode, m, nb, P.lds(), ps, &a));
             }
         }
         if (c->timing && P.ev1) {
@@ -1431,6 +1468,16 @@ extern "C" hfx_status hfx_build_jk_multi_dev(hfx_ctx* c, int ndens, const double
     for (size_t pi = 0; pi < c->plans.size(); ++pi) {
         const SubPlan& P = c->plans[pi];
         const size_t budget = 160 * 1024 - 256;
+        if (P.rys) {   // small sums per density in both modes, row sets in MODE 0
+            gmode[pi] = P.mode == 0 && !P.priv ? 0 : 1;
+            const size_t one = (size_t)hfx_class_rys_lds(P.cid, gmode[pi], 1);
+            const size_t per = (size_t)hfx_class_rys_lds(P.cid, gmode[pi], 2) - one + 8 +
+                               (gmode[pi] == 0 ? P.lds_bytes : 0);
+            const size_t fit = 1 + (budget - one - (gmode[pi] == 0 ? P.lds_bytes : 0)) / per;
+            group[pi] = (int)std::min<size_t>(fit, (size_t)ndens);
+            nwork += 8 * (size_t)((ndens + group[pi] - 1) / group[pi]);
+            continue;
+        }
         const size_t fit = P.lds_tab < budget ? (budget - P.lds_tab) / std::max<size_t>(1, P.lds_bytes) : 0;
         const bool lds = P.mode == 0 && !P.priv && fit >= 1;
         gmode[pi] = lds ? 0 : 1;
@@ -1478,6 +1525,7 @@ extern "C" hfx_status hfx_build_jk_multi_dev(hfx_ctx* c, int ndens, const double
         a.tasks = P.d_tasks;
         a.moff = c->d_moff;
         a.boys64 = c->d_boys64;
+        a.rys = rys_block_of(c, P.cid);
         a.D = Dp;
         a.W = WJ;
         a.WK = WK;
@@ -1506,8 +1554,12 @@ extern "C" hfx_status hfx_build_jk_multi_dev(hfx_ctx* c, int ndens, const double
             b.wket = KL.d_wket_multi + (size_t)d0 * a.kstride;
             b.work = c->d_multi_work + wofs;
             wofs += 8;
-            const size_t lds = P.lds_tab + (gmode[pi] == 0 ? (size_t)b.ndens * P.lds_bytes : 0);
-            HIPCK(hfx_launch_class_multi(P.cid, gmode[pi], nblocks, lds, ps, &b));
+            const size_t rows = gmode[pi] == 0 ? (size_t)b.ndens * P.lds_bytes : 0;
+            if (P.rys)
+                HIPCK(hfx_launch_class_rys(P.cid, gmode[pi], 0, 1, nblocks,
+                                           (size_t)hfx_class_rys_lds(P.cid, gmode[pi], b.ndens) + rows, ps, &b));
+            else
+                HIPCK(hfx_launch_class_multi(P.cid, gmode[pi], nblocks, P.lds_tab + rows, ps, &b));
         }
     }
     HIPCK(join_streams(c, ns, st));

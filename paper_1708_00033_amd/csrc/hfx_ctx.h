@@ -45,7 +45,7 @@ struct SubPlan {
     size_t lds_bytes = 0;     // bra rows F_I, F_J (LDS digestion)
     size_t lds_dst = 0;       // the bra's staged D' rows (LDS digestion with D rows)
     int dstage = 0;           // ClassArgs::dstage: bit 0 shell a's D' rows staged, bit 1 shell b's
-    size_t lds_tab = 0;       // the class's FP64 Boys rows in LDS
+    size_t lds_tab = 0;       // the class's FP64 Boys rows in LDS (rys: integrals and small sums)
     int mode = 0;             // digestion actually used (LDS may fall back to global)
     // timing (when enabled): events around this launch, summed milliseconds
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -57,6 +57,7 @@ struct SubPlan {
     size_t lds() const { return (mode == 0 ? (lds_bytes + lds_dst) * (wave ? wave : nbl) : 0) + lds_tab; }
     bool persist = false;     // persistent launch through per-XCD work counters
     int wave = 0;             // > 0: one task per wave (persistent), this many waves per workgroup
+    bool rys = false;         // cooperative Rys kernel
     bool kr = false;          // register-tiled persistent kernel (ket primitives in registers), FP64
     bool priv = false;        // private digestion: global atomics into the per-XCD copies of W
     int nbl = 1;              // bras per task (register-tiled blocks of Q-adjacent bras)
@@ -129,6 +130,7 @@ struct hfx_ctx {
     unsigned long long* d_work = nullptr;        // 8 queue counters per plan (16 apart)
     std::vector<double> Qshell;         // nshell x nshell Schwarz bounds (host)
     double* d_boys64 = nullptr;
+    double* d_rys = nullptr;            // Rys quadrature tables
     double* d_cscale = nullptr;
     double* d_S = nullptr;
     double* d_H = nullptr;
@@ -232,5 +234,11 @@ int hfx_class_resident_blocks_kr(int cid, int mode, int kp, int nbl, size_t lds_
 hipError_t hfx_launch_class_multi(int cid, int mode, int nblocks, size_t lds_bytes, hipStream_t stream,
                                   const ClassArgs* args);
 hipError_t hfx_launch_schwarz(int cid, const PairInfo* pairs, int npairs, const PrimPair* prim, const double* boys,
-                              double* Q, hipStream_t stream);
+                              const double* rys, double* Q, hipStream_t stream);
+int hfx_class_is_rys(int cid);
+int hfx_class_rys_lds(int cid, int mode, int ndens);
+int hfx_class_rys_kets(int cid);
+hipError_t hfx_launch_class_rys(int cid, int mode, int mixed, int multi, int nblocks, size_t lds_bytes,
+                                hipStream_t stream, const ClassArgs* args);
+int hfx_class_resident_blocks_rys(int cid, int mode, int mixed, size_t lds_bytes);
 }

@@ -76,6 +76,7 @@ struct ClassArgs {
     int qlen;                           // entries per XCD queue (tasks = 8 qlen)
     const long long* __restrict__ moff; // per molecule: element offset of its blocks in D', W
     const double* __restrict__ boys64;
+    const double* __restrict__ rys;     // cooperative classes: the quadrature table of their point count
     const double* __restrict__ D;       // component-scaled density D'
     double* __restrict__ W;             // accumulator, F_2e = s (W + W^T) s / 8
     double* __restrict__ wket;          // LDS mode: ket-block J sums, [component][ket position]
@@ -141,6 +142,26 @@ __host__ __device__ constexpr int boys_block(int L) { return L == 0 ? 1 : (L == 
 #define BOYS_EXP_SLOT 8
 __host__ __device__ constexpr int boys_entries() { return BOYS_NT * BOYS_ROW; }
 __host__ __device__ constexpr int boys_lds_bytes() { return BOYS_NT * BOYS_LROW64 * 8; }
+
+// ---- Rys quadrature tables ----------------------------------------------------
+// For n = RYS_NMIN..RYS_NMAX points, over T in [0, RYS_NT): per unit interval
+// k and point r one row of RYS_NC coefficients of the root x_r = t_r^2 in
+// powers of z = 2 (T - k) - 1, then RYS_NC of the weight w_r (12 coefficients:
+// moments to 2e-15 relative, the rounding of the sums; 11 give 5e-15, 10 give
+// 2e-13); after the intervals the n pairs (h_r, v_r) of the asymptotic
+// x_r = h_r / T, w_r = v_r / sqrt(T).
+#define RYS_NMIN 4
+#define RYS_NMAX 5
+#define RYS_NT 60
+#define RYS_NC 12
+#define RYS_ROW (2 * RYS_NC)
+__host__ __device__ constexpr int rys_block(int n) {   // first entry of the n-point block
+    int o = 0;
+    for (int k = RYS_NMIN; k < n; ++k) o += RYS_NT * k * RYS_ROW + 2 * RYS_NMAX;
+    return o;
+}
+#define RYS_TAB_ENTRIES (rys_block(RYS_NMAX + 1))
+void hfx_rys_table(double* tab);   // host, RYS_TAB_ENTRIES entries
 
 __device__ __forceinline__ double hfx_sqrt(double x) { return sqrt(x); }
 // 1/sqrt(x) for x > 0: hardware estimate refined by Newton steps

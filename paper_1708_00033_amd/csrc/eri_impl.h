@@ -284,13 +284,13 @@ __device__ __forceinline__ void flush_counts(const ClassArgs& a, unsigned c64, u
 // in FP64, the rest, a suffix of its Q-sorted range, in FP32 widened to FP64
 // before digestion, both in the same launch and into the same LDS rows).
 //
-// LDS of a class kernel: the class's FP64 Boys rows (padded rows,
-// BOYS_LROW64 apart; the FP32 evaluation rounds their coefficients), then
+// LDS of a class kernel: the class's FP64 Boys rows (the FP32 evaluation
+// rounds their coefficients), then
 // (MODE 0) the bra rows F_I, F_J of the current task.
 template <class E>
 struct LdsLayout {
     static constexpr int L = E::LA + E::LB + E::LC + E::LD;
-    static constexpr int ROWS = BOYS_NT * BOYS_LROW64;   // offset of the bra rows, doubles
+    static constexpr int ROWS = boys_rows(L) * BOYS_ROW;   // offset of the bra rows, doubles
 };
 
 // Uniform per workgroup: padding tasks (XCD striping) and other shards' bras do nothing.
@@ -301,10 +301,9 @@ __device__ __forceinline__ bool task_active(const ClassArgs& a, const int4 task)
 template <class E>
 __device__ __forceinline__ void load_boys_lds(const ClassArgs& a, double* t64) {
     using LL = LdsLayout<E>;
-    const double* __restrict__ g64 = a.boys64 + (size_t)boys_block(LL::L) * BOYS_NT * BOYS_ROW;
-    for (int i = threadIdx.x; i < boys_entries(); i += E::WGS)
-        t64[(i / BOYS_ROW) * BOYS_LROW64 + i % BOYS_ROW] = g64[i];
-    for (int k = threadIdx.x; k < BOYS_NT; k += E::WGS) t64[k * BOYS_LROW64 + BOYS_EXP_SLOT] = a.boys64[BOYS_EXP_OFF + k];
+    const double2* __restrict__ g = reinterpret_cast<const double2*>(a.boys64 + boys_block(LL::L));
+    double2* t = reinterpret_cast<double2*>(t64);
+    for (int i = threadIdx.x; i < LL::ROWS / 2; i += E::WGS) t[i] = g[i];
     __syncthreads();
 }
 
@@ -407,13 +406,13 @@ __device__ __forceinline__ void class_task(const ClassArgs& a, const int ti, con
         if (s >= (lo ? split : send)) continue;   // the part's last, partial slot
         double I[NI];
         if (!FP32 || lo) {
-            E::template run<double, BOYS_LROW64>((const double*)(a.prim + bra.prim_off), bra.nprim, a.kprim + s,
+            E::template run<double>((const double*)(a.prim + bra.prim_off), bra.nprim, a.kprim + s,
                                                  kfs, kps, a.knprim, bra.AB, a.ket[s].AB, t64, I);
             ++n64;
         } else if constexpr (FP32) {
             // FP32 primitive copies, the FP64 Boys rows rounded
             float If[NI];
-            E::template run<float, BOYS_LROW64>(a.prim32 + (size_t)bra.prim_off * HFX_PRIM_FIELDS, bra.nprim,
+            E::template run<float>(a.prim32 + (size_t)bra.prim_off * HFX_PRIM_FIELDS, bra.nprim,
                                                 a.kprim32 + s, kfs, kps, a.knprim, bra.AB, a.ket[s].AB, t64, If);
 #pragma unroll
             for (int i = 0; i < NI; ++i) I[i] = (double)If[i];
@@ -541,7 +540,7 @@ __device__ __forceinline__ void class_task_kr(const ClassArgs& a, const int ti, 
             if (!(qs * bra[i].Q >= a.tau) || ks > r0 + i) continue;
             const double g = sbra[i] * gk * ((kb.z == bra[i].a && kb.w == bra[i].b) ? 1.0 : 2.0);
             double I[NI];
-            E::template run_kr<double, BOYS_LROW64, KP>(a.prim + bra[i].prim_off, bra[i].nprim, kv, bra[i].AB, kab,
+            E::template run_kr<double, KP>(a.prim + bra[i].prim_off, bra[i].nprim, kv, bra[i].AB, kab,
                                                         t64, I);
             ++n64;
             hit = true;
@@ -674,7 +673,7 @@ __device__ __forceinline__ void class_task_multi(const ClassArgs& a, const int t
             const double g = sbra * (kb.z != kb.w ? 2.0 : 1.0) * ((kb.z == bra.a && kb.w == bra.b) ? 1.0 : 2.0);
             double I[NI];
             if (valid) {
-                E::template run<double, BOYS_LROW64>((const double*)(a.prim + bra.prim_off), bra.nprim, a.kprim + s,
+                E::template run<double>((const double*)(a.prim + bra.prim_off), bra.nprim, a.kprim + s,
                                                      a.nket_list * a.knprim, a.nket_list, a.knprim, bra.AB, a.ket[s].AB,
                                                      t64, I);
                 ++n64;
@@ -843,7 +842,7 @@ __global__ __launch_bounds__(HFX_WG) void k_schwarz(const PairInfo* __restrict__
     // ket read from the array-of-structures layout: field stride 1, primitive stride 10 doubles
     E::template run<double>((const double*)(prim + pr.prim_off), pr.nprim, (const double*)(prim + pr.prim_off), 1,
                             (int)(sizeof(PrimPair) / sizeof(double)), pr.nprim, pr.AB, pr.AB,
-                            boys + (size_t)boys_block(E::LA + E::LB + E::LC + E::LD) * BOYS_NT * BOYS_ROW, I);
+                            boys + boys_block(E::LA + E::LB + E::LC + E::LD), I);
     double mx = 0.0;
 #pragma unroll
     for (int m = 0; m < NA; ++m)
@@ -938,19 +937,19 @@ struct ClassKernelsKr {
 #define HFX_CLASS_TU(cid, fname, la_, lb_, lc_, ld_, wgs_, wgs_alt_)                                               \
     struct Eval##cid {                                                                                 \
         static constexpr int LA = la_, LB = lb_, LC = lc_, LD = ld_, WGS = wgs_;                       \
-        template <typename R, int BS = BOYS_ROW, typename SP = double, typename TT = R>                \
+        template <typename R, typename SP = double>                                                    \
         __device__ __forceinline__ static void run(const SP* bp, int nbp, const SP* kq0, int kfs,      \
                                                    int kps, int nkp, const double* ab,                 \
-                                                   const double* cd, const TT* tab, R* out) {          \
-            fname<R, BS, SP, TT>(bp, nbp, kq0, kfs, kps, nkp, R(ab[0]), R(ab[1]), R(ab[2]), R(cd[0]),  \
-                                 R(cd[1]), R(cd[2]), tab, out);                                        \
+                                                   const double* cd, const double* tab, R* out) {      \
+            fname<R, SP>(bp, nbp, kq0, kfs, kps, nkp, R(ab[0]), R(ab[1]), R(ab[2]), R(cd[0]),          \
+                         R(cd[1]), R(cd[2]), tab, out);                                                \
         }                                                                                              \
-        template <typename R, int BS, int KP>                                                          \
+        template <typename R, int KP>                                                                  \
         __device__ __forceinline__ static void run_kr(const PrimPair* bp, int nbp,                     \
                                                       const R (&kv)[KP][9], const double* ab,          \
-                                                      const double* cd, const R* tab, R* out) {        \
-            fname##_kr<R, BS, KP>(bp, nbp, kv, R(ab[0]), R(ab[1]), R(ab[2]), R(cd[0]), R(cd[1]),       \
-                                  R(cd[2]), tab, out);                                                 \
+                                                      const double* cd, const double* tab, R* out) {   \
+            fname##_kr<R, KP>(bp, nbp, kv, R(ab[0]), R(ab[1]), R(ab[2]), R(cd[0]), R(cd[1]),           \
+                              R(cd[2]), tab, out);                                                     \
         }                                                                                              \
     };                                                                                                 \
     struct Eval##cid##A : Eval##cid {                                                                   \

@@ -216,12 +216,12 @@ class ClassGen:
         lines = []
         L = self.L
         # R: evaluation precision; SP: storage of the primitive data (the FP32
-        # evaluation reads FP32 copies); TT: the Boys table rows
-        lines.append("template <typename R, int BS = BOYS_ROW, typename SP = double, typename TT = R>")
+        # evaluation reads FP32 copies)
+        lines.append("template <typename R, typename SP = double>")
         lines.append(f"__device__ __forceinline__ void {fname}(")
         lines.append("    const SP* __restrict__ bp, int nbp, const SP* __restrict__ kq0, int kfs, int kps,")
         lines.append("    int nkp, const R AB0, const R AB1, const R AB2, const R CD0, const R CD1, const R CD2,")
-        lines.append("    const TT* __restrict__ boys_tab, R* __restrict__ out) {")
+        lines.append("    const double* __restrict__ boys_tab, R* __restrict__ out) {")
         for a in acc_name.values():
             lines.append(f"  R {a} = R(0);")
         lines.append("  // ket primitives (per lane, structure of arrays: field stride kfs, primitive stride kps)")
@@ -239,15 +239,19 @@ class ClassGen:
                "const R p = R(B[0]), i2p = R(B[1]), Kb = R(B[8]);",
                "const R PA0 = R(B[5]), PA1 = R(B[6]), PA2 = R(B[7]);",
                "const R PQ0 = R(B[2]) - Q0, PQ1 = R(B[3]) - Q1, PQ2 = R(B[4]) - Q2;",
-               "const R rs = hfx_rsqrt(p + q);   // 1/sqrt(p+q)",
-               "const R ipq = rs * rs;",
-               "const R rho = p * q * ipq;",
-               "const R T = rho * (PQ0 * PQ0 + PQ1 * PQ1 + PQ2 * PQ2);",
-               "const R pref = Kb * Kk * rs;",
-               f"R F[{L + 1}];",
-               f"boys_eval<R, {L}, BS>(T, F, boys_tab);"]
+               ]
+        if L == 0:   # F_0 / sqrt(p + q) in one step
+            blk.append("const R F0s = Kb * Kk * boys_zero(p + q, p * q * (PQ0 * PQ0 + PQ1 * PQ1 + PQ2 * PQ2), boys_tab);")
+        else:
+            blk += ["const R rs = hfx_rsqrt(p + q);   // 1/sqrt(p+q)",
+                    "const R ipq = rs * rs;",
+                    "const R rho = p * q * ipq;",
+                    "const R T = rho * (PQ0 * PQ0 + PQ1 * PQ1 + PQ2 * PQ2);",
+                    "const R pref = Kb * Kk * rs;",
+                    f"R F[{L + 1}];",
+                    f"boys_eval<R, {L}>(T, F, boys_tab);"]
         body = list(self.vrr_code)
-        base = [f"const R b{m} = pref * F[{m}];" for m in sorted(self.base_used)]
+        base = ["const R b0 = F0s;"] if L == 0 else [f"const R b{m} = pref * F[{m}];" for m in sorted(self.base_used)]
         if L > 0:
             blk += ["const R WP0 = -q * ipq * PQ0, WP1 = -q * ipq * PQ1, WP2 = -q * ipq * PQ2;",
                     "const R WQ0 = p * ipq * PQ0, WQ1 = p * ipq * PQ1, WQ2 = p * ipq * PQ2;",
@@ -296,7 +300,7 @@ class ClassGen:
         # primitive loop is outermost (one set of scalar loads per bra
         # primitive) and the KP ket primitives inside it are unrolled, so
         # their independent Boys / recurrence chains interleave.
-        kr = [f"template <typename R, int BS, int KP>\n__device__ __forceinline__ void {fname}_kr(",
+        kr = [f"template <typename R, int KP>\n__device__ __forceinline__ void {fname}_kr(",
               "    const PrimPair* __restrict__ bp, int nbp, const R (&kv)[KP][9], const R AB0, const R AB1,",
               "    const R AB2, const R CD0, const R CD1, const R CD2, const R* __restrict__ boys_tab,",
               "    R* __restrict__ out) {"]

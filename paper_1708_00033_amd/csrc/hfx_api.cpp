@@ -55,14 +55,17 @@ static const int kPairL[6][2] = {{0, 0}, {1, 0}, {1, 1}, {2, 0}, {2, 1}, {2, 2}}
 
 static hfx_status replan(hfx_ctx* c);
 
-// The quadrature table of a cooperative class (null for the others): L/2 + 1 points.
-static const double* rys_block_of(const hfx_ctx* c, int cid) {
-    if (!hfx_class_is_rys(cid)) return nullptr;
+// Total angular momentum of a class.
+static int class_L(int cid) {
     int B = 0;
     while ((B + 1) * (B + 2) / 2 <= cid) ++B;
     const int K = cid - B * (B + 1) / 2;
-    const int L = kPairL[B][0] + kPairL[B][1] + kPairL[K][0] + kPairL[K][1];
-    return c->d_rys + rys_block(L / 2 + 1);
+    return kPairL[B][0] + kPairL[B][1] + kPairL[K][0] + kPairL[K][1];
+}
+
+// The quadrature table of a cooperative class (null for the others): L/2 + 1 points.
+static const double* rys_block_of(const hfx_ctx* c, int cid) {
+    return hfx_class_is_rys(cid) ? c->d_rys + rys_block(class_L(cid) / 2 + 1) : nullptr;
 }
 
 constexpr int kXcds = 8;   // XCDs of an MI355X: private digestion keeps one copy of W per XCD
@@ -238,9 +241,12 @@ extern "C" hfx_status hfx_create(const hfx_options* opt, hfx_ctx** out) {
         for (int k = 0; k < 21 && ok; ++k) ok = r.scratch[k] <= kScratchBudget;
         if (!ok) { delete c; return HFX_ERR_DEVICE; }
     }
-    std::vector<double> tab((size_t)BOYS_TAB_ENTRIES);
-    hfx_boys_table(tab.data());
-    static const std::vector<double> rys = [] {   // about 25 ms: once per process
+    static const std::vector<double> tab = [] {   // tens of milliseconds each: once per process
+        std::vector<double> t((size_t)BOYS_TAB_ENTRIES);
+        hfx_boys_table(t.data());
+        return t;
+    }();
+    static const std::vector<double> rys = [] {
         std::vector<double> t((size_t)RYS_TAB_ENTRIES);
         hfx_rys_table(t.data());
         return t;
@@ -394,7 +400,7 @@ static hfx_status plan_sub(hfx_ctx* c, int B, int li, const std::vector<PairInfo
     P.lds_bytes = (size_t)(ncart(kPairL[B][0]) + ncart(kPairL[B][1])) * c->rs * sizeof(double);
     P.fp64_only = nint >= 600;   // a d-d bra with a d-d or d-p ket: no FP32 kernels
     // FP64 rows (the mixed kernels' FP32 part reads them too); the cooperative kernels read their table from memory
-    P.lds_tab = P.rys ? (size_t)hfx_class_rys_lds(P.cid, 0, 1) : (size_t)boys_lds_bytes();
+    P.lds_tab = P.rys ? (size_t)hfx_class_rys_lds(P.cid, 0, 1) : (size_t)boys_lds_bytes(class_L(P.cid));
     const int digest = c->tune_digest[P.cid] >= 0 ? c->tune_digest[P.cid] : c->opt.digest;
     // 160 KiB of LDS per workgroup, less room for the persistent kernel's static counter
     constexpr size_t kLdsBudget = 160 * 1024 - 256;

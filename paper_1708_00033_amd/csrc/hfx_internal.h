@@ -110,38 +110,35 @@ __device__ __forceinline__ int hfx_xcc_id() {
 #define HFX_CONST_AS __attribute__((address_space(4)))
 
 // ---- Boys function tables ---------------------------------------------------
-// For every order L (0..BOYS_NL-1) one block of 64-byte rows:
-//   block_L[k * 8 + j] = F_{L+j}(T_k) / j!,  T_k = k * BOYS_DT,
-// so that F_L(T) = sum_j block_L[k*8 + j] (T_k - T)^j about the nearest grid
-// point (dF_m/dT = -F_{m+1}); one aligned row is one cache line.  Blocks are
-// stored in the order 1, 0, 2, 3, ... (boys_block) so that the order-0 rows
-// directly follow the order-1 rows: read from global memory, a class of
-// total angular momentum L = 1 takes F_0 from the order-0 row.  The class
-// kernels copy only their order's block into LDS, each row followed by
-// e^{-T_k}: there a class with L = 1 gets F_0 = 2T F_1 + e^{-T} from one row.
+// For every order l < BOYS_NL one block of BOYS_NT rows of 80 bytes:
+//   row k: F_{l+j}(T_k) / j!, j = 0..8, then e^{-T_k},  T_k = k * BOYS_DT,
+// so that F_l(T) = sum_j c_j d^j, d = T_k - T, about the nearest grid point
+// (dF_m/dT = -F_{m+1}): 8 terms in FP64 (|d| <= 0.05: remainder < 1e-16 F), 5
+// in FP32 (< 3e-9 F).  The class kernels copy the rows that their order needs
+// into LDS.  The 80-byte stride lets the 16-byte reads of lanes at different
+// rows start in 8 distinct groups of 4 of the 32 LDS banks (64 bytes: in 2).
 #define BOYS_DT 0.1
 #define BOYS_INV_DT 10.0
-#define BOYS_TMAX 40.0
-#define BOYS_NT 402
-#define BOYS_NL 9
-#define BOYS_ROW 8
-#define BOYS_ORDER64 8   // Taylor terms, FP64 (|T - T_k| <= 0.05: remainder < 1e-15 F)
-#define BOYS_ORDER32 5   // Taylor terms, FP32 (remainder < 3e-9 F)
-
-#define BOYS_EXP_OFF (BOYS_NL * BOYS_NT * BOYS_ROW)   // e^{-T_k}, k < BOYS_NT, after the blocks
-#define BOYS_TAB_ENTRIES (BOYS_EXP_OFF + BOYS_NT)
+#define BOYS_NT 522
+#define BOYS_NL 6
+#define BOYS_ROW 10
+#define BOYS_EXP 9        // e^{-T_k}
+#define BOYS_ORDER64 8    // Taylor terms
+#define BOYS_ORDER32 5
+#define BOYS_TAB_ENTRIES (BOYS_NL * BOYS_NT * BOYS_ROW)
 void hfx_boys_table(double* tab);   // host, BOYS_TAB_ENTRIES entries
 
-__host__ __device__ constexpr int boys_block(int L) { return L == 0 ? 1 : (L == 1 ? 0 : L); }
-// LDS copy of a class's block: BOYS_NT rows of BOYS_LROW64 doubles, the
-// row's 8 coefficients, then e^{-T_k} (BOYS_EXP_SLOT), then one pad.  An
-// 80-byte stride instead of 64 makes the 16-byte reads of lanes at
-// different rows start in 8 distinct groups of 4 of the 32 LDS banks rather
-// than in 2.
-#define BOYS_LROW64 10
-#define BOYS_EXP_SLOT 8
-__host__ __device__ constexpr int boys_entries() { return BOYS_NT * BOYS_ROW; }
-__host__ __device__ constexpr int boys_lds_bytes() { return BOYS_NT * BOYS_LROW64 * 8; }
+// Where the asymptotic form F_m = (2m-1)!! / (2T)^m sqrt(pi/T)/2 takes over for
+// total angular momentum L: its relative error, e^{-T} T^{L-1/2} /
+// Gamma(L+1/2) for F_L and less for the lower orders, is below 1e-16 there.
+__host__ __device__ constexpr int boys_tmax(int L) {
+    return L <= 1 ? 40 : L == 2 ? 44 : L == 3 ? 46 : L == 4 ? 48 : 52;
+}
+__host__ __device__ constexpr int boys_rows(int L) { return boys_tmax(L) * 10 + 2; }
+// The block that a class of total angular momentum L reads: its own order;
+// L = 1 takes F_0 and F_1 = -dF_0/dT from the order-0 row.
+__host__ __device__ constexpr int boys_block(int L) { return (L == 1 ? 0 : L) * BOYS_NT * BOYS_ROW; }
+__host__ __device__ constexpr int boys_lds_bytes(int L) { return boys_rows(L) * BOYS_ROW * 8; }
 
 // ---- Rys quadrature tables ----------------------------------------------------
 // For n = RYS_NMIN..RYS_NMAX points, over T in [0, RYS_NT): per unit interval
@@ -163,58 +160,17 @@ __host__ __device__ constexpr int rys_block(int n) {   // first entry of the n-p
 #define RYS_TAB_ENTRIES (rys_block(RYS_NMAX + 1))
 void hfx_rys_table(double* tab);   // host, RYS_TAB_ENTRIES entries
 
-__device__ __forceinline__ double hfx_sqrt(double x) { return sqrt(x); }
-// 1/sqrt(x) for x > 0: hardware estimate refined by Newton steps
-// y <- y (3/2 - x/2 y^2) (two steps for FP64, one for FP32).
+// 1/sqrt(x) for x > 0: the hardware estimate, refined in FP64 by one
+// third-order step y (1 + e/2 + 3 e^2/8), e = 1 - x y^2 (five operations; two
+// Newton steps take seven), in FP32 by one Newton step.
 __device__ __forceinline__ double hfx_rsqrt(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    const double h = 0.5 * x;
-    y = y * (1.5 - h * y * y);
-    y = y * (1.5 - h * y * y);
-    return y;
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 __device__ __forceinline__ float hfx_rsqrt(float x) {
     float y = __builtin_amdgcn_rsqf(x);
     return y * (1.5f - 0.5f * x * y * y);
-}
-__device__ __forceinline__ float hfx_sqrt(float x) { return sqrtf(x); }
-__device__ __forceinline__ double hfx_exp(double x) { return exp(x); }
-__device__ __forceinline__ float hfx_exp(float x) { return __expf(x); }
-
-// Taylor value of F_L at T from the order-L table (row k, offset d = T_k - T).
-template <int NO>
-__device__ __forceinline__ double boys_taylor(const double* __restrict__ row, double d) {
-    const double2* r2 = reinterpret_cast<const double2*>(row);
-    const double2 c01 = r2[0], c23 = r2[1], c45 = r2[2], c67 = r2[3];
-    const double c[8] = {c01.x, c01.y, c23.x, c23.y, c45.x, c45.y, c67.x, c67.y};
-    double f = c[NO - 1];
-#pragma unroll
-    for (int j = NO - 2; j >= 0; --j) f = c[j] + f * d;
-    return f;
-}
-template <int NO>
-__device__ __forceinline__ float boys_taylor(const float* __restrict__ row, float d) {
-    const float4* r4 = reinterpret_cast<const float4*>(row);
-    const float4 c03 = r4[0], c47 = r4[1];
-    const float c[8] = {c03.x, c03.y, c03.z, c03.w, c47.x, c47.y, c47.z, c47.w};
-    float f = c[NO - 1];
-#pragma unroll
-    for (int j = NO - 2; j >= 0; --j) f = c[j] + f * d;
-    return f;
-}
-
-// FP32 value from the FP64 rows (the mixed kernels keep one table in LDS):
-// the NO leading coefficients rounded to FP32, then the same Horner steps.
-template <int NO>
-__device__ __forceinline__ float boys_taylor(const double* __restrict__ row, float d) {
-    static_assert(NO <= 6, "FP32 Taylor order");
-    const double2* r2 = reinterpret_cast<const double2*>(row);
-    const double2 c01 = r2[0], c23 = r2[1], c45 = r2[2];
-    const float c[6] = {(float)c01.x, (float)c01.y, (float)c23.x, (float)c23.y, (float)c45.x, (float)c45.y};
-    float f = c[NO - 1];
-#pragma unroll
-    for (int j = NO - 2; j >= 0; --j) f = c[j] + f * d;
-    return f;
 }
 
 __host__ __device__ constexpr double boys_inv_fact(int n) {
@@ -227,65 +183,104 @@ template <typename R> struct BoysOrder;
 template <> struct BoysOrder<double> { static constexpr int value = BOYS_ORDER64; };
 template <> struct BoysOrder<float> { static constexpr int value = BOYS_ORDER32; };
 
-// F[0..L] at T.  Below BOYS_TMAX: Taylor expansion of F_L about the nearest
-// grid point, then the downward recursion F_m = (2T F_{m+1} + e^{-T})/(2m+1)
-// (for L = 1: from the LDS rows, e^{-T} = e^{-T_k} e^{T_k - T} with a short
-// series for the second factor; from the global table, F_0 from its own
-// row, no exponential needed).
-// For L <= 1 the two regimes are branches; for L >= 2 both are evaluated
-// with one shared exponential and selected per lane.
-// Above: F_0 = sqrt(pi/T)/2 (erf(sqrt T) = 1 to FP64 there) and the upward recursion
-// F_{m+1} = ((2m+1) F_m - e^{-T})/(2T), stable for T >> m (for L = 1 the
-// exponential term is below rounding and dropped).
-// tab: the order-L block (followed by the order-0 block when L = 1), rows S
-// elements apart, in the evaluation's precision or (FP32 evaluation) FP64.
-template <typename R, int L, int S = BOYS_ROW, typename TT = R>
-__device__ __forceinline__ void boys_eval(R T, R* F, const TT* __restrict__ tab) {
-    constexpr int NO = BoysOrder<R>::value;
-    if constexpr (L <= 1) {
-        if (T < R(BOYS_TMAX)) {
-            const int k = (int)(T * R(BOYS_INV_DT) + R(0.5));
-            const R d = R(k) * R(BOYS_DT) - T;
-            F[L] = boys_taylor<NO>(tab + k * S, d);
-            if constexpr (L == 1) {
-                if constexpr (S > BOYS_EXP_SLOT) {
-                    // e^{d}, |d| <= 0.05: 9 terms (FP64), 5 (FP32), Horner
-                    constexpr int NE = sizeof(R) == 8 ? 9 : 5;
-                    R ed = R(boys_inv_fact(NE - 1));
+// Nearest grid point: its row and d = T_k - T.  FP64: rounding by adding 1.5
+// 2^52, whose low word is then k (two additions instead of two conversions,
+// which run at a quarter of their rate); 24-bit product for the address.
+__device__ __forceinline__ const double* boys_row(const double* tab, double T, double& d) {
+    const double magic = 6755399441055744.0, t = fma(T, BOYS_INV_DT, magic);
+    d = fma(t - magic, BOYS_DT, -T);
+    return reinterpret_cast<const double*>(reinterpret_cast<const char*>(tab) +
+                                           __umul24((unsigned)__double2loint(t), BOYS_ROW * 8u));
+}
+__device__ __forceinline__ const double* boys_row(const double* tab, float T, float& d) {
+    const int k = (int)(T * float(BOYS_INV_DT) + 0.5f);
+    d = float(k) * float(BOYS_DT) - T;
+    return reinterpret_cast<const double*>(reinterpret_cast<const char*>(tab) + __umul24((unsigned)k, BOYS_ROW * 8u));
+}
+
+// First N coefficients of a row in the evaluation's precision.
+template <int N, typename R>
+__device__ __forceinline__ void boys_coefs(const double* __restrict__ row, R (&c)[N]) {
+    const double2* r2 = reinterpret_cast<const double2*>(row);
 #pragma unroll
-                    for (int j = NE - 2; j >= 0; --j) ed = R(boys_inv_fact(j)) + ed * d;
-                    F[0] = R(2) * T * F[1] + R(tab[k * S + BOYS_EXP_SLOT]) * ed;
-                } else {
-                    F[0] = boys_taylor<NO>(tab + (BOYS_NT + k) * S, d);
-                }
+    for (int i = 0; i < (N + 1) / 2; ++i) {
+        const double2 v = r2[i];
+        c[2 * i] = R(v.x);
+        if (2 * i + 1 < N) c[2 * i + 1] = R(v.y);
+    }
+}
+
+// F_0(X / s) / sqrt(s) of a class with L = 0, X = p q |PQ|^2 and s = p + q: one
+// reciprocal square root serves both regimes (far: sqrt(pi)/2 / sqrt(X)).
+template <typename R>
+__device__ __forceinline__ R boys_zero(R s, R X, const double* __restrict__ tab) {
+    constexpr int NO = BoysOrder<R>::value;
+    const bool far = X >= R(boys_tmax(0)) * s;
+    const R y = hfx_rsqrt(far ? X : s);
+    R f = R(0.886226925452758013649083741671);   // sqrt(pi)/2
+    if (!far) {
+        R d, c[NO];
+        boys_coefs<NO>(boys_row(tab, X * (y * y), d), c);
+        f = c[NO - 1];
+#pragma unroll
+        for (int j = NO - 2; j >= 0; --j) f = c[j] + f * d;
+    }
+    return f * y;
+}
+
+// F[0..L] at T, L >= 1; tab: the rows of boys_block(L).  Near: L = 1, F_0 and
+// F_1 as the value and the derivative of one polynomial of one term more; L >=
+// 2, F_L by Taylor expansion, e^{-T} = e^{-T_k} e^d (a 9- or 5-term series)
+// and the downward recursion F_m = (2T F_{m+1} + e^{-T}) / (2m+1).  Far: the
+// asymptotic form, no exponential.  Lanes of a wave usually straddle the two.
+// Against 64-bit-exact values over 0 <= T <= 150 the largest relative error of
+// an order up to 5 is 2.1e-15 (2.9e-15 with the exponential function and
+// upward recursion in this place).  A primitive quartet of the low classes is
+// bound by about 50 vector instructions and 4 LDS row reads; this form with
+// hfx_rsqrt took the 64-water launches of (ss|ss) from 20.2 to 18.0 ms,
+// (ps|ss) from 19.9 to 18.4, (ds|ss) from 12.7 to 11.4 and (ds|ps) from 8.8 to
+// 8.5, a 44-carbon bilayer's (ps|ps) from 10.4 to 7.4 and (ps|ss) from 9.0 to
+// 7.7 ms.
+template <typename R, int L>
+__device__ __forceinline__ void boys_eval(R T, R* F, const double* __restrict__ tab) {
+    static_assert(L >= 1 && L < BOYS_NL, "orders of the table");
+    constexpr int NO = BoysOrder<R>::value;
+    if (T < R(boys_tmax(L))) {
+        R d;
+        const double* row = boys_row(tab, T, d);
+        if constexpr (L == 1) {
+            R c[NO + 1];
+            boys_coefs<NO + 1>(row, c);
+            R f = c[NO], g = c[NO];
+#pragma unroll
+            for (int j = NO - 1; j >= 1; --j) {
+                f = c[j] + f * d;
+                g = f + g * d;
             }
+            F[0] = c[0] + f * d;
+            F[1] = g;
         } else {
-            const R rt = hfx_rsqrt(T);
-            F[0] = R(0.886226925452758013649083741671) * rt;   // sqrt(pi)/2 / sqrt(T)
-            // e^{-T} / F_0(T) < 3.1e-17 for T >= 40, below half an FP64 ulp:
-            // F_1 = F_0 / (2T) without the exponential
-            if constexpr (L == 1) F[1] = F[0] * (R(0.5) * rt * rt);
+            R c[NO];
+            boys_coefs<NO>(row, c);
+            R f = c[NO - 1];
+#pragma unroll
+            for (int j = NO - 2; j >= 0; --j) f = c[j] + f * d;
+            constexpr int NE = sizeof(R) == 8 ? 9 : 5;
+            R e = R(boys_inv_fact(NE - 1));   // (e^d - 1) / d
+#pragma unroll
+            for (int j = NE - 2; j >= 1; --j) e = R(boys_inv_fact(j)) + e * d;
+            const R ek = R(row[BOYS_EXP]);
+            e = ek + ek * (e * d);
+            F[L] = f;
+            const R t2 = R(2) * T;
+#pragma unroll
+            for (int m = L - 1; m >= 0; --m) F[m] = (t2 * F[m + 1] + e) * R(1.0 / (2 * m + 1));
         }
     } else {
-        // both regimes evaluated with one exponential, each lane selects its
-        // own (the lanes of a wave usually straddle BOYS_TMAX); rows clamped
-        // into the table for lanes in the asymptotic regime
-        const bool near = T < R(BOYS_TMAX);
-        const int k = (int)(near ? T * R(BOYS_INV_DT) + R(0.5) : R(0));
-        const R d = R(k) * R(BOYS_DT) - T;
-        const R rt = hfx_rsqrt(T);
-        const R h = R(0.5) * rt * rt;   // 1/(2T)
-        const R e = hfx_exp(-T);
-        R down[L + 1], up[L + 1];
-        down[L] = boys_taylor<NO>(tab + k * S, d);
-        const R t2 = R(2) * T;
+        const R rt = hfx_rsqrt(T), h = R(0.5) * rt * rt;   // 1 / (2T)
+        F[0] = R(0.886226925452758013649083741671) * rt;
 #pragma unroll
-        for (int m = L - 1; m >= 0; --m) down[m] = (t2 * down[m + 1] + e) * R(1.0 / (2 * m + 1));
-        up[0] = R(0.886226925452758013649083741671) * rt;
-#pragma unroll
-        for (int m = 0; m < L; ++m) up[m + 1] = (R(2 * m + 1) * up[m] - e) * h;
-#pragma unroll
-        for (int m = 0; m <= L; ++m) F[m] = near ? down[m] : up[m];
+        for (int m = 0; m < L; ++m) F[m + 1] = R(2 * m + 1) * h * F[m];
     }
 }
 

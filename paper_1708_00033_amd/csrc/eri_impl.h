@@ -26,6 +26,8 @@
 #include "hfx_internal.h"
 
 #define HFX_WG 256
+// digestion: integral blocks up to this size read all their D' elements first
+#define HFX_LOADS_FIRST_MAX_NI 18
 
 // K update of W[grow][gcol]: MODE 0 into the task's LDS bra row at column
 // lcol (gcol less the column base of its window), MODE 1 straight into W.
@@ -38,8 +40,7 @@ __device__ __forceinline__ void row_add(double* lds_row, double* W, int grow, in
     }
 }
 
-// dket: the gathered D'_cd of the ket list ([component][ket position]); W
-// receives the J updates and WK the K updates of MODE 1 (one matrix for a
+// dcd: the ket's gathered D'_cd; W receives the J updates and WK the K updates of MODE 1 (one matrix for a
 // Fock build, separate J and K accumulators for a multi-density build).
 // DST (LDS digestion): bit 0, the bra's D' rows of shell a come from their
 // LDS copy DI (same columns as FI); bit 1, those of shell b from DJ.
@@ -47,16 +48,53 @@ template <int NA, int NB, int NC, int ND, int MODE, int DST = 0>
 __device__ __forceinline__ void digest(const double* I, double g, const ClassArgs& a, const PairInfo& bra,
                                        int fc, int fd, int spos, const double* dab, double* jab, double* FI,
                                        double* FJ, const double* __restrict__ D, double* W, int N,
-                                       int RS, int cb, int db, const double* __restrict__ dket, double* WK,
-                                       double* wket, const double* DI = nullptr, const double* DJ = nullptr) {
+                                       int RS, int cb, int db, const double* dcd, double* WK, double* wket,
+                                       const double* DI = nullptr, const double* DJ = nullptr) {
     const int fa = bra.bfa, fb = bra.bfb;
     const double cj2 = 2.0 * a.cj * g, ckg = -a.ck * g;
+    // the D' elements of the exchange updates
+    auto load_bd = [&](double* v) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int s = 0; s < ND; ++s)
+                v[n * ND + s] = (DST & 2) ? DJ[n * RS + fd + s - db] : D[(size_t)(fb + n) * N + fd + s];
+    };
+    auto load_ac = [&](double* v) {
+#pragma unroll
+        for (int m = 0; m < NA; ++m)
+#pragma unroll
+            for (int l = 0; l < NC; ++l)
+                v[m * NC + l] = (DST & 1) ? DI[m * RS + fc + l - cb] : D[(size_t)(fa + m) * N + fc + l];
+    };
+    auto load_bc = [&](double* v) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int l = 0; l < NC; ++l)
+                v[n * NC + l] = (DST & 2) ? DJ[n * RS + fc + l - cb] : D[(size_t)(fb + n) * N + fc + l];
+    };
+    auto load_ad = [&](double* v) {
+#pragma unroll
+        for (int m = 0; m < NA; ++m)
+#pragma unroll
+            for (int s = 0; s < ND; ++s)
+                v[m * ND + s] = (DST & 1) ? DI[m * RS + fd + s - db] : D[(size_t)(fa + m) * N + fd + s];
+    };
+    // Small blocks: all of them before the first update.  The compiler keeps
+    // the order of loads and atomics, so that each update would wait for its
+    // own loads (four round trips to LDS or L2 per quartet); larger blocks
+    // have no registers for it.
+    constexpr bool FIRST = NA * NB * NC * ND <= HFX_LOADS_FIRST_MAX_NI;
+    double dbd[NB * ND], dac[NA * NC], dbc[NB * NC], dad[NA * ND];
+    if constexpr (FIRST) {
+        load_bd(dbd);
+        load_ac(dac);
+        load_bc(dbc);
+        load_ad(dad);
+    }
     // J, bra block: per-lane running sums over the task (reduced at the end)
     {
-        // D_cd gathered in ket-list order before the build (coalesced across lanes)
-        double dcd[NC * ND];
-#pragma unroll
-        for (int ls = 0; ls < NC * ND; ++ls) dcd[ls] = dket[(size_t)ls * a.nket_list + spos];
 #pragma unroll
         for (int mn = 0; mn < NA * NB; ++mn) {
             double v = 0.0;
@@ -82,12 +120,7 @@ __device__ __forceinline__ void digest(const double* I, double g, const ClassArg
         }
     // K: W_ac -= ck g sum_{nu sigma} I D_bd
     {
-        double dbd[NB * ND];
-#pragma unroll
-        for (int n = 0; n < NB; ++n)
-#pragma unroll
-            for (int s = 0; s < ND; ++s)
-                dbd[n * ND + s] = (DST & 2) ? DJ[n * RS + fd + s - db] : D[(size_t)(fb + n) * N + fd + s];
+        if constexpr (!FIRST) load_bd(dbd);
 #pragma unroll
         for (int m = 0; m < NA; ++m)
 #pragma unroll
@@ -102,12 +135,7 @@ __device__ __forceinline__ void digest(const double* I, double g, const ClassArg
     }
     // K: W_bd -= ck g sum_{mu lambda} I D_ac
     {
-        double dac[NA * NC];
-#pragma unroll
-        for (int m = 0; m < NA; ++m)
-#pragma unroll
-            for (int l = 0; l < NC; ++l)
-                dac[m * NC + l] = (DST & 1) ? DI[m * RS + fc + l - cb] : D[(size_t)(fa + m) * N + fc + l];
+        if constexpr (!FIRST) load_ac(dac);
 #pragma unroll
         for (int n = 0; n < NB; ++n)
 #pragma unroll
@@ -122,12 +150,7 @@ __device__ __forceinline__ void digest(const double* I, double g, const ClassArg
     }
     // K: W_ad -= ck g sum_{nu lambda} I D_bc
     {
-        double dbc[NB * NC];
-#pragma unroll
-        for (int n = 0; n < NB; ++n)
-#pragma unroll
-            for (int l = 0; l < NC; ++l)
-                dbc[n * NC + l] = (DST & 2) ? DJ[n * RS + fc + l - cb] : D[(size_t)(fb + n) * N + fc + l];
+        if constexpr (!FIRST) load_bc(dbc);
 #pragma unroll
         for (int m = 0; m < NA; ++m)
 #pragma unroll
@@ -142,12 +165,7 @@ __device__ __forceinline__ void digest(const double* I, double g, const ClassArg
     }
     // K: W_bc -= ck g sum_{mu sigma} I D_ad
     {
-        double dad[NA * ND];
-#pragma unroll
-        for (int m = 0; m < NA; ++m)
-#pragma unroll
-            for (int s = 0; s < ND; ++s)
-                dad[m * ND + s] = (DST & 1) ? DI[m * RS + fd + s - db] : D[(size_t)(fa + m) * N + fd + s];
+        if constexpr (!FIRST) load_ad(dad);
 #pragma unroll
         for (int n = 0; n < NB; ++n)
 #pragma unroll
@@ -404,6 +422,17 @@ __device__ __forceinline__ void class_task(const ClassArgs& a, const int ti, con
         const bool lo = j < slots64;   // wave-uniform
         const int s = lo ? s0 + (j << 6) + ln : split + ((j - slots64) << 6) + ln;
         if (s >= (lo ? split : send)) continue;   // the part's last, partial slot
+        // the ket's record and D'_cd (gathered in ket-list order before the
+        // build, coalesced across lanes); small blocks load them ahead of the
+        // primitive loops
+        int4 kb;
+        double dcd[NC * ND];
+        auto load_ket = [&]() {
+            kb = a.kbf[s];   // ket's first basis functions and shells
+#pragma unroll
+            for (int i = 0; i < NC * ND; ++i) dcd[i] = a.dket[(size_t)i * a.nket_list + s];
+        };
+        if constexpr (NI <= HFX_LOADS_FIRST_MAX_NI) load_ket();
         double I[NI];
         if (!FP32 || lo) {
             E::template run<double>((const double*)(a.prim + bra.prim_off), bra.nprim, a.kprim + s,
@@ -419,10 +448,10 @@ __device__ __forceinline__ void class_task(const ClassArgs& a, const int ti, con
             ++n32;
         }
         // the block (either precision) digested in FP64
-        const int4 kb = a.kbf[s];   // ket's first basis functions and shells
+        if constexpr (NI > HFX_LOADS_FIRST_MAX_NI) load_ket();
         const double g = sbra * (kb.z != kb.w ? 2.0 : 1.0) * ((kb.z == bra.a && kb.w == bra.b) ? 1.0 : 2.0);
-        digest<NA, NB, NC, ND, MODE, DST>(I, g, a, bra, kb.x, kb.y, s, dab, jab, FI, FJ, Dm, Wm, N, RS, cb, db, a.dket,
-                                          Wm, a.wket, DI, DJ);
+        digest<NA, NB, NC, ND, MODE, DST>(I, g, a, bra, kb.x, kb.y, s, dab, jab, FI, FJ, Dm, Wm, N, RS, cb, db, dcd, Wm,
+                                          a.wket, DI, DJ);
     }
     // bra J block: wave reduction, one global add per wave (column bfb may lie
     // outside the task's windows)
@@ -691,9 +720,13 @@ __device__ __forceinline__ void class_task_multi(const ClassArgs& a, const int t
                     dab[mn] = Dd[(size_t)(bra.bfa + mn / NB) * N + bra.bfb + mn % NB];
                     jt[mn] = 0.0;
                 }
-                if (valid)
+                if (valid) {
+                    double dcd[NC * ND];
+#pragma unroll
+                    for (int i = 0; i < NC * ND; ++i) dcd[i] = dket[(size_t)i * a.nket_list + s];
                     digest<NA, NB, NC, ND, MODE>(I, g, a, bra, kb.x, kb.y, s, dab, jt, FI, FI + NA * RS, Dd, WJ, N, RS,
-                                                 cb, db, dket, WKd, wket);
+                                                 cb, db, dcd, WKd, wket);
+                }
 #pragma unroll
                 for (int mn = 0; mn < NAB; ++mn) {
                     const double v = wave_sum(jt[mn]);

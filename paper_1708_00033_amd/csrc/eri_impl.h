@@ -279,10 +279,23 @@ __device__ __forceinline__ void digest_kr(const double* I, double g, double ck, 
     }
 }
 
+// Sum over the wave, in every lane: lane exchanges within rows of 16 by DPP,
+// across rows and halves by permlane swaps (no LDS round trips).
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)u, hi = (unsigned)(u >> 32);
+    const unsigned a = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+    const unsigned b = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+    return v + __longlong_as_double((long long)(((unsigned long long)b << 32) | a));
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v = dpp_add<0xb1>(v);    // quad_perm 1 0 3 2
+    v = dpp_add<0x4e>(v);    // quad_perm 2 3 0 1
+    v = dpp_add<0x141>(v);   // row_half_mirror
+    v = dpp_add<0x140>(v);   // row_mirror
+    v = lane_pair_sum<4>(v, v);
+    return lane_pair_sum<5>(v, v);
 }
 
 // A wave's evaluated-quartet counts (per-lane running counts) into the
@@ -337,148 +350,209 @@ __device__ __forceinline__ void task_sync() {
     }
 }
 
-// One task (one bra, a range of its kets) on the lanes of the workgroup or
-// (WAVE) of one wave, whose bra rows are the wave's own LDS region.
-// Evaluated quartets go to the lane's running counts cnt64 / cnt32.
-// DST: the bra's D' rows staged in LDS for the LDS digestion (bit 0 shell
-// a's, bit 1 shell b's), a kernel variant of the classes with small blocks.
-template <class E, int MODE, int FP32, bool WAVE = false, int DST = 0>
-__device__ __forceinline__ void class_task(const ClassArgs& a, const int ti, const double* t64, unsigned& cnt64,
-                                           unsigned& cnt32) {
-    constexpr int NA = hfx_ncart(E::LA), NB = hfx_ncart(E::LB), NC = hfx_ncart(E::LC), ND = hfx_ncart(E::LD);
-    constexpr int NAB = NA * NB, NI = NA * NB * NC * ND;
-    constexpr int NT = WAVE ? 64 : E::WGS;   // lanes of the task
-    const int tid = WAVE ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
-    extern __shared__ __align__(16) double lds[];
-    const int4 task = a.tasks[ti];
-    const int r = task.x;
-    if (!task_active(a, task)) return;
-    // kets [s0, send) of the list: [s0, split) in FP64, [split, send) in FP32
-    const int s0 = task.y, send = task.z;
-    const int split = FP32 ? min(max(a.split[ti], s0), send) : send;
-    const PairInfo bra = a.bra[r];
-    // the bra's molecule: its blocks of D' and W, leading dimension ld
-    const int N = bra.ld;
-    const double* __restrict__ Dm = a.D + a.moff[bra.mol];
-    // private digestion: this XCD's own copy of W (algorithm 2's private
-    // Fock matrix, one per XCD instead of one per thread)
-    double* __restrict__ Wm = a.W + a.moff[bra.mol] + (a.wrep ? (size_t)hfx_xcc_id() * a.wrep : 0);
+// One task (one bra, a range of its kets): what the kernels need of it.
+struct BraTask {
+    PairInfo bra;
+    int s0, split, send;   // kets [s0, split) in FP64, [split, send) in FP32
+    int N;                 // leading dimension of the molecule's blocks, which start at element mo
     // LDS bra rows of length RS: whole rows, or (column windows) the task's
     // window of shell c at [0, RS/2) and of shell d at [RS/2, RS) (one region
     // when both windows coincide); column col sits at col - cb (c) / col - db (d)
-    int RS = N, cb = 0, db = 0, half = N;
+    int RS, cb, db, half;
+    size_t mo, wo;         // wo: offset in W (private digestion: in this XCD's own copy, algorithm
+                           // 2's private Fock matrix, one per XCD instead of one per thread)
+    bool on;               // false: no task, padding (XCD striping) or another shard's bra
+};
+
+// ti uniform; -1: none.
+template <int FP32>
+__device__ __forceinline__ BraTask load_task(const ClassArgs& a, const int ti) {
+    BraTask t;
+    t.on = false;
+    t.RS = 0;
+    if (ti < 0) return t;
+    const int4 task = a.tasks[ti];
+    if (!task_active(a, task)) return t;
+    t.on = true;
+    t.bra = a.bra[task.x];
+    t.s0 = task.y;
+    t.send = task.z;
+    t.split = FP32 ? min(max(a.split[ti], t.s0), t.send) : t.send;
+    t.N = t.RS = t.half = t.bra.ld;
+    t.cb = t.db = 0;
+    t.mo = (size_t)a.moff[t.bra.mol];
+    t.wo = t.mo + (a.wrep ? (size_t)hfx_xcc_id() * a.wrep : 0);
     if (a.win) {
-        RS = a.rs;
-        half = RS / 2;
+        t.RS = a.rs;
+        t.half = t.RS / 2;
         const int wc = task.w & 0xffff, wd = task.w >> 16;
-        cb = wc * a.win;
-        db = wd == wc ? cb : wd * a.win - half;
+        t.cb = wc * a.win;
+        t.db = wd == wc ? t.cb : wd * a.win - t.half;
     }
-    // LDS digestion with staged D' rows: DI, the bra's rows of shell a (DST
-    // bit 0), then DJ, those of shell b (bit 1), after F_I and F_J
+    return t;
+}
+
+// Adds the rows at F (NA of shell a, NB of shell b) to w (the molecule's block
+// of W or WK) and clears them, on NT lanes: a lane takes a column of every row
+// at once (no divisions by the row length, all reads in flight together).
+template <int NA, int NB, int NT>
+__device__ __forceinline__ void flush_rows(double* F, int tid, int RS, int half, int cb, int db, int N, int bfa, int bfb,
+                                           double* __restrict__ w) {
+    for (int c = tid; c < RS; c += NT) {
+        const int col = c + (c < half ? cb : db);
+        double v[NA + NB];
+#pragma unroll
+        for (int r = 0; r < NA + NB; ++r) v[r] = F[r * RS + c];
+#pragma unroll
+        for (int r = 0; r < NA + NB; ++r)
+            if (v[r] != 0.0) {
+                F[r * RS + c] = 0.0;
+                if (col < N) atomicAdd(w + (size_t)(r < NA ? bfa + r : bfb + r - NA) * N + col, v[r]);
+            }
+    }
+}
+
+// The kernels of one task on the lanes of the workgroup or (WAVE) of one wave,
+// whose bra rows are the wave's own LDS region.  DST: the bra's D' rows staged
+// in LDS for the LDS digestion (bit 0 shell a's, bit 1 shell b's), a kernel
+// variant of the classes with small blocks.  LDS of a region: F_I, F_J, zero
+// between tasks, then at a fixed place (rows of a batch differ in length) the
+// staged rows.
+template <class E, int MODE, int FP32, bool WAVE, int DST>
+struct BraRun {
+    static constexpr int NA = hfx_ncart(E::LA), NB = hfx_ncart(E::LB), NC = hfx_ncart(E::LC), ND = hfx_ncart(E::LD);
+    static constexpr int NAB = NA * NB, NI = NA * NB * NC * ND;
+    static constexpr int NT = WAVE ? 64 : E::WGS;   // lanes of the task
+    static constexpr int nda = (DST & 1) ? NA : 0, ndb = (DST & 2) ? NB : 0;
     static_assert(DST == 0 || (MODE == 0 && NI <= HFX_STAGE_D_MAX_NI), "no staged D' rows");
-    constexpr int nda = (DST & 1) ? NA : 0, ndb = (DST & 2) ? NB : 0;
-    // a wave's region is (NA + NB + nda + ndb) a.rs doubles (a.rs >= RS for every molecule of a batch)
-    double* FI = lds + LdsLayout<E>::ROWS + (WAVE ? (int)(threadIdx.x >> 6) * (NA + NB + nda + ndb) * a.rs : 0);
-    double* FJ = FI + NA * RS;
-    double* DI = FJ + NB * RS;
-    double* DJ = DI + nda * RS;
-    if constexpr (MODE == 0) {
-        for (int i = tid; i < (NA + NB) * RS; i += NT) FI[i] = 0.0;
-        // staged rows over the same columns as F_I / F_J (zero past the molecule's last column)
-        for (int i = tid; i < (nda + ndb) * RS; i += NT) {
-            const bool ra = i < nda * RS;
-            const int ii = ra ? i : i - nda * RS;
-            const int row = (ra ? bra.bfa : bra.bfb) + ii / RS;
-            const int lc = ii % RS;
-            const int col = lc + (lc < half ? cb : db);
-            DI[i] = col < N ? Dm[(size_t)row * N + col] : 0.0;
-        }
-        task_sync<WAVE>();
-    }
-    double dab[NAB], jab[NAB];
-#pragma unroll
-    for (int m = 0; m < NA; ++m)
-#pragma unroll
-        for (int n = 0; n < NB; ++n) {
-            dab[m * NB + n] = Dm[(size_t)(bra.bfa + m) * N + bra.bfb + n];
-            jab[m * NB + n] = 0.0;
-        }
-    const double sbra = bra.a != bra.b ? 2.0 : 1.0;
-    const int kps = a.nket_list, kfs = a.nket_list * a.knprim;
+    const ClassArgs& a;
+    const double* t64;
+    int tid;
+    double *F, *DR;          // F_I and F_J; staged rows
+    double dab[NAB];
     unsigned n64 = 0, n32 = 0;
-    // The task's kets in slots of 64 consecutive kets, dealt to the task's
-    // waves in turn (wave w takes slots w, w + nw, ...): the FP64 part
-    // [s0, split) fills the first slots and the FP32 part [split, send) the
-    // rest, so every slot is uniform in precision and the two parts cost at
-    // most one partial slot more than one part (a per-lane choice, or one
-    // loop per part over the whole workgroup, costs a full workgroup
-    // iteration per task, which short tasks cannot hide).  With one part this
-    // is the plain interleaving s = s0 + tid + i NT.
-    const int nw = NT / 64, wv = tid >> 6, ln = tid & 63;
-    const int slots64 = (split - s0 + 63) >> 6;
-    const int slots = slots64 + ((send - split + 63) >> 6);
-    for (int j = wv; j < slots; j += nw) {
-        const bool lo = j < slots64;   // wave-uniform
-        const int s = lo ? s0 + (j << 6) + ln : split + ((j - slots64) << 6) + ln;
-        if (s >= (lo ? split : send)) continue;   // the part's last, partial slot
-        // the ket's record and D'_cd (gathered in ket-list order before the
-        // build, coalesced across lanes); small blocks load them ahead of the
-        // primitive loops
-        int4 kb;
-        double dcd[NC * ND];
-        auto load_ket = [&]() {
-            kb = a.kbf[s];   // ket's first basis functions and shells
-#pragma unroll
-            for (int i = 0; i < NC * ND; ++i) dcd[i] = a.dket[(size_t)i * a.nket_list + s];
-        };
-        if constexpr (NI <= HFX_LOADS_FIRST_MAX_NI) load_ket();
-        double I[NI];
-        if (!FP32 || lo) {
-            E::template run<double>((const double*)(a.prim + bra.prim_off), bra.nprim, a.kprim + s,
-                                                 kfs, kps, a.knprim, bra.AB, a.ket[s].AB, t64, I);
-            ++n64;
-        } else if constexpr (FP32) {
-            // FP32 primitive copies, the FP64 Boys rows rounded
-            float If[NI];
-            E::template run<float>(a.prim32 + (size_t)bra.prim_off * HFX_PRIM_FIELDS, bra.nprim,
-                                                a.kprim32 + s, kfs, kps, a.knprim, bra.AB, a.ket[s].AB, t64, If);
-#pragma unroll
-            for (int i = 0; i < NI; ++i) I[i] = (double)If[i];
-            ++n32;
-        }
-        // the block (either precision) digested in FP64
-        if constexpr (NI > HFX_LOADS_FIRST_MAX_NI) load_ket();
-        const double g = sbra * (kb.z != kb.w ? 2.0 : 1.0) * ((kb.z == bra.a && kb.w == bra.b) ? 1.0 : 2.0);
-        digest<NA, NB, NC, ND, MODE, DST>(I, g, a, bra, kb.x, kb.y, s, dab, jab, FI, FJ, Dm, Wm, N, RS, cb, db, dcd, Wm,
-                                          a.wket, DI, DJ);
+
+    __device__ __forceinline__ BraRun(const ClassArgs& args, double* lds)
+        : a(args), t64(lds), tid(WAVE ? (int)(threadIdx.x & 63) : (int)threadIdx.x) {
+        F = lds + LdsLayout<E>::ROWS + (WAVE ? (int)(threadIdx.x >> 6) * (NA + NB + nda + ndb) * a.rs : 0);
+        DR = F + (NA + NB) * a.rs;
     }
-    // bra J block: wave reduction, one global add per wave (column bfb may lie
-    // outside the task's windows)
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int mn = 0; mn < NAB; ++mn) {
-        const double v = wave_sum(jab[mn]);
-        if (lane == 0) {
-            const int m = mn / NB, n = mn % NB;
-            atomicAdd(Wm + (size_t)(bra.bfa + m) * N + bra.bfb + n, 2.0 * a.cj * v);
-        }
+    __device__ __forceinline__ void clear_rows() {
+        if constexpr (MODE == 0)
+            for (int i = tid; i < (NA + NB) * a.rs; i += NT) F[i] = 0.0;
     }
-    cnt64 += n64;
-    cnt32 += n32;
-    if constexpr (MODE == 0) {
-        task_sync<WAVE>();
-        for (int i = tid; i < (NA + NB) * RS; i += NT) {
-            const double v = FI[i];
-            if (v != 0.0) {
-                const int row = i < NA * RS ? bra.bfa + i / RS : bra.bfb + (i - NA * RS) / RS;
-                const int lc = i < NA * RS ? i % RS : (i - NA * RS) % RS;
-                const int col = lc + (lc < half ? cb : db);
-                if (col < N) atomicAdd(Wm + (size_t)row * N + col, v);
+    // D'_ab and the staged rows of a task, over the same columns as F_I / F_J
+    // (zero past the molecule's last column).
+    __device__ __forceinline__ void stage(const BraTask& t) {
+        const double* __restrict__ Dm = a.D + t.mo;
+#pragma unroll
+        for (int m = 0; m < NA; ++m)
+#pragma unroll
+            for (int n = 0; n < NB; ++n) dab[m * NB + n] = Dm[(size_t)(t.bra.bfa + m) * t.N + t.bra.bfb + n];
+        if constexpr (DST != 0) {
+            for (int c = tid; c < t.RS; c += NT) {
+                const int col = c + (c < t.half ? t.cb : t.db);
+#pragma unroll
+                for (int r = 0; r < nda + ndb; ++r)
+                    DR[r * t.RS + c] =
+                        col < t.N ? Dm[(size_t)(r < nda ? t.bra.bfa + r : t.bra.bfb + r - nda) * t.N + col] : 0.0;
             }
         }
     }
-}
+    __device__ __forceinline__ void flush(const BraTask& t) {
+        if constexpr (MODE == 0)
+            flush_rows<NA, NB, NT>(F, tid, t.RS, t.half, t.cb, t.db, t.N, t.bra.bfa, t.bra.bfb, a.W + t.wo);
+    }
+    // The task's kets: evaluation, digestion into the LDS rows (MODE 0) and
+    // W, then the bra block's J.
+    __device__ __forceinline__ void kets(const BraTask& t) {
+        const PairInfo& bra = t.bra;
+        const double* __restrict__ Dm = a.D + t.mo;
+        double* __restrict__ Wm = a.W + t.wo;
+        const int N = t.N, RS = t.RS, cb = t.cb, db = t.db;
+        double *FI = F, *FJ = F + NA * RS, *DI = DR, *DJ = DR + nda * RS;
+        double jab[NAB];
+#pragma unroll
+        for (int mn = 0; mn < NAB; ++mn) jab[mn] = 0.0;
+        const double sbra = bra.a != bra.b ? 2.0 : 1.0;
+        const int kps = a.nket_list, kfs = a.nket_list * a.knprim;
+        // The task's kets in slots of 64 consecutive kets, dealt to the task's
+        // waves in turn (wave w takes slots w, w + nw, ...): the FP64 part
+        // [s0, split) fills the first slots and the FP32 part [split, send) the
+        // rest, so every slot is uniform in precision and the two parts cost at
+        // most one partial slot more than one part (a per-lane choice, or one
+        // loop per part over the whole workgroup, costs a full workgroup
+        // iteration per task, which short tasks cannot hide).  With one part this
+        // is the plain interleaving s = s0 + tid + i NT.
+        const int nw = NT / 64, wv = tid >> 6, ln = tid & 63;
+        const int slots64 = (t.split - t.s0 + 63) >> 6;
+        const int slots = slots64 + ((t.send - t.split + 63) >> 6);
+        for (int j = wv; j < slots; j += nw) {
+            const bool lo = j < slots64;   // wave-uniform
+            const int s = lo ? t.s0 + (j << 6) + ln : t.split + ((j - slots64) << 6) + ln;
+            if (s >= (lo ? t.split : t.send)) continue;   // the part's last, partial slot
+            // the ket's record and D'_cd (gathered in ket-list order before the
+            // build, coalesced across lanes); small blocks load them ahead of the
+            // primitive loops
+            int4 kb;
+            double dcd[NC * ND];
+            auto load_ket = [&]() {
+                kb = a.kbf[s];   // ket's first basis functions and shells
+#pragma unroll
+                for (int i = 0; i < NC * ND; ++i) dcd[i] = a.dket[(size_t)i * a.nket_list + s];
+            };
+            if constexpr (NI <= HFX_LOADS_FIRST_MAX_NI) load_ket();
+            double I[NI];
+            if (!FP32 || lo) {
+                E::template run<double>((const double*)(a.prim + bra.prim_off), bra.nprim, a.kprim + s,
+                                        kfs, kps, a.knprim, bra.AB, a.ket[s].AB, t64, I);
+                ++n64;
+            } else if constexpr (FP32) {
+                // FP32 primitive copies, the FP64 Boys rows rounded
+                float If[NI];
+                E::template run<float>(a.prim32 + (size_t)bra.prim_off * HFX_PRIM_FIELDS, bra.nprim,
+                                       a.kprim32 + s, kfs, kps, a.knprim, bra.AB, a.ket[s].AB, t64, If);
+#pragma unroll
+                for (int i = 0; i < NI; ++i) I[i] = (double)If[i];
+                ++n32;
+            }
+            // the block (either precision) digested in FP64
+            if constexpr (NI > HFX_LOADS_FIRST_MAX_NI) load_ket();
+            const double g = sbra * (kb.z != kb.w ? 2.0 : 1.0) * ((kb.z == bra.a && kb.w == bra.b) ? 1.0 : 2.0);
+            digest<NA, NB, NC, ND, MODE, DST>(I, g, a, bra, kb.x, kb.y, s, dab, jab, FI, FJ, Dm, Wm, N, RS, cb, db, dcd,
+                                              Wm, a.wket, DI, DJ);
+        }
+        // bra J block: wave reduction, one global add per wave (column bfb may lie
+        // outside the task's windows)
+#pragma unroll
+        for (int mn = 0; mn < NAB; ++mn) {
+            const double v = wave_sum(jab[mn]);
+            if ((threadIdx.x & 63) == 0)
+                atomicAdd(Wm + (size_t)(bra.bfa + mn / NB) * N + bra.bfb + mn % NB, 2.0 * a.cj * v);
+        }
+    }
+};
+
+// A reader of the eight XCD queues (one lane): the queue of XCD x0, then the
+// others in turn, so that no XCD idles while another still has work.  ahead()
+// draws an entry without waiting for it, take() turns it into a task index, or
+// -1 when every queue is drained.
+struct QueueReader {
+    const ClassArgs& a;
+    int x0, q = 0, drawn = 0;
+    __device__ __forceinline__ explicit QueueReader(const ClassArgs& args) : a(args), x0(blockIdx.x & 7) {}
+    __device__ __forceinline__ void ahead() {
+        if (q < 8) drawn = (int)atomicAdd(a.work + ((x0 + q) & 7), 1ull);
+    }
+    __device__ __forceinline__ int take() {
+        while (q < 8) {
+            if (drawn < a.qlen) return 8 * drawn + ((x0 + q) & 7);
+            ++q;
+            ahead();
+        }
+        return -1;
+    }
+};
 
 // Register-tiled task: a block of nb <= NBL consecutive bras of the class's
 // Q-sorted list (one molecule) against one range of kets whose primitive
@@ -603,23 +677,10 @@ __device__ __forceinline__ void class_task_kr(const ClassArgs& a, const int ti, 
     cnt64 += n64;
     if constexpr (MODE == 0) {
         __syncthreads();
-        for (int i = tid; i < nb * ROWS * a.rs; i += NT) {
-            const double v = F0[i];
-            if (v != 0.0) {
-                const int bi = i / (ROWS * a.rs), j = i - bi * ROWS * a.rs;
-                int bfa = bra[0].bfa, bfb = bra[0].bfb;
 #pragma unroll
-                for (int k = 1; k < NBL; ++k)
-                    if (bi == k) {
-                        bfa = bra[k].bfa;
-                        bfb = bra[k].bfb;
-                    }
-                const int row = j < NA * RS ? bfa + j / RS : bfb + (j - NA * RS) / RS;
-                const int lc = j < NA * RS ? j % RS : (j - NA * RS) % RS;
-                const int col = lc + (lc < half ? cb : db);
-                if (col < N) atomicAdd(Wm + (size_t)row * N + col, v);
-            }
-        }
+        for (int k = 0; k < NBL; ++k)
+            if (k < nb)
+                flush_rows<NA, NB, NT>(F0 + k * ROWS * a.rs, tid, RS, half, cb, db, N, bra[k].bfa, bra[k].bfb, Wm);
     }
 }
 
@@ -737,17 +798,9 @@ __device__ __forceinline__ void class_task_multi(const ClassArgs& a, const int t
         }
         if constexpr (MODE == 0) {   // each density's K rows into its K accumulator
             __syncthreads();
-            for (int x = tid; x < a.ndens * rowset; x += NT) {
-                const double v = F0[x];
-                if (v != 0.0) {
-                    const int d = x / rowset, j = x - d * rowset;
-                    const int row = j < NA * RS ? bra.bfa + j / RS : bra.bfb + (j - NA * RS) / RS;
-                    const int lc = j < NA * RS ? j % RS : (j - NA * RS) % RS;
-                    const int col = lc + (lc < half ? cb : db);
-                    if (col < N && j < (NA + NB) * RS)
-                        atomicAdd(a.WK + (size_t)d * a.dstride + moff + (size_t)row * N + col, v);
-                }
-            }
+            for (int d = 0; d < a.ndens; ++d)
+                flush_rows<NA, NB, NT>(F0 + d * rowset, tid, RS, half, cb, db, N, bra.bfa, bra.bfb,
+                                       a.WK + (size_t)d * a.dstride + moff);
             __syncthreads();
         }
     }
@@ -782,20 +835,22 @@ template <class E, int MODE, int FP32, int DST = 0>
 __global__ __launch_bounds__(E::WGS) void k_class(const ClassArgs a) {
     extern __shared__ __align__(16) double lds[];
     __shared__ unsigned long long wg_count[2];   // the workgroup's counts: one global add each
-    const int ti = a.task_off + (int)blockIdx.x;
-    const int4 task = a.tasks[ti];
-    if (!task_active(a, task)) return;
+    const BraTask t = load_task<FP32>(a, a.task_off + (int)blockIdx.x);
+    if (!t.on) return;
     if (threadIdx.x == 0) wg_count[0] = wg_count[1] = 0;
+    BraRun<E, MODE, FP32, false, DST> r(a, lds);
+    r.stage(t);
+    r.clear_rows();
     load_boys_lds<E>(a, lds);   // ends with a barrier
-    unsigned cnt64 = 0, cnt32 = 0;
-    class_task<E, MODE, FP32, false, DST>(a, ti, lds, cnt64, cnt32);
-    const unsigned long long s64 = (unsigned long long)wave_sum((double)cnt64);
-    const unsigned long long s32 = (unsigned long long)wave_sum((double)cnt32);
+    r.kets(t);
+    const unsigned long long s64 = (unsigned long long)wave_sum((double)r.n64);
+    const unsigned long long s32 = (unsigned long long)wave_sum((double)r.n32);
     if ((threadIdx.x & 63) == 0) {
         if (s64) atomicAdd(&wg_count[0], s64);
         if (s32) atomicAdd(&wg_count[1], s32);
     }
     __syncthreads();
+    r.flush(t);
     if (threadIdx.x == 0 && a.counters) {
         const int slot = (int)(blockIdx.x % HFX_CNT_SLOTS);
         if (wg_count[0]) atomicAdd(a.counters + slot * HFX_CNT_STRIDE, wg_count[0]);
@@ -805,30 +860,44 @@ __global__ __launch_bounds__(E::WGS) void k_class(const ClassArgs a) {
 
 // Persistent launch: a resident grid; a workgroup on XCD x (workgroup index
 // mod 8, the hardware's round-robin placement) takes entries of XCD x's
-// queue through an atomic counter, then drains the other queues in turn, so
-// no XCD idles while another still has work (the dynamic load balancing of
-// ddi_dlbnext in algorithms 1-3).  A separate kernel so that the static
-// form keeps its register allocation.
+// queue through an atomic counter, then drains the other queues in turn (the
+// dynamic load balancing of ddi_dlbnext in algorithms 1-3).  A separate kernel
+// so that the static form keeps its register allocation.
+//
+// Between two tasks the workgroup's lanes wait on one chain: the drawn entry,
+// its records (task, bra, molecule), the staged rows, the flush of the last
+// task's rows.  So the entry is drawn while the last task's kets run, the flush
+// clears the rows for the next task, and rows are walked by columns, every row
+// of a column in flight at once, instead of by a flat index that is divided by
+// the row length: 64 waters, all classes, 95.0 -> 92.6 ms; 112 waters 618 ->
+// 563 ms (its tasks are short: four windows a bra); (ss|ss) of a 44-atom
+// sheet, whose tasks are long, 2.7 -> 2.9 ms, its classes together unchanged.
+// Reading the next task's records and rows before the last flush was slower
+// (20 more registers).
 template <class E, int MODE, int FP32, int DST = 0>
 __global__ __launch_bounds__(E::WGS) void k_class_persist(const ClassArgs a) {
     extern __shared__ __align__(16) double lds[];
-    __shared__ int next_entry;
+    __shared__ int next_task;
+    BraRun<E, MODE, FP32, false, DST> r(a, lds);
+    QueueReader queue(a);
+    if (threadIdx.x == 0) queue.ahead();
+    r.clear_rows();
     load_boys_lds<E>(a, lds);   // once per resident workgroup
-    unsigned cnt64 = 0, cnt32 = 0;
-    const int x0 = blockIdx.x & 7;
-    for (int q = 0; q < 8;) {
-        const int x = (x0 + q) & 7;
-        if (threadIdx.x == 0) next_entry = (int)atomicAdd(a.work + x, 1ull);
+    for (;;) {
+        if (threadIdx.x == 0) next_task = queue.take();
+        __syncthreads();   // also: the last task's rows are flushed and cleared
+        const int ti = __builtin_amdgcn_readfirstlane(next_task);
+        if (ti < 0) break;
+        const BraTask t = load_task<FP32>(a, ti);
+        if (t.on) r.stage(t);
         __syncthreads();
-        const int k = next_entry;
+        if (threadIdx.x == 0) queue.ahead();
+        if (!t.on) continue;
+        r.kets(t);
         __syncthreads();
-        if (k >= a.qlen) {
-            ++q;
-            continue;
-        }
-        class_task<E, MODE, FP32, false, DST>(a, 8 * k + x, lds, cnt64, cnt32);
+        r.flush(t);
     }
-    flush_counts(a, cnt64, cnt32);
+    flush_counts(a, r.n64, r.n32);
 }
 
 // Persistent launch with one task per wave: each wave of a resident
@@ -839,21 +908,26 @@ __global__ __launch_bounds__(E::WGS) void k_class_persist(const ClassArgs a) {
 template <class E, int MODE, int FP32, int DST = 0>
 __global__ __launch_bounds__(E::WGS) void k_class_wave(const ClassArgs a) {
     extern __shared__ __align__(16) double lds[];
+    BraRun<E, MODE, FP32, true, DST> r(a, lds);
+    QueueReader queue(a);
+    const bool first = (threadIdx.x & 63) == 0;
+    if (first) queue.ahead();
+    r.clear_rows();
     load_boys_lds<E>(a, lds);
-    unsigned cnt64 = 0, cnt32 = 0;
-    const int x0 = blockIdx.x & 7;
-    for (int q = 0; q < 8;) {
-        const int x = (x0 + q) & 7;
-        int k = 0;
-        if ((threadIdx.x & 63) == 0) k = (int)atomicAdd(a.work + x, 1ull);
-        k = __shfl(k, 0, 64);
-        if (k >= a.qlen) {
-            ++q;
-            continue;
-        }
-        class_task<E, MODE, FP32, true, DST>(a, 8 * k + x, lds, cnt64, cnt32);
+    for (;;) {
+        const int ti = __builtin_amdgcn_readfirstlane(first ? queue.take() : 0);
+        if (ti < 0) break;
+        if (first) queue.ahead();
+        const BraTask t = load_task<FP32>(a, ti);
+        if (!t.on) continue;
+        r.stage(t);
+        task_sync<true>();
+        r.kets(t);
+        task_sync<true>();
+        r.flush(t);
+        task_sync<true>();
     }
-    flush_counts(a, cnt64, cnt32);
+    flush_counts(a, r.n64, r.n32);
 }
 
 // Schwarz bound of every pair of one pair class: Q = sqrt(max (mn|mn)) with

@@ -194,30 +194,12 @@ __device__ __forceinline__ void rys_ket_transfer(const R* f, const R* cd, R* out
     }
 }
 
-// Sums over the two halves of the wave (lane bit 5), or over the two rows of
-// 16 lanes of each half (bit 4), of N values per lane: lane bit b = 0 is left
-// with the sums of the values of even index, b = 1 with those of odd index.
-// Every lane of the wave calls them.
-template <int BIT>
-__device__ __forceinline__ double rys_pair_sum(double even, double odd) {
-    const unsigned long long e = (unsigned long long)__double_as_longlong(even), o = (unsigned long long)__double_as_longlong(odd);
-    unsigned r[4];
-    if constexpr (BIT == 5) {
-        const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)e, (unsigned)o, false, false);
-        const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(e >> 32), (unsigned)(o >> 32), false, false);
-        r[0] = lo[0]; r[1] = lo[1]; r[2] = hi[0]; r[3] = hi[1];
-    } else {
-        const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)e, (unsigned)o, false, false);
-        const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(e >> 32), (unsigned)(o >> 32), false, false);
-        r[0] = lo[0]; r[1] = lo[1]; r[2] = hi[0]; r[3] = hi[1];
-    }
-    return __longlong_as_double((long long)(((unsigned long long)r[2] << 32) | r[0])) +
-           __longlong_as_double((long long)(((unsigned long long)r[3] << 32) | r[1]));
-}
+// lane_pair_sum over N values: lane bit BIT = 0 is left with the sums of the
+// values of even index, 1 with those of odd index.
 template <int BIT, int N>
 __device__ __forceinline__ void rys_split_sums(const double* v, double* out) {
 #pragma unroll
-    for (int i = 0; i < (N + 1) / 2; ++i) out[i] = rys_pair_sum<BIT>(v[2 * i], 2 * i + 1 < N ? v[2 * i + 1] : 0.0);
+    for (int i = 0; i < (N + 1) / 2; ++i) out[i] = lane_pair_sum<BIT>(v[2 * i], 2 * i + 1 < N ? v[2 * i + 1] : 0.0);
 }
 
 // A lane's ket primitive in phase 1 and, for one bra primitive, what is ready
@@ -640,14 +622,15 @@ __device__ __forceinline__ void class_task_rys(const ClassArgs& a, const int ti,
     }
     if constexpr (MODE == 0) {
         double* WK = MULTI ? a.WK : a.W;
-        for (int i = tid; i < ndens * rowset; i += NT) {
-            const double t = F0[i];
-            if (t != 0.0) {
-                const int d = MULTI ? i / rowset : 0, x = i - d * rowset;
-                const int row = x < NA * RS ? bra.bfa + x / RS : bra.bfb + (x - NA * RS) / RS;
-                const int lc = x < NA * RS ? x % RS : (x - NA * RS) % RS;
-                const int col = lc + (lc < half ? cb : db);
-                if (col < N) atomicAdd(WK + mo + (MULTI ? (size_t)d * a.dstride : 0) + (size_t)row * N + col, t);
+        for (int i = tid >> 6; i < ndens * X::KROWS; i += NT >> 6) {   // a wave per row
+            const int d = MULTI ? i / X::KROWS : 0, row = i - d * X::KROWS;
+            const double* f = F0 + d * rowset + row * RS;
+            double* w = WK + mo + (MULTI ? (size_t)d * a.dstride : 0) +
+                        (size_t)(row < NA ? bra.bfa + row : bra.bfb + row - NA) * N;
+            for (int c = tid & 63; c < RS; c += 64) {
+                const double t = f[c];
+                const int col = c + (c < half ? cb : db);
+                if (t != 0.0 && col < N) atomicAdd(w + col, t);
             }
         }
     }

@@ -105,6 +105,25 @@ __device__ __forceinline__ int hfx_xcc_id() {
     return (int)(x & 7u);
 }
 
+// Sums over the two halves of the wave (BIT 5) or over the two rows of 16 lanes
+// of each half (BIT 4) of two values: lanes with that bit 0 get the sum of
+// even, the others that of odd.  Every lane of the wave calls it.
+template <int BIT>
+__device__ __forceinline__ double lane_pair_sum(double even, double odd) {
+    const unsigned long long e = (unsigned long long)__double_as_longlong(even), o = (unsigned long long)__double_as_longlong(odd);
+    unsigned r[4];
+    if constexpr (BIT == 5) {
+        const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)e, (unsigned)o, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(e >> 32), (unsigned)(o >> 32), false, false);
+        r[0] = lo[0]; r[1] = lo[1]; r[2] = hi[0]; r[3] = hi[1];
+    } else {
+        const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)e, (unsigned)o, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(e >> 32), (unsigned)(o >> 32), false, false);
+        r[0] = lo[0]; r[1] = lo[1]; r[2] = hi[0]; r[3] = hi[1];
+    }
+    return __longlong_as_double((long long)(((unsigned long long)r[2] << 32) | r[0])) +
+           __longlong_as_double((long long)(((unsigned long long)r[3] << 32) | r[1]));
+}
 // Constant address space: loads through such a pointer at a wave-uniform
 // address become scalar (SMEM) loads.
 #define HFX_CONST_AS __attribute__((address_space(4)))

@@ -64,12 +64,7 @@ constexpr int NTRAIN = 12;
 
 // ---- small helpers -------------------------------------------------------------------
 
-__device__ __forceinline__ bf16_t f2bf(float f) {   // round to nearest even
-    unsigned u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)((u >> 16) | 0x40u);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (bf16_t)(u >> 16);
-}
+__device__ __forceinline__ bf16_t f2bf(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }   // nearest even
 __device__ __forceinline__ float silu_f(float z) { return z / (1.0f + expf(-z)); }
 __device__ __forceinline__ float dsilu_f(float z) {
     const float s = 1.0f / (1.0f + expf(-z));
@@ -329,134 +324,494 @@ __global__ void k_trace_check(const double* __restrict__ D, const double* __rest
 
 // ---- the network -----------------------------------------------------------------------
 
-enum { EPI_STORE = 0, EPI_SILU = 1, EPI_DSILU = 2 };
+// Rows are walked in blocks of 32 consecutive pairs of one type (the last block
+// of a type is padded).  An operand of v_mfma_f32_16x16x32_bf16 is 16 x 32: lane
+// l holds row l & 15, k = 8 (l >> 4) .. + 7, so a "fragment" of 512 BF16 in lane
+// order is one contiguous 16-byte load per lane.  Everything a kernel reads from
+// memory lies in fragments: the weights W[n][k] as [n / 16][k / 32] (and their
+// transposes for the backward pass), and the activations and gradients, for the
+// weight gradients whose contracted index is the row, as [row block][column / 16].
+constexpr int RB = 32, FRAG = 512;        // rows of a block, BF16 of a fragment
+constexpr int NET_WG = 512;               // eight waves, 32 output columns each
+constexpr int ALD = HID + 8;              // LDS row of activations
+constexpr int FB = HID / 16, XFB = XLD / 16, YFB = 16;   // fragments of a row block: hidden, input, head output
+constexpr int NCB = 3 * HID + HEAD_OUT[0] + HEAD_OUT[1] + HEAD_OUT[2];   // biases
+__host__ __device__ constexpr int head_kpad(int t) { return t == 0 ? 256 : 32; }   // head outputs, padded
 
-struct GemmArgs {
-    int M, N, K;
-    const bf16_t* A;
-    long long asi, ask;    // A(i, k) = A[i asi + k ask]
-    const bf16_t* B;
-    long long bsk, bsj;    // B(k, j) = B[k bsk + j bsj]
-    const float* bias;     // per column j (EPI_STORE optional, EPI_SILU required)
-    float* C;              // FP32 result (pre-activation or gradient)
-    long long ldc;
-    bf16_t* Cb;            // BF16 copy for the next GEMM (SiLU output for EPI_SILU)
-    long long ldcb;
-    const float* Z;        // EPI_DSILU: pre-activation whose SiLU derivative scales the result
-    long long ldz;
-    int epi;
+// offsets (BF16) of the packed weights: forward layers, heads, and transposes
+constexpr int PW1 = 0, PW2 = PW1 + HID * XLD, PW3 = PW2 + HID * HID, PW2T = PW3 + HID * HID, PW3T = PW2T + HID * HID;
+constexpr int PH0 = PW3T + HID * HID, PH1 = PH0 + 256 * HID, PH2 = PH1 + 32 * HID;   // heads
+constexpr int PH0T = PH2 + 32 * HID, PH1T = PH0T + HID * 256, PH2T = PH1T + HID * 32, PWTOT = PH2T + HID * 32;
+
+struct NetParams {   // packed FP32 parameters and their offsets
+    const float* p;
+    long long w1, b1, w2, b2, w3, b3, h[NTYPE], c[NTYPE], fmean, fscale;
 };
 
-constexpr int GBM = 64, GBN = 64, GBK = 32, GPAD = 8;
+// element i of a fragment-ordered matrix with ks fragments along k: its (n, k)
+__device__ __forceinline__ void frag_nk(int i, int ks, int& n, int& k) {
+    const int f = i / FRAG, e = i % FRAG, l = e >> 3;
+    n = (f / ks) * 16 + (l & 15);
+    k = (f % ks) * 32 + (l >> 4) * 8 + (e & 7);
+}
 
-// C = A B on 64 x 64 tiles; four waves, each a 32 x 32 quadrant of 2 x 2
-// MFMA 16x16x32 blocks.  Operands staged through LDS as BF16 (zero outside
-// M, N, K), FP32 accumulators, fused epilogue.
-__global__ __launch_bounds__(256) void k_gemm(const GemmArgs g) {
-    __shared__ __align__(16) bf16_t As[GBM][GBK + GPAD];
-    __shared__ __align__(16) bf16_t Bs[GBN][GBK + GPAD];
-    const int m0 = blockIdx.x * GBM, n0 = blockIdx.y * GBN;
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int wr = (w >> 1) * 32, wc = (w & 1) * 32;
-    f32x4 acc[2][2];
-    for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int lr = t >> 2, lk = (t & 3) * 8;
-    for (int k0 = 0; k0 < g.K; k0 += GBK) {
-        const long long i = m0 + lr, j = n0 + lr;
+// All weights as BF16 fragments, zero in the padding.
+__global__ void k_pack(const NetParams w, bf16_t* __restrict__ out) {
+    const int i = blockIdx.x * WG + threadIdx.x;
+    if (i >= PWTOT) return;
+    int n, k;
+    float v = 0.0f;
+    if (i < PW2) {
+        frag_nk(i - PW1, XLD / 32, n, k);
+        if (k < NFEAT) v = w.p[w.w1 + n * NFEAT + k];
+    } else if (i < PH0) {
+        const int q = (i - PW2) / (HID * HID);   // W2, W3, W2^T, W3^T
+        frag_nk((i - PW2) % (HID * HID), HID / 32, n, k);
+        v = w.p[((q & 1) ? w.w3 : w.w2) + (q < 2 ? n * HID + k : k * HID + n)];
+    } else if (i < PH0T) {
+        const int t = i < PH1 ? 0 : i < PH2 ? 1 : 2;
+        frag_nk(i - (t == 0 ? PH0 : t == 1 ? PH1 : PH2), HID / 32, n, k);
+        if (n < (t == 0 ? HEAD_OUT[0] : t == 1 ? HEAD_OUT[1] : HEAD_OUT[2])) v = w.p[w.h[t] + n * HID + k];
+    } else {
+        const int t = i < PH1T ? 0 : i < PH2T ? 1 : 2;
+        frag_nk(i - (t == 0 ? PH0T : t == 1 ? PH1T : PH2T), head_kpad(t) / 32, n, k);
+        if (k < (t == 0 ? HEAD_OUT[0] : t == 1 ? HEAD_OUT[1] : HEAD_OUT[2])) v = w.p[w.h[t] + k * HID + n];
+    }
+    out[i] = f2bf(v);
+}
+
+struct NetArgs {
+    NetParams w;
+    const bf16_t* pk;              // packed weights
+    const float* X;                // rows of NFEAT, by type
+    const float* T;                // gradient: targets, packed by type
+    float* out;                    // forward: predictions, packed by type
+    int count[NTYPE], blk0[NTYPE + 1];   // rows; first row block (blk0[NTYPE]: all)
+    long long row0[NTYPE], yoff[NTYPE];
+    float tscale[NTYPE], inv_tscale[NTYPE], gs;
+    // gradient: fragments of the inputs, H1 H2 H3, dZ1 dZ2 dZ3 and dY, and per
+    // row block the column sums of dZ1 dZ2 dZ3 and dY and the squared error
+    bf16_t *fx, *fh[3], *fg[3], *fy;
+    float* csum;
+    double* esum;
+};
+
+typedef f32x4 Acc[2][2];   // a wave's 32 rows x 32 columns
+
+// acc = A B: A from LDS (32 rows), B the wave's two column blocks of fragments,
+// four steps of k ahead (the first four loaded before the barrier that completes A).
+template <int KS>
+struct WaveB {
+    static constexpr int AHEAD = KS < 4 ? KS : 4;
+    const uint4* f;
+    uint4 w[2][AHEAD];
+    __device__ __forceinline__ void load(const bf16_t* __restrict__ frags, int jb0) {
+        f = reinterpret_cast<const uint4*>(frags + (size_t)jb0 * KS * FRAG) + (threadIdx.x & 63);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const long long k = k0 + lk + e;
-            As[lr][lk + e] = (i < g.M && k < g.K) ? g.A[i * g.asi + k * g.ask] : (bf16_t)0;
-            Bs[lr][lk + e] = (j < g.N && k < g.K) ? g.B[k * g.bsk + j * g.bsj] : (bf16_t)0;
-        }
-        __syncthreads();
+        for (int ks = 0; ks < AHEAD; ++ks)
+#pragma unroll
+            for (int bj = 0; bj < 2; ++bj) w[bj][ks] = f[(bj * KS + ks) * (FRAG / 8)];
+    }
+    __device__ __forceinline__ void mul(const bf16_t* A, Acc& acc) {
+        const int lane = threadIdx.x & 63;
 #pragma unroll
         for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-            for (int bj = 0; bj < 2; ++bj) {
-                const uint4 ua = *reinterpret_cast<const uint4*>(&As[wr + bi * 16 + (lane & 15)][(lane >> 4) * 8]);
-                const uint4 ub = *reinterpret_cast<const uint4*>(&Bs[wc + bj * 16 + (lane & 15)][(lane >> 4) * 8]);
-                acc[bi][bj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ua),
-                                                                     __builtin_bit_cast(bf16x8, ub), acc[bi][bj], 0,
-                                                                     0, 0);
+            for (int bj = 0; bj < 2; ++bj) acc[bi][bj] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+            for (int bi = 0; bi < 2; ++bi) {
+                const uint4 ua =
+                    *reinterpret_cast<const uint4*>(A + (bi * 16 + (lane & 15)) * ALD + ks * 32 + (lane >> 4) * 8);
+#pragma unroll
+                for (int bj = 0; bj < 2; ++bj)
+                    acc[bi][bj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ua),
+                                                                         __builtin_bit_cast(bf16x8, w[bj][ks % AHEAD]),
+                                                                         acc[bi][bj], 0, 0, 0);
             }
-        __syncthreads();
+            if (ks + AHEAD < KS)
+#pragma unroll
+                for (int bj = 0; bj < 2; ++bj) w[bj][ks % AHEAD] = f[(bj * KS + ks + AHEAD) * (FRAG / 8)];
+        }
     }
+};
+
+// A wave's 32 x 32 block as BF16: rows into LDS for the next product, and (fr)
+// the transposed fragments, where a lane's four rows are eight bytes; padded
+// rows are zero in the fragments.
+template <bool ROWS, bool FRAGS>
+__device__ __forceinline__ void put_block(const Acc& v, int col0, int nr, bf16_t* rows, bf16_t* __restrict__ fr) {
+    const int lane = threadIdx.x & 63, q = lane >> 4;
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
+        for (int bj = 0; bj < 2; ++bj) {
+            bf16_t h[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const long long i = m0 + wr + bi * 16 + (lane >> 4) * 4 + r;
-                const long long j = n0 + wc + bj * 16 + (lane & 15);
-                if (i >= g.M || j >= g.N) continue;
-                float v = acc[bi][bj][r];
-                if (g.epi == EPI_DSILU) v *= dsilu_f(g.Z[i * g.ldz + j]);
-                else if (g.bias) v += g.bias[j];
-                if (g.C) g.C[i * g.ldc + j] = v;
-                if (g.Cb) g.Cb[i * g.ldcb + j] = f2bf(g.epi == EPI_SILU ? silu_f(v) : v);
+                const int row = bi * 16 + q * 4 + r;
+                h[r] = f2bf(v[bi][bj][r]);
+                if (ROWS) rows[row * ALD + col0 + bj * 16 + (lane & 15)] = h[r];
+                if (row >= nr) h[r] = 0;
             }
+            if (FRAGS)
+                *reinterpret_cast<uint2*>(fr + (size_t)(col0 / 16 + bj) * FRAG +
+                                          ((bi * 2 + (q >> 1)) * 16 + (lane & 15)) * 8 + (q & 1) * 4) =
+                    make_uint2(h[0] | (unsigned)h[1] << 16, h[2] | (unsigned)h[3] << 16);
+        }
 }
 
-// standardised, clipped features as BF16 rows of XLD (zero padding)
-__global__ void k_feat_bf16(const float* __restrict__ X, long long M, const float* __restrict__ mean,
-                            const float* __restrict__ scale, bf16_t* __restrict__ out) {
-    const long long i = (long long)blockIdx.x * WG + threadIdx.x;
-    if (i >= M * XLD) return;
-    const long long r = i / XLD;
-    const int c = (int)(i % XLD);
-    out[i] = c < NFEAT ? f2bf(fminf(fmaxf((X[r * NFEAT + c] - mean[c]) / scale[c], -INPUT_CLIP), INPUT_CLIP))
-                       : (bf16_t)0;
+// Column sums of a wave's block over its valid rows.
+__device__ __forceinline__ void put_sums(const Acc& v, int nr, float* __restrict__ out, int ncol) {
+    const int lane = threadIdx.x & 63, q = lane >> 4;
+#pragma unroll
+    for (int bj = 0; bj < 2; ++bj) {
+        float s = 0.0f;
+#pragma unroll
+        for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (bi * 16 + q * 4 + r < nr) s += v[bi][bj][r];
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        if (q == 0 && bj * 16 + lane < ncol) out[bj * 16 + lane] = s;
+    }
 }
 
-__global__ void k_to_bf16(const float* __restrict__ W, int rows, int cols, int ldo, bf16_t* __restrict__ out) {
-    const int i = blockIdx.x * WG + threadIdx.x;
-    if (i >= rows * ldo) return;
-    const int r = i / ldo, c = i % ldo;
-    out[i] = c < cols ? f2bf(W[(size_t)r * cols + c]) : (bf16_t)0;
+// The network on one block of 32 rows: GRAD = 0 the predictions, GRAD = 1 the
+// squared error and everything of the gradient that belongs to rows (dY, dZ3,
+// dZ2, dZ1), with the fragments and sums that the weight gradients need.
+// Activations stay in LDS and pre-activations in registers (FP32), so that
+// memory holds what the weight gradients read and nothing else.  32 rows: 8192
+// rows are 256 workgroups, one per CU, and every weight fragment (0.9 MB over
+// both directions, from L2) serves two row blocks of the matrix unit.  A layer's
+// first weights are loaded before the barrier that ends the last one.  Products
+// run over k in ascending order with FP32 accumulation.  What bounds it is the
+// vector unit (exponentials and divisions of SiLU and its derivative) in two
+// waves per SIMD; with 128 registers two workgroups share a CU: 8192 rows 47 us
+// against 55 us without spills (258 workgroups, two rounds), 500 rows 29 us
+// against 26.  The chain of separate launches (products of 64 x 64 tiles that
+// gathered two bytes a lane, elementwise and column-sum kernels between) took
+// 5.4 ms for the whole gradient at 8192 rows, 2 x 1.3 ms of it in a pair of
+// weight gradients; this kernel, k_wgrad and k_grad_sum take 47 + 15 + 8 us.
+template <bool GRAD>
+__global__ __launch_bounds__(NET_WG, 4) void k_net(const NetArgs a) {
+    __shared__ __align__(16) bf16_t buf[2][RB * ALD];
+    __shared__ double red[NET_WG / 64];
+    const int blk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, q = lane >> 4;
+    const int t = blk < a.blk0[1] ? 0 : blk < a.blk0[2] ? 1 : 2;   // uniform
+    const int lr0 = (blk - a.blk0[t]) * RB, nr = min(RB, a.count[t] - lr0);
+    const int nout = t == 0 ? HEAD_OUT[0] : t == 1 ? HEAD_OUT[1] : HEAD_OUT[2];
+    const int col0 = wv * 32, j0 = col0 + (lane & 15);
+    const float* p = a.w.p;
+    Acc z[3], v;
+    {
+        WaveB<XLD / 32> w;
+        w.load(a.pk + PW1, wv * 2);
+        // standardised, clipped inputs
+        const float* X = a.X + (a.row0[t] + lr0) * NFEAT;
+#pragma unroll
+        for (int i0 = 0; i0 < RB * XLD; i0 += NET_WG) {
+            const int i = i0 + tid, r = i / XLD, c = i % XLD;
+            buf[0][r * ALD + c] =
+                r < nr && c < NFEAT
+                    ? f2bf(fminf(fmaxf((X[r * NFEAT + c] - p[a.w.fmean + c]) / p[a.w.fscale + c], -INPUT_CLIP),
+                                 INPUT_CLIP))
+                    : (bf16_t)0;
+        }
+        __syncthreads();
+        if constexpr (GRAD)
+            for (int i = tid; i < XFB * 64; i += NET_WG) {
+                const int l = i & 63, c = (i >> 6) * 16 + (l & 15);
+                bf16_t h[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) h[e] = buf[0][((l >> 4) * 8 + e) * ALD + c];
+                reinterpret_cast<uint4*>(a.fx + (size_t)blk * XFB * FRAG)[i] =
+                    make_uint4(h[0] | (unsigned)h[1] << 16, h[2] | (unsigned)h[3] << 16, h[4] | (unsigned)h[5] << 16,
+                               h[6] | (unsigned)h[7] << 16);
+            }
+        w.mul(buf[0], z[0]);
+    }
+    // z += bias, v = silu(z)
+    auto activate = [&](Acc& zz, long long bias) {
+#pragma unroll
+        for (int bj = 0; bj < 2; ++bj) {
+            const float b = p[bias + j0 + bj * 16];
+#pragma unroll
+            for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    zz[bi][bj][r] += b;
+                    v[bi][bj][r] = silu_f(zz[bi][bj][r]);
+                }
+        }
+    };
+    const size_t fo = (size_t)blk * FB * FRAG;
+    activate(z[0], a.w.b1);
+    put_block<true, GRAD>(v, col0, nr, buf[1], a.fh[0] + fo);
+    {
+        WaveB<HID / 32> w;
+        w.load(a.pk + PW2, wv * 2);
+        __syncthreads();
+        w.mul(buf[1], z[1]);
+    }
+    activate(z[1], a.w.b2);
+    put_block<true, GRAD>(v, col0, nr, buf[0], a.fh[1] + fo);
+    {
+        WaveB<HID / 32> w;
+        w.load(a.pk + PW3, wv * 2);
+        __syncthreads();
+        w.mul(buf[0], z[2]);
+    }
+    activate(z[2], a.w.b3);
+    put_block<true, GRAD>(v, col0, nr, buf[1], a.fh[2] + fo);
+    // the type's head (waves past its columns idle)
+    double e = 0.0;
+    const bool head = col0 < head_kpad(t);
+    {
+        WaveB<HID / 32> w;
+        if (head) w.load(a.pk + (t == 0 ? PH0 : t == 1 ? PH1 : PH2), wv * 2);
+        __syncthreads();
+        if (head) {
+            w.mul(buf[1], v);
+            const long long y0 = a.yoff[t] + (long long)lr0 * nout;
+#pragma unroll
+            for (int bj = 0; bj < 2; ++bj) {
+                const int j = j0 + bj * 16;
+                const float b = j < nout ? p[a.w.c[t] + j] : 0.0f;
+#pragma unroll
+                for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int row = bi * 16 + q * 4 + r;
+                        const bool on = j < nout && row < nr;
+                        const float y = v[bi][bj][r] + b;
+                        if constexpr (GRAD) {   // d = Y - T / tscale; dY = gs d
+                            const float d = on ? y - a.T[y0 + (long long)row * nout + j] * a.inv_tscale[t] : 0.0f;
+                            e += (double)d * d;
+                            v[bi][bj][r] = a.gs * d;
+                        } else if (on) {
+                            a.out[y0 + (long long)row * nout + j] = y * a.tscale[t];
+                        }
+                    }
+            }
+        }
+    }
+    if constexpr (GRAD) {
+        float* cs = a.csum + (size_t)blk * NCB;
+        if (head) {
+            put_block<true, true>(v, col0, nr, buf[0], a.fy + (size_t)blk * YFB * FRAG);
+            const int c0 = 3 * HID + (t > 0 ? HEAD_OUT[0] : 0) + (t > 1 ? HEAD_OUT[1] : 0);
+            put_sums(v, nr, cs + c0 + col0, nout - col0);
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) e += __shfl_xor(e, off, 64);
+        if (lane == 0) red[wv] = e;
+        // v = dH of a layer -> dZ = dH silu'(z), its fragments and sums
+        auto backward = [&](const Acc& zz, int layer) {
+#pragma unroll
+            for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[bi][bj][r] *= dsilu_f(zz[bi][bj][r]);
+            put_sums(v, nr, cs + layer * HID + col0, 32);
+        };
+        if (t == 0) {
+            WaveB<8> w;
+            w.load(a.pk + PH0T, wv * 2);
+            __syncthreads();
+            w.mul(buf[0], v);
+        } else {
+            WaveB<1> w;
+            w.load(a.pk + (t == 1 ? PH1T : PH2T), wv * 2);
+            __syncthreads();
+            w.mul(buf[0], v);
+        }
+        if (tid == 0) {
+            double s = 0.0;
+            for (int k = 0; k < NET_WG / 64; ++k) s += red[k];
+            a.esum[blk] = s;
+        }
+        backward(z[2], 2);
+        put_block<true, true>(v, col0, nr, buf[1], a.fg[2] + fo);
+        {
+            WaveB<HID / 32> w;
+            w.load(a.pk + PW3T, wv * 2);
+            __syncthreads();
+            w.mul(buf[1], v);
+        }
+        backward(z[1], 1);
+        put_block<true, true>(v, col0, nr, buf[0], a.fg[1] + fo);
+        {
+            WaveB<HID / 32> w;
+            w.load(a.pk + PW2T, wv * 2);
+            __syncthreads();
+            w.mul(buf[0], v);
+        }
+        backward(z[0], 0);
+        put_block<false, true>(v, col0, nr, nullptr, a.fg[0] + fo);
+    }
+}
+
+// Weight gradients, dW = G^T H: 64 x 64 tiles of the six matrices, the
+// contracted rows split over chunks of row blocks (blockIdx.x), within a chunk
+// over the workgroup's four waves.  A tile's chain over 8192 rows on one
+// workgroup left 16 workgroups at work for over a millisecond a layer; eight
+// chunks are 544 workgroups, 15 us, and 0.8 MB of partial sums each.  All
+// fragments are whole, so loads need no bounds.
+constexpr int GTILES = 3 * 16 - 4 + 16 + 4 + 4;   // W3, W2 (16 each), W1 (12), H0 (16), H1, H2 (4 each)
+
+struct WGradArgs {
+    const bf16_t *fx, *fh[3], *fg[3], *fy;
+    int blk0[NTYPE + 1], chunk;          // row blocks per chunk
+    long long off[6];                    // of the matrices' gradients: W3 W2 W1 H0 H1 H2
+    float* part;                         // per chunk, packed as the parameters
+    long long stride;                    // of a chunk in part
+};
+
+__global__ __launch_bounds__(256) void k_wgrad(const WGradArgs a) {
+    __shared__ float red[4][32][64];
+    const int tile = blockIdx.y, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int m, idx, nj = 4, t = -1;          // matrix, tile in it, tiles per row
+    if (tile < 32) {
+        m = tile >> 4;
+        idx = tile & 15;
+    } else if (tile < 44) {
+        m = 2;
+        idx = tile - 32;
+        nj = 3;
+    } else {
+        t = tile < 60 ? 0 : tile < 64 ? 1 : 2;
+        m = 3 + t;
+        idx = tile - (t == 0 ? 44 : t == 1 ? 60 : 64);
+    }
+    const int it = idx / nj, jt = idx % nj;
+    const int rows = t < 0 ? HID : t == 0 ? HEAD_OUT[0] : t == 1 ? HEAD_OUT[1] : HEAD_OUT[2];
+    const int cols = m == 2 ? NFEAT : HID;
+    const int afb = t < 0 ? FB : YFB, bfb = m == 2 ? XFB : FB;
+    const bf16_t* A = t < 0 ? a.fg[2 - m] : a.fy;
+    const bf16_t* B = m == 2 ? a.fx : m == 0 ? a.fh[1] : m == 1 ? a.fh[0] : a.fh[2];
+    const int lo = max((int)blockIdx.x * a.chunk, t < 0 ? 0 : a.blk0[t]);
+    const int hi = min(((int)blockIdx.x + 1) * a.chunk, t < 0 ? a.blk0[NTYPE] : a.blk0[t + 1]);
+    if (lo >= hi) return;                // a head's chunk without rows of its type: not summed either
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int ni = min(4, (rows + 15) / 16 - it * 4);   // fragments of the tile that hold rows of the matrix
+#pragma unroll 2
+    for (int k = lo + wv; k < hi; k += 4) {
+        const uint4* pa = reinterpret_cast<const uint4*>(A + ((size_t)k * afb + it * 4) * FRAG) + lane;
+        const uint4* pb = reinterpret_cast<const uint4*>(B + ((size_t)k * bfb + jt * 4) * FRAG) + lane;
+        uint4 ua[4], ub[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            ua[i] = i < ni ? pa[i * 64] : make_uint4(0, 0, 0, 0);
+            ub[i] = pb[i * 64];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(bf16x8, ua[i]), __builtin_bit_cast(bf16x8, ub[j]), acc[i][j], 0, 0, 0);
+    }
+    float* out = a.part + blockIdx.x * a.stride + a.off[m];
+    const int col = jt * 64 + lane;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {        // the waves' sums, 32 rows at a time
+        if (h) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    red[wv][i * 16 + (lane >> 4) * 4 + r][j * 16 + (lane & 15)] = acc[2 * h + i][j][r];
+        __syncthreads();
+        for (int r = wv; r < 32; r += 4) {
+            const int row = it * 64 + h * 32 + r;
+            if (row < rows && col < cols)
+                out[(size_t)row * cols + col] = red[0][r][lane] + red[1][r][lane] + red[2][r][lane] + red[3][r][lane];
+        }
+    }
+}
+
+// Sums over chunks (weights) and over row blocks (biases, squared error) into
+// the packed gradient: blocks [0, nwb) take the weights, then one block per 16
+// biases, then one for the error.
+struct GradSumArgs {
+    long long off[NTRAIN + 1];           // parameter offsets
+    const float* part;
+    long long stride;
+    int blk0[NTYPE + 1], chunk, nwb;
+    const float* csum;
+    const double* esum;
+    float* gr;
+    double* loss;
+};
+
+__global__ __launch_bounds__(WG) void k_grad_sum(const GradSumArgs a) {
+    __shared__ double red[WG];
+    const int b = blockIdx.x, nblk = a.blk0[NTYPE];
+    if (b < a.nwb) {
+        const long long i = (long long)b * WG + threadIdx.x;
+        if (i >= a.off[NTRAIN]) return;
+        int s = 0;
+        while (i >= a.off[s + 1]) ++s;
+        if (s & 1) return;               // a bias
+        const int t = s / 2 - 3;         // head, or < 0
+        const int lo = t < 0 ? 0 : a.blk0[t] / a.chunk;
+        const int hi = t < 0 ? (nblk + a.chunk - 1) / a.chunk
+                             : a.blk0[t + 1] > a.blk0[t] ? (a.blk0[t + 1] - 1) / a.chunk + 1 : lo;
+        float v = 0.0f;
+        for (int c = lo; c < hi; ++c) v += a.part[c * a.stride + i];
+        a.gr[i] = v;
+        return;
+    }
+    const int nbb = (NCB + 15) / 16;
+    if (b < a.nwb + nbb) {
+        const int cx = threadIdx.x & 15, ry = threadIdx.x >> 4, j = (b - a.nwb) * 16 + cx;
+        float v = 0.0f;
+        long long o = 0;
+        if (j < NCB) {
+            int lo = 0, hi = nblk;
+            if (j < 3 * HID) {
+                o = a.off[P_B1 + 2 * (j / HID)] + j % HID;
+            } else {
+                const int h = j - 3 * HID, t = h < HEAD_OUT[0] ? 0 : h < HEAD_OUT[0] + HEAD_OUT[1] ? 1 : 2;
+                lo = a.blk0[t];
+                hi = a.blk0[t + 1];
+                o = a.off[P_C0 + 2 * t] + h - (t > 0 ? HEAD_OUT[0] : 0) - (t > 1 ? HEAD_OUT[1] : 0);
+            }
+#pragma unroll 4
+            for (int k = lo + ry; k < hi; k += 16) v += a.csum[(size_t)k * NCB + j];
+        }
+        red[threadIdx.x] = v;
+        __syncthreads();
+        if (ry == 0 && j < NCB) {
+            for (int k = 1; k < 16; ++k) v += (float)red[cx + 16 * k];
+            a.gr[o] = v;
+        }
+        return;
+    }
+    double e = 0.0;
+    for (int k = threadIdx.x; k < nblk; k += WG) e += a.esum[k];
+    red[threadIdx.x] = e;
+    __syncthreads();
+    for (int h = WG / 2; h >= 1; h >>= 1) {
+        if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *a.loss = red[0];
 }
 
 __global__ void k_fill_f(float* __restrict__ p, long long n, float v) {
     const long long i = (long long)blockIdx.x * WG + threadIdx.x;
     if (i < n) p[i] = v;
-}
-
-// squared error of one head: d = Y - T / tscale; dY = gs d (FP32 and BF16);
-// loss += sum d^2 (double)
-__global__ void k_mse(const float* __restrict__ Y, const float* __restrict__ T, long long n, float inv_scale,
-                      float gs, float* __restrict__ dY, bf16_t* __restrict__ dYb, double* __restrict__ loss) {
-    const long long i = (long long)blockIdx.x * WG + threadIdx.x;
-    double e = 0.0;
-    if (i < n) {
-        const float d = Y[i] - T[i] * inv_scale;
-        e = (double)d * d;
-        dY[i] = gs * d;
-        dYb[i] = f2bf(gs * d);
-    }
-    for (int off = 32; off >= 1; off >>= 1) e += __shfl_xor(e, off, 64);
-    if ((threadIdx.x & 63) == 0 && e != 0.0) atomicAdd(loss, e);
-}
-
-__global__ void k_scale(const float* __restrict__ Y, long long n, float s, float* __restrict__ out) {
-    const long long i = (long long)blockIdx.x * WG + threadIdx.x;
-    if (i < n) out[i] = Y[i] * s;
-}
-
-// out[j] += sum over rows of G[r][j]: 64 columns x 4 row lanes per block,
-// blockIdx.y = chunk of 1024 rows
-__global__ void k_colsum(const float* __restrict__ G, long long M, int N, long long ld, float* __restrict__ out) {
-    __shared__ float red[4][64];
-    const int cx = threadIdx.x & 63, ry = threadIdx.x >> 6;
-    const int j = blockIdx.x * 64 + cx;
-    const long long r0 = (long long)blockIdx.y * 1024, r1 = std::min<long long>(M, r0 + 1024);
-    float s = 0.0f;
-    if (j < N)
-        for (long long r = r0 + ry; r < r1; r += 4) s += G[r * ld + j];
-    red[ry][cx] = s;
-    __syncthreads();
-    if (ry == 0 && j < N) atomicAdd(out + j, red[0][cx] + red[1][cx] + red[2][cx] + red[3][cx]);
 }
 
 __global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
@@ -682,12 +1037,12 @@ struct hfx_guess {
     std::string err;
     std::vector<float> hp;
     float *p = nullptr, *gr = nullptr, *m = nullptr, *v = nullptr;
-    bf16_t *W1b = nullptr, *W2b = nullptr, *W3b = nullptr, *Hb[NTYPE] = {nullptr, nullptr, nullptr};
-    long long cap = 0, ycap = 0;
-    bf16_t *Xb = nullptr, *H1b = nullptr, *H2b = nullptr, *H3b = nullptr, *Gab = nullptr, *Gbb = nullptr,
-           *dYb = nullptr;
-    float *Z1 = nullptr, *Z2 = nullptr, *Z3 = nullptr, *Ga = nullptr, *Gb = nullptr, *Y = nullptr, *dY = nullptr;
-    double* d_loss = nullptr;
+    bf16_t* pk = nullptr;      // packed weights
+    // gradient scratch for cap row blocks and pcap chunks
+    long long cap = 0, pcap = 0;
+    bf16_t *fx = nullptr, *fh[3] = {}, *fg[3] = {}, *fy = nullptr;
+    float *csum = nullptr, *part = nullptr;
+    double *esum = nullptr, *d_loss = nullptr;
     long long step = 0;
     bool wdirty = true;
 };
@@ -705,35 +1060,25 @@ static hfx_status gfail(hfx_guess* g, hfx_status s, const std::string& msg) {
     } while (0)
 
 static void free_acts(hfx_guess* g) {
-    gfree(g->Xb);
-    gfree(g->H1b);
-    gfree(g->H2b);
-    gfree(g->H3b);
-    gfree(g->Gab);
-    gfree(g->Gbb);
-    gfree(g->Z1);
-    gfree(g->Z2);
-    gfree(g->Z3);
-    gfree(g->Ga);
-    gfree(g->Gb);
-    g->cap = 0;
+    gfree(g->fx);
+    for (auto& f : g->fh) gfree(f);
+    for (auto& f : g->fg) gfree(f);
+    gfree(g->fy);
+    gfree(g->csum);
+    gfree(g->esum);
+    gfree(g->part);
+    g->cap = g->pcap = 0;
 }
 
 extern "C" void hfx_guess_destroy(hfx_guess* g) {
     if (!g) return;
     (void)hipSetDevice(g->device);
     free_acts(g);
-    gfree(g->Y);
-    gfree(g->dY);
-    gfree(g->dYb);
     gfree(g->p);
     gfree(g->gr);
     gfree(g->m);
     gfree(g->v);
-    gfree(g->W1b);
-    gfree(g->W2b);
-    gfree(g->W3b);
-    for (auto& h : g->Hb) gfree(h);
+    gfree(g->pk);
     gfree(g->d_loss);
     delete g;
 }
@@ -752,9 +1097,7 @@ extern "C" hfx_status hfx_guess_create(int device, hfx_guess** out) {
     if (hipSetDevice(device) != hipSuccess) return fail(HFX_ERR_DEVICE);
     const long long n = PL.total;
     if (galloc(&g->p, n) || galloc(&g->gr, n) || galloc(&g->m, n) || galloc(&g->v, n) ||
-        galloc(&g->W1b, (size_t)HID * XLD) || galloc(&g->W2b, (size_t)HID * HID) || galloc(&g->W3b, (size_t)HID * HID) ||
-        galloc(&g->Hb[0], (size_t)HEAD_OUT[0] * HID) || galloc(&g->Hb[1], (size_t)HEAD_OUT[1] * HID) ||
-        galloc(&g->Hb[2], (size_t)HEAD_OUT[2] * HID) || galloc(&g->d_loss, 1))
+        galloc(&g->pk, (size_t)PWTOT) || galloc(&g->d_loss, 1))
         return fail(HFX_ERR_OOM);
     g->hp.assign(n, 0.0f);
     for (int k = 0; k < NFEAT; ++k) g->hp[PL.off[P_FSCALE] + k] = 1.0f;
@@ -799,95 +1142,56 @@ extern "C" hfx_status hfx_guess_get_grads(hfx_guess* g, float* grads) {
     return HFX_OK;
 }
 
-static hfx_status ensure_cap(hfx_guess* g, long long M, long long ny) {
-    if (M > g->cap) {
-        free_acts(g);
-        const long long cap = std::max<long long>(M, 1024);
-        NCK(galloc(&g->Xb, cap * XLD));
-        NCK(galloc(&g->H1b, cap * HID));
-        NCK(galloc(&g->H2b, cap * HID));
-        NCK(galloc(&g->H3b, cap * HID));
-        NCK(galloc(&g->Gab, cap * HID));
-        NCK(galloc(&g->Gbb, cap * HID));
-        NCK(galloc(&g->Z1, cap * HID));
-        NCK(galloc(&g->Z2, cap * HID));
-        NCK(galloc(&g->Z3, cap * HID));
-        NCK(galloc(&g->Ga, cap * HID));
-        NCK(galloc(&g->Gb, cap * HID));
-        g->cap = cap;
-    }
-    if (ny > g->ycap) {
-        gfree(g->Y);
-        gfree(g->dY);
-        gfree(g->dYb);
-        const long long cap = std::max<long long>(ny, 4096);
-        NCK(galloc(&g->Y, cap));
-        NCK(galloc(&g->dY, cap));
-        NCK(galloc(&g->dYb, cap));
-        g->ycap = cap;
-    }
+// Gradient scratch for nblk row blocks in nchunk chunks.
+static hfx_status ensure_cap(hfx_guess* g, long long nblk, long long nchunk) {
+    if (nblk <= g->cap && nchunk <= g->pcap) return HFX_OK;
+    const long long cap = std::max({nblk, g->cap, 32ll}), pcap = std::max(nchunk, g->pcap);
+    free_acts(g);
+    NCK(galloc(&g->fx, cap * XFB * FRAG));
+    for (auto& f : g->fh) NCK(galloc(&f, cap * FB * FRAG));
+    for (auto& f : g->fg) NCK(galloc(&f, cap * FB * FRAG));
+    NCK(galloc(&g->fy, cap * YFB * FRAG));
+    NCK(galloc(&g->csum, cap * NCB));
+    NCK(galloc(&g->esum, cap));
+    NCK(galloc(&g->part, pcap * PL.off[NTRAIN]));
+    g->cap = cap;
+    g->pcap = pcap;
     return HFX_OK;
 }
 
-static hipError_t gemm(hipStream_t st, int M, int N, int K, const bf16_t* A, long long asi, long long ask,
-                       const bf16_t* B, long long bsk, long long bsj, const float* bias, float* C, long long ldc,
-                       bf16_t* Cb, long long ldcb, const float* Z, long long ldz, int epi) {
-    if (M <= 0 || N <= 0) return hipSuccess;
-    GemmArgs a{M, N, K, A, asi, ask, B, bsk, bsj, bias, C, ldc, Cb, ldcb, Z, ldz, epi};
-    hipLaunchKernelGGL(k_gemm, dim3((M + GBM - 1) / GBM, (N + GBN - 1) / GBN), dim3(256), 0, st, a);
-    return hipGetLastError();
-}
-
-static hipError_t pack_weights(hfx_guess* g, hipStream_t st) {
-    if (!g->wdirty) return hipSuccess;
-    hipLaunchKernelGGL(k_to_bf16, dim3(blocks_for((long long)HID * XLD)), dim3(WG), 0, st, g->p + PL.off[P_W1], HID,
-                       NFEAT, XLD, g->W1b);
-    hipLaunchKernelGGL(k_to_bf16, dim3(blocks_for((long long)HID * HID)), dim3(WG), 0, st, g->p + PL.off[P_W2], HID,
-                       HID, HID, g->W2b);
-    hipLaunchKernelGGL(k_to_bf16, dim3(blocks_for((long long)HID * HID)), dim3(WG), 0, st, g->p + PL.off[P_W3], HID,
-                       HID, HID, g->W3b);
+// The network's arguments for a batch: rows of type t follow those of type
+// t - 1 in X, its outputs in the packed blocks.
+static hfx_status net_args(hfx_guess* g, const float* dX, const int* counts, NetArgs& a, long long& ny) {
     for (int t = 0; t < NTYPE; ++t)
-        hipLaunchKernelGGL(k_to_bf16, dim3(blocks_for((long long)HEAD_OUT[t] * HID)), dim3(WG), 0, st,
-                           g->p + PL.off[P_H0 + 2 * t], HEAD_OUT[t], HID, HID, g->Hb[t]);
-    g->wdirty = false;
-    return hipGetLastError();
-}
-
-// rows of type t start at row0[t]; head outputs of type t start at yoff[t]
-static void layout(const int* counts, long long* row0, long long* yoff, long long& M, long long& ny) {
-    M = 0;
+        if (counts[t] < 0) return gfail(g, HFX_ERR_INVALID_ARG, "guess: negative row count");
+    a = NetArgs{};
+    a.w = NetParams{g->p,
+                    PL.off[P_W1], PL.off[P_B1], PL.off[P_W2], PL.off[P_B2], PL.off[P_W3], PL.off[P_B3],
+                    {PL.off[P_H0], PL.off[P_H1], PL.off[P_H2]},
+                    {PL.off[P_C0], PL.off[P_C1], PL.off[P_C2]},
+                    PL.off[P_FMEAN], PL.off[P_FSCALE]};
+    a.pk = g->pk;
+    a.X = dX;
+    long long M = 0;
     ny = 0;
     for (int t = 0; t < NTYPE; ++t) {
-        row0[t] = M;
-        yoff[t] = ny;
+        a.count[t] = counts[t];
+        a.row0[t] = M;
+        a.yoff[t] = ny;
+        a.blk0[t + 1] = a.blk0[t] + (counts[t] + RB - 1) / RB;
+        a.tscale[t] = g->hp[PL.off[P_TSCALE] + t];
+        a.inv_tscale[t] = 1.0f / a.tscale[t];
         M += counts[t];
         ny += (long long)counts[t] * HEAD_OUT[t];
     }
+    return HFX_OK;
 }
 
-static hfx_status forward(hfx_guess* g, const float* dX, const int* counts, hipStream_t st, long long* row0,
-                          long long* yoff, long long& M, long long& ny) {
-    for (int t = 0; t < NTYPE; ++t)
-        if (counts[t] < 0) return gfail(g, HFX_ERR_INVALID_ARG, "guess: negative row count");
-    layout(counts, row0, yoff, M, ny);
-    hfx_status s = ensure_cap(g, M, ny);
-    if (s != HFX_OK) return s;
-    NCK(pack_weights(g, st));
-    if (M == 0) return HFX_OK;
-    hipLaunchKernelGGL(k_feat_bf16, dim3(blocks_for(M * XLD)), dim3(WG), 0, st, dX, M, g->p + PL.off[P_FMEAN],
-                       g->p + PL.off[P_FSCALE], g->Xb);
-    NCK(hipGetLastError());
-    const float* p = g->p;
-    NCK(gemm(st, (int)M, HID, NFEAT, g->Xb, XLD, 1, g->W1b, 1, XLD, p + PL.off[P_B1], g->Z1, HID, g->H1b, HID, nullptr,
-             0, EPI_SILU));
-    NCK(gemm(st, (int)M, HID, HID, g->H1b, HID, 1, g->W2b, 1, HID, p + PL.off[P_B2], g->Z2, HID, g->H2b, HID, nullptr,
-             0, EPI_SILU));
-    NCK(gemm(st, (int)M, HID, HID, g->H2b, HID, 1, g->W3b, 1, HID, p + PL.off[P_B3], g->Z3, HID, g->H3b, HID, nullptr,
-             0, EPI_SILU));
-    for (int t = 0; t < NTYPE; ++t)
-        NCK(gemm(st, counts[t], HEAD_OUT[t], HID, g->H3b + row0[t] * HID, HID, 1, g->Hb[t], 1, HID,
-                 p + PL.off[P_C0 + 2 * t], g->Y + yoff[t], HEAD_OUT[t], nullptr, 0, nullptr, 0, EPI_STORE));
-    return HFX_OK;
+static hipError_t pack_weights(hfx_guess* g, const NetParams& w, hipStream_t st) {
+    if (!g->wdirty) return hipSuccess;
+    hipLaunchKernelGGL(k_pack, dim3(blocks_for(PWTOT)), dim3(WG), 0, st, w, g->pk);
+    g->wdirty = false;
+    return hipGetLastError();
 }
 
 extern "C" hfx_status hfx_guess_forward_dev(hfx_guess* g, const float* dX, const int* counts, float* dT,
@@ -895,15 +1199,14 @@ extern "C" hfx_status hfx_guess_forward_dev(hfx_guess* g, const float* dX, const
     if (!g || !counts || !dT || !dX) return HFX_ERR_INVALID_ARG;
     NCK(hipSetDevice(g->device));
     hipStream_t st = (hipStream_t)stream;
-    long long row0[NTYPE], yoff[NTYPE], M, ny;
-    hfx_status s = forward(g, dX, counts, st, row0, yoff, M, ny);
+    NetArgs a;
+    long long ny;
+    hfx_status s = net_args(g, dX, counts, a, ny);
     if (s != HFX_OK) return s;
-    for (int t = 0; t < NTYPE; ++t) {
-        const long long n = (long long)counts[t] * HEAD_OUT[t];
-        if (n)
-            hipLaunchKernelGGL(k_scale, dim3(blocks_for(n)), dim3(WG), 0, st, g->Y + yoff[t], n,
-                               g->hp[PL.off[P_TSCALE] + t], dT + yoff[t]);
-    }
+    NCK(pack_weights(g, a.w, st));
+    a.out = dT;
+    if (a.blk0[NTYPE] > 0)
+        hipLaunchKernelGGL(k_net<false>, dim3(a.blk0[NTYPE]), dim3(NET_WG), 0, st, a);
     NCK(hipGetLastError());
     return HFX_OK;
 }
@@ -913,48 +1216,50 @@ extern "C" hfx_status hfx_guess_grad_dev(hfx_guess* g, const float* dX, const in
     if (!g || !counts || !dT || !dX) return HFX_ERR_INVALID_ARG;
     NCK(hipSetDevice(g->device));
     hipStream_t st = (hipStream_t)stream;
-    long long row0[NTYPE], yoff[NTYPE], M, ny;
-    hfx_status s = forward(g, dX, counts, st, row0, yoff, M, ny);
+    NetArgs a;
+    long long ny;
+    hfx_status s = net_args(g, dX, counts, a, ny);
     if (s != HFX_OK) return s;
+    const int nblk = a.blk0[NTYPE];
+    // Chunks in eights: the workgroups of a chunk, eight apart in launch order,
+    // then share an XCD, whose L2 holds the chunk's fragments (30 KB a row
+    // block).  At most 32: the partial sums stay below 25 MB for any batch.
+    const int want = nblk <= 16 ? 1 : 8 * std::min(4, (nblk + 255) / 256);
+    const int chunk = std::max(1, (nblk + want - 1) / want), nchunk = nblk <= 16 ? 1 : want;
+    s = ensure_cap(g, nblk, nchunk);
+    if (s != HFX_OK) return s;
+    NCK(pack_weights(g, a.w, st));
     if (ny == 0) return gfail(g, HFX_ERR_INVALID_ARG, "guess: empty batch");
-    hipLaunchKernelGGL(k_fill_f, dim3(blocks_for(PL.total)), dim3(WG), 0, st, g->gr, PL.total, 0.0f);
-    NCK(hipMemsetAsync(g->d_loss, 0, 8, st));
-    const float gs = 2.0f / (float)ny;
-    float* gr = g->gr;
-    for (int t = 0; t < NTYPE; ++t) {
-        const long long n = (long long)counts[t] * HEAD_OUT[t];
-        if (!n) continue;
-        hipLaunchKernelGGL(k_mse, dim3(blocks_for(n)), dim3(WG), 0, st, g->Y + yoff[t], dT + yoff[t], n,
-                           1.0f / g->hp[PL.off[P_TSCALE] + t], gs, g->dY + yoff[t], g->dYb + yoff[t], g->d_loss);
-        const int nt = HEAD_OUT[t];
-        // head weights: dH_t = dY_t^T H3_t; bias: column sums of dY_t
-        NCK(gemm(st, nt, HID, counts[t], g->dYb + yoff[t], 1, nt, g->H3b + row0[t] * HID, HID, 1, nullptr,
-                 gr + PL.off[P_H0 + 2 * t], HID, nullptr, 0, nullptr, 0, EPI_STORE));
-        hipLaunchKernelGGL(k_colsum, dim3((nt + 63) / 64, (unsigned)((counts[t] + 1023) / 1024)), dim3(256), 0, st,
-                           g->dY + yoff[t], (long long)counts[t], nt, (long long)nt, gr + PL.off[P_C0 + 2 * t]);
-        // dZ3 (rows of type t) = (dY_t H_t) * silu'(Z3)
-        NCK(gemm(st, counts[t], HID, nt, g->dYb + yoff[t], nt, 1, g->Hb[t], HID, 1, nullptr, g->Ga + row0[t] * HID,
-                 HID, g->Gab + row0[t] * HID, HID, g->Z3 + row0[t] * HID, HID, EPI_DSILU));
+    WGradArgs wg{};
+    GradSumArgs gs{};
+    a.T = dT;
+    a.gs = 2.0f / (float)ny;
+    a.fx = g->fx;
+    a.fy = g->fy;
+    a.csum = g->csum;
+    a.esum = g->esum;
+    wg.fx = g->fx;
+    wg.fy = g->fy;
+    for (int k = 0; k < 3; ++k) {
+        wg.fh[k] = a.fh[k] = g->fh[k];
+        wg.fg[k] = a.fg[k] = g->fg[k];
     }
-    // layer 3: dW3 = dZ3^T H2, db3, dZ2 = (dZ3 W3) * silu'(Z2)
-    NCK(gemm(st, HID, HID, (int)M, g->Gab, 1, HID, g->H2b, HID, 1, nullptr, gr + PL.off[P_W3], HID, nullptr, 0,
-             nullptr, 0, EPI_STORE));
-    hipLaunchKernelGGL(k_colsum, dim3(HID / 64, (unsigned)((M + 1023) / 1024)), dim3(256), 0, st, g->Ga, M, HID,
-                       (long long)HID, gr + PL.off[P_B3]);
-    NCK(gemm(st, (int)M, HID, HID, g->Gab, HID, 1, g->W3b, HID, 1, nullptr, g->Gb, HID, g->Gbb, HID, g->Z2, HID,
-             EPI_DSILU));
-    // layer 2
-    NCK(gemm(st, HID, HID, (int)M, g->Gbb, 1, HID, g->H1b, HID, 1, nullptr, gr + PL.off[P_W2], HID, nullptr, 0,
-             nullptr, 0, EPI_STORE));
-    hipLaunchKernelGGL(k_colsum, dim3(HID / 64, (unsigned)((M + 1023) / 1024)), dim3(256), 0, st, g->Gb, M, HID,
-                       (long long)HID, gr + PL.off[P_B2]);
-    NCK(gemm(st, (int)M, HID, HID, g->Gbb, HID, 1, g->W2b, HID, 1, nullptr, g->Ga, HID, g->Gab, HID, g->Z1, HID,
-             EPI_DSILU));
-    // layer 1: dW1 = dZ1^T Xstd (164 input columns), db1
-    NCK(gemm(st, HID, NFEAT, (int)M, g->Gab, 1, HID, g->Xb, XLD, 1, nullptr, gr + PL.off[P_W1], NFEAT, nullptr, 0,
-             nullptr, 0, EPI_STORE));
-    hipLaunchKernelGGL(k_colsum, dim3(HID / 64, (unsigned)((M + 1023) / 1024)), dim3(256), 0, st, g->Ga, M, HID,
-                       (long long)HID, gr + PL.off[P_B1]);
+    const int mats[6] = {P_W3, P_W2, P_W1, P_H0, P_H1, P_H2};
+    for (int k = 0; k < 6; ++k) wg.off[k] = PL.off[mats[k]];
+    for (int t = 0; t <= NTYPE; ++t) wg.blk0[t] = gs.blk0[t] = a.blk0[t];
+    for (int k = 0; k <= NTRAIN; ++k) gs.off[k] = PL.off[k];
+    wg.chunk = gs.chunk = chunk;
+    wg.stride = gs.stride = PL.off[NTRAIN];
+    wg.part = g->part;
+    gs.part = g->part;
+    gs.nwb = (int)blocks_for(PL.off[NTRAIN]);
+    gs.csum = g->csum;
+    gs.esum = g->esum;
+    gs.gr = g->gr;
+    gs.loss = g->d_loss;
+    hipLaunchKernelGGL(k_net<true>, dim3(nblk), dim3(NET_WG), 0, st, a);
+    hipLaunchKernelGGL(k_wgrad, dim3(nchunk, GTILES), dim3(256), 0, st, wg);
+    hipLaunchKernelGGL(k_grad_sum, dim3(gs.nwb + (NCB + 15) / 16 + 1), dim3(WG), 0, st, gs);
     NCK(hipGetLastError());
     if (loss) {
         double l = 0.0;

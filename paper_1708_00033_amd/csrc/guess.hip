@@ -702,7 +702,6 @@ __global__ __launch_bounds__(256) void k_wgrad(const WGradArgs a) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int ni = min(4, (rows + 15) / 16 - it * 4);   // fragments of the tile that hold rows of the matrix
-#pragma unroll 2
     for (int k = lo + wv; k < hi; k += 4) {
         const uint4* pa = reinterpret_cast<const uint4*>(A + ((size_t)k * afb + it * 4) * FRAG) + lane;
         const uint4* pb = reinterpret_cast<const uint4*>(B + ((size_t)k * bfb + jt * 4) * FRAG) + lane;

@@ -1030,7 +1030,7 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
         if (s != HFX_OK) return s;
     }
 
-    // ---- one-electron integrals, one launch per molecule (its own nuclei) ----
+    // ---- one-electron integrals ----
     std::vector<double> atoms(4 * (size_t)natom);
     for (long long a = 0; a < natom; ++a) {
         atoms[4 * a] = xyz[3 * a];
@@ -1038,42 +1038,52 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
         atoms[4 * a + 2] = xyz[3 * a + 2];
         atoms[4 * a + 3] = Z[a];
     }
+    std::vector<OneElMol> one(nmol);
+    std::vector<int> order;
+    order.reserve(nshell);
+    for (int m = 0; m < nmol; ++m) {
+        const MolInfo& M = c->mol[m];
+        OneElMol& o = one[m];
+        o.natom = M.natom;
+        o.aoff = M.aoff;
+        o.nbf = M.nbf;
+        o.boff = M.boff;
+        o.moff = M.moff;
+        for (int l = 0; l < 3; ++l) {
+            o.first[l] = (int)order.size();
+            for (int s = M.soff; s < M.soff + M.nshell; ++s)
+                if (c->shells[s].l == l) order.push_back(s);
+            o.n[l] = (int)order.size() - o.first[l];
+        }
+    }
     const size_t ne = c->nelem;
     ShellHost* dsh = nullptr;
-    double *dexp = nullptr, *dcoef = nullptr, *datoms = nullptr, *dT = nullptr, *dV = nullptr;
+    OneElMol* dmols = nullptr;
+    int* dorder = nullptr;
+    double *dexp = nullptr, *dcoef = nullptr, *datoms = nullptr;
     HIPCK(dalloc(&dsh, nshell));
+    HIPCK(dalloc(&dmols, nmol));
+    HIPCK(dalloc(&dorder, order.size()));
     HIPCK(dalloc(&dexp, c->exps.size()));
     HIPCK(dalloc(&dcoef, c->coefs.size()));
     HIPCK(dalloc(&datoms, atoms.size()));
     HIPCK(dalloc(&c->d_S, ne));
-    HIPCK(dalloc(&dT, ne));
-    HIPCK(dalloc(&dV, ne));
+    HIPCK(dalloc(&c->d_H, ne));
     HIPCK(hipMemcpy(dsh, c->shells.data(), nshell * sizeof(ShellHost), hipMemcpyHostToDevice));
+    HIPCK(hipMemcpy(dmols, one.data(), nmol * sizeof(OneElMol), hipMemcpyHostToDevice));
+    HIPCK(hipMemcpy(dorder, order.data(), order.size() * sizeof(int), hipMemcpyHostToDevice));
     HIPCK(hipMemcpy(dexp, c->exps.data(), c->exps.size() * 8, hipMemcpyHostToDevice));
     HIPCK(hipMemcpy(dcoef, c->coefs.data(), c->coefs.size() * 8, hipMemcpyHostToDevice));
     HIPCK(hipMemcpy(datoms, atoms.data(), atoms.size() * 8, hipMemcpyHostToDevice));
-    for (int m = 0; m < nmol; ++m) {
-        const MolInfo& M = c->mol[m];
-        HIPCK(hfx_one_electron(dsh + M.soff, M.nshell, dexp, dcoef, datoms + 4 * (size_t)M.aoff, M.natom,
-                               c->d_cscale + M.boff, c->d_boys64, M.nbf, c->d_S + M.moff, dT + M.moff, dV + M.moff,
-                               0));
-    }
-    HIPCK(dalloc(&c->d_H, ne));
-    HIPCK(hipMemcpy(c->d_H, dT, ne * 8, hipMemcpyDeviceToDevice));
-    {
-        const double one = 1.0;
-        rocblas_set_pointer_mode(c->blas, rocblas_pointer_mode_host);
-        rocblas_set_stream(c->blas, 0);
-        if (rocblas_daxpy(c->blas, (rocblas_int)ne, &one, dV, 1, c->d_H, 1) != rocblas_status_success)
-            return hfx_fail(c, HFX_ERR_DEVICE, "rocblas_daxpy failed");
-    }
+    HIPCK(hfx_one_electron(nmol, one.data(), dmols, dorder, dsh, dexp, dcoef, datoms, c->d_cscale, c->d_boys64, c->d_S,
+                           c->d_H, 0));
     HIPCK(hipDeviceSynchronize());
     dfree(dsh);
+    dfree(dmols);
+    dfree(dorder);
     dfree(dexp);
     dfree(dcoef);
     dfree(datoms);
-    dfree(dT);
-    dfree(dV);
     HIPCK(dalloc(&c->d_W, ne));
     HIPCK(dalloc(&c->d_Dp, ne));
     c->loaded = true;

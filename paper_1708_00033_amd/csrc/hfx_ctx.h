@@ -78,6 +78,14 @@ struct MolInfo {
     double enuc = 0.0;
 };
 
+// A molecule of a batch for the one-electron kernels: its shells of angular
+// momentum l are n[l] entries from first[l] of the order.
+struct OneElMol {
+    int n[3], first[3];
+    int natom, aoff, nbf, boff;
+    long long moff;
+};
+
 struct GuessPairsDev;   // learned-guess pair data (guess.hip)
 
 struct hfx_ctx {
@@ -208,9 +216,9 @@ hipError_t hfx_scatter_ket(const PairInfo* kets, int n, int nc, int nd, const do
                            double* W, hipStream_t st);
 hipError_t hfx_assemble(const double* H, const double* W, const double* cs, int nmol, const long long* moff,
                         const int* mdim, const int* mboff, int max_ld, double* F, int* bad, hipStream_t st);
-hipError_t hfx_one_electron(const void* sh, int nshell, const double* exps, const double* coefs, const double* atoms,
-                            int natom, const double* cs, const double* boys, int n, double* S, double* T, double* V,
-                            hipStream_t st);
+hipError_t hfx_one_electron(int nmol, const OneElMol* hmols, const OneElMol* mols, const int* order,
+                            const ShellHost* sh, const double* exps, const double* coefs, const double* atoms,
+                            const double* cscale, const double* boys, double* S, double* H, hipStream_t st);
 hipError_t hfx_antisym(const double* A, int n, double* out, hipStream_t st);
 int hfx_dot_partial(const double* a, const double* b, size_t n, int mode, double* out, hipStream_t st);
 int hfx_energy_partial(const double* D, const double* H, const double* F, size_t n, double* out, hipStream_t st);

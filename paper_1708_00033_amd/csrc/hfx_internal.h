@@ -124,6 +124,25 @@ __device__ __forceinline__ double lane_pair_sum(double even, double odd) {
     return __longlong_as_double((long long)(((unsigned long long)r[2] << 32) | r[0])) +
            __longlong_as_double((long long)(((unsigned long long)r[3] << 32) | r[1]));
 }
+// Sum over the wave, in every lane: lane exchanges within rows of 16 by DPP,
+// across rows and halves by permlane swaps (no LDS round trips).
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)u, hi = (unsigned)(u >> 32);
+    const unsigned a = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+    const unsigned b = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+    return v + __longlong_as_double((long long)(((unsigned long long)b << 32) | a));
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    v = dpp_add<0xb1>(v);    // quad_perm 1 0 3 2
+    v = dpp_add<0x4e>(v);    // quad_perm 2 3 0 1
+    v = dpp_add<0x141>(v);   // row_half_mirror
+    v = dpp_add<0x140>(v);   // row_mirror
+    v = lane_pair_sum<4>(v, v);
+    return lane_pair_sum<5>(v, v);
+}
+
 // Constant address space: loads through such a pointer at a wave-uniform
 // address become scalar (SMEM) loads.
 #define HFX_CONST_AS __attribute__((address_space(4)))

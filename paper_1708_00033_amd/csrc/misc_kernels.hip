@@ -1,6 +1,5 @@
 // Support kernels around the class kernels: density preparation, the
-// per-bra FP64/FP32 split, Fock assembly, one-electron integrals and the
-// small SCF helpers.  All are HBM-bound elementwise passes or tiny.
+// per-bra FP64/FP32 split, Fock assembly and the small SCF helpers.  All are HBM-bound elementwise passes or tiny.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -127,164 +126,6 @@ __global__ void k_scatter_ket(const PairInfo* __restrict__ kets, int n, int nc, 
     const PairInfo p = kets[s];
     const size_t idx = (size_t)moff[p.mol] + (size_t)(p.bfa + comp / nd) * p.ld + p.bfb + comp % nd;
     W[idx] += v;
-}
-
-// ---- one-electron integrals (Obara-Saika) ------------------------------------
-// One thread per shell pair (a >= b).  Overlap from the 1-D recursion
-//   S_{i+1,j} = X_PA S_ij + (i S_{i-1,j} + j S_{i,j-1})/(2p), same for j with X_PB;
-// kinetic from -1/2 d^2/dx^2 acting on the ket Gaussian:
-//   T_ij = -1/2 [ j(j-1) S_{i,j-2} - 2 beta (2j+1) S_ij + 4 beta^2 S_{i,j+2} ];
-// nuclear attraction from the vertical recursion on centre A,
-//   [a+1_i]^(m) = PA_i [a]^(m) - PC_i [a]^(m+1) + a_i/(2p) ([a-1_i]^(m) - [a-1_i]^(m+1)),
-//   [0]^(m) = 2 pi / p exp(-alpha beta/p |AB|^2) F_m(p |PC|^2),
-// then the transfer (a|b+1_i) = (a+1_i|b) + AB_i (a|b).
-struct ShellDev {
-    double x, y, z;
-    int l, nprim, prim_off, bf;
-};
-
-__device__ __forceinline__ int cart_index(int x, int y, int z) {   // lexicographic index within |l|
-    const int l = x + y + z;
-    (void)l;
-    const int yz = y + z;
-    return yz * (yz + 1) / 2 + z;
-}
-
-__device__ __forceinline__ void cart_comp_dev(int l, int c, int* e) {
-    int k = 0;
-    for (int x = l; x >= 0; --x)
-        for (int y = l - x; y >= 0; --y) {
-            if (k == c) { e[0] = x; e[1] = y; e[2] = l - x - y; return; }
-            ++k;
-        }
-}
-
-__global__ void k_one_electron(const ShellDev* __restrict__ sh, int nshell, const double* __restrict__ exps,
-                               const double* __restrict__ coefs, const double* __restrict__ atoms /*x,y,z,Z*/,
-                               int natom, const double* __restrict__ cs, const double* __restrict__ boys, int n,
-                               double* __restrict__ S, double* __restrict__ T, double* __restrict__ V) {
-    const long long pid = (long long)blockIdx.x * MISC_WG + threadIdx.x;
-    const long long npair = (long long)nshell * (nshell + 1) / 2;
-    if (pid >= npair) return;
-    int a = (int)((sqrt(8.0 * (double)pid + 1.0) - 1.0) * 0.5);
-    while ((long long)a * (a + 1) / 2 > pid) --a;
-    while ((long long)(a + 1) * (a + 2) / 2 <= pid) ++a;
-    const int b = (int)(pid - (long long)a * (a + 1) / 2);
-    const ShellDev A = sh[a], B = sh[b];
-    const int la = A.l, lb = B.l, na = (la + 1) * (la + 2) / 2, nb = (lb + 1) * (lb + 2) / 2;
-    const double Ap[3] = {A.x, A.y, A.z}, Bp[3] = {B.x, B.y, B.z};
-    const double AB[3] = {A.x - B.x, A.y - B.y, A.z - B.z};
-    const double ab2 = AB[0] * AB[0] + AB[1] * AB[1] + AB[2] * AB[2];
-    double s_acc[36], t_acc[36], v_acc[36];
-    for (int i = 0; i < 36; ++i) s_acc[i] = t_acc[i] = v_acc[i] = 0.0;
-    for (int ia = 0; ia < A.nprim; ++ia)
-        for (int ib = 0; ib < B.nprim; ++ib) {
-            const double al = exps[A.prim_off + ia], be = exps[B.prim_off + ib];
-            const double cc = coefs[A.prim_off + ia] * coefs[B.prim_off + ib];
-            const double p = al + be, i2p = 0.5 / p, mu = al * be / p;
-            const double P[3] = {(al * A.x + be * B.x) / p, (al * A.y + be * B.y) / p, (al * A.z + be * B.z) / p};
-            const double kab = exp(-mu * ab2);
-            // 1-D overlaps S[x][i][j], i <= 2, j <= 4
-            double S1[3][3][5];
-            for (int x = 0; x < 3; ++x) {
-                const double PA = P[x] - Ap[x], PB = P[x] - Bp[x];
-                for (int i = 0; i < 3; ++i)
-                    for (int j = 0; j < 5; ++j) S1[x][i][j] = 0.0;
-                S1[x][0][0] = sqrt(M_PI / p);
-                for (int i = 0; i <= la; ++i) {
-                    if (i > 0)
-                        S1[x][i][0] = PA * S1[x][i - 1][0] + (i - 1 > 0 ? (i - 1) * i2p * S1[x][i - 2][0] : 0.0);
-                    for (int j = 1; j <= lb + 2; ++j)
-                        S1[x][i][j] = PB * S1[x][i][j - 1] + i2p * ((i > 0 ? i * S1[x][i - 1][j - 1] : 0.0) +
-                                                                     (j - 1 > 0 ? (j - 1) * S1[x][i][j - 2] : 0.0));
-                }
-            }
-            // nuclear attraction: [e]^(m), |e| <= la+lb <= 4, m <= 4
-            const int L = la + lb;
-            const int off[6] = {0, 1, 4, 10, 20, 35};
-            double Vacc[35];   // sum over nuclei of -Z [e]^(0), indexed by total order blocks
-            for (int i = 0; i < 35; ++i) Vacc[i] = 0.0;
-            for (int c = 0; c < natom; ++c) {
-                const double Z = atoms[4 * c + 3];
-                if (Z == 0.0) continue;
-                const double PC[3] = {P[0] - atoms[4 * c], P[1] - atoms[4 * c + 1], P[2] - atoms[4 * c + 2]};
-                const double Tc = p * (PC[0] * PC[0] + PC[1] * PC[1] + PC[2] * PC[2]);
-                double F[5];
-                boys_eval<double, 4>(Tc, F, boys + boys_block(4));
-                // e laid out as [lvl][comp] with offsets 0,1,4,10,20 ; m in [0..L-lvl]
-                double th[35][5];
-                const double pre = 2.0 * M_PI / p * kab;
-                for (int m = 0; m <= L; ++m) th[0][m] = pre * F[m];
-                for (int lvl = 1; lvl <= L; ++lvl) {
-                    const int nc = (lvl + 1) * (lvl + 2) / 2;
-                    for (int k = 0; k < nc; ++k) {
-                        int e[3];
-                        cart_comp_dev(lvl, k, e);
-                        int dir = e[0] > 0 ? 0 : (e[1] > 0 ? 1 : 2);
-                        int e1[3] = {e[0], e[1], e[2]};
-                        e1[dir] -= 1;
-                        const int i1 = off[lvl - 1] + cart_index(e1[0], e1[1], e1[2]);
-                        int i2 = -1;
-                        if (e1[dir] > 0) {
-                            int e2[3] = {e1[0], e1[1], e1[2]};
-                            e2[dir] -= 1;
-                            i2 = off[lvl - 2] + cart_index(e2[0], e2[1], e2[2]);
-                        }
-                        const double PAd = P[dir] - Ap[dir];
-                        for (int m = 0; m <= L - lvl; ++m) {
-                            double v = PAd * th[i1][m] - PC[dir] * th[i1][m + 1];
-                            if (i2 >= 0) v += e1[dir] * i2p * (th[i2][m] - th[i2][m + 1]);
-                            th[off[lvl] + k][m] = v;
-                        }
-                    }
-                }
-                for (int i = 0; i < off[L + 1]; ++i) Vacc[i] -= Z * th[i][0];
-            }
-            // assemble the Cartesian blocks
-            for (int mu = 0; mu < na; ++mu)
-                for (int nu = 0; nu < nb; ++nu) {
-                    int ea[3], eb[3];
-                    cart_comp_dev(la, mu, ea);
-                    cart_comp_dev(lb, nu, eb);
-                    double s3 = 1.0, t3 = 0.0;
-                    double sx[3], tx[3];
-                    for (int x = 0; x < 3; ++x) {
-                        const int i = ea[x], j = eb[x];
-                        sx[x] = S1[x][i][j];
-                        tx[x] = -0.5 * ((j >= 2 ? j * (j - 1) * S1[x][i][j - 2] : 0.0) -
-                                        2.0 * be * (2 * j + 1) * S1[x][i][j] + 4.0 * be * be * S1[x][i][j + 2]);
-                    }
-                    s3 = sx[0] * sx[1] * sx[2];
-                    t3 = tx[0] * sx[1] * sx[2] + sx[0] * tx[1] * sx[2] + sx[0] * sx[1] * tx[2];
-                    // transfer: (ea | eb) from [e] with |e| >= la via (a|b+1_i) = (a+1_i|b) + AB_i (a|b)
-                    // expand (x-B)^j = sum_k C(j,k) (x-A)^{j-k} (A-B)^k per axis
-                    double vv = 0.0;
-                    for (int kx = 0; kx <= eb[0]; ++kx)
-                        for (int ky = 0; ky <= eb[1]; ++ky)
-                            for (int kz = 0; kz <= eb[2]; ++kz) {
-                                const int ex = ea[0] + eb[0] - kx, ey = ea[1] + eb[1] - ky, ez = ea[2] + eb[2] - kz;
-                                const int lvl = ex + ey + ez;
-                                const double binx = (kx == 0 || kx == eb[0]) ? 1.0 : (double)eb[0];
-                                const double biny = (ky == 0 || ky == eb[1]) ? 1.0 : (double)eb[1];
-                                const double binz = (kz == 0 || kz == eb[2]) ? 1.0 : (double)eb[2];
-                                const double f = binx * biny * binz * pow(AB[0], kx) * pow(AB[1], ky) * pow(AB[2], kz);
-                                vv += f * Vacc[off[lvl] + cart_index(ex, ey, ez)];
-                            }
-                    const double k3 = kab;   // overlap/kinetic carry exp(-mu AB^2) once (3-D product)
-                    s_acc[mu * nb + nu] += cc * k3 * s3;
-                    t_acc[mu * nb + nu] += cc * k3 * t3;
-                    v_acc[mu * nb + nu] += cc * vv;
-                }
-        }
-    for (int mu = 0; mu < na; ++mu)
-        for (int nu = 0; nu < nb; ++nu) {
-            const int r = A.bf + mu, c = B.bf + nu;
-            const double sc = cs[r] * cs[c];
-            const double sv = sc * s_acc[mu * nb + nu], tv = sc * t_acc[mu * nb + nu], vv = sc * v_acc[mu * nb + nu];
-            S[(size_t)r * n + c] = sv; S[(size_t)c * n + r] = sv;
-            T[(size_t)r * n + c] = tv; T[(size_t)c * n + r] = tv;
-            V[(size_t)r * n + c] = vv; V[(size_t)c * n + r] = vv;
-        }
 }
 
 // ---- SCF helpers ------------------------------------------------------------------
@@ -456,15 +297,6 @@ hipError_t hfx_scatter_ket(const PairInfo* kets, int n, int nc, int nd, const do
 hipError_t hfx_assemble(const double* H, const double* W, const double* cs, int nmol, const long long* moff,
                         const int* mdim, const int* mboff, int max_ld, double* F, int* bad, hipStream_t st) {
     hipLaunchKernelGGL(k_assemble, ragged_grid(max_ld, nmol), dim3(MISC_WG), 0, st, H, W, cs, moff, mdim, mboff, F, bad);
-    return hipGetLastError();
-}
-hipError_t hfx_one_electron(const void* sh, int nshell, const double* exps, const double* coefs, const double* atoms,
-                            int natom, const double* cs, const double* boys, int n, double* S, double* T, double* V,
-                            hipStream_t st) {
-    const long long npair = (long long)nshell * (nshell + 1) / 2;
-    if (npair == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_one_electron, dim3((unsigned)((npair + MISC_WG - 1) / MISC_WG)), dim3(MISC_WG), 0, st,
-                       (const ShellDev*)sh, nshell, exps, coefs, atoms, natom, cs, boys, n, S, T, V);
     return hipGetLastError();
 }
 hipError_t hfx_antisym(const double* A, int n, double* out, hipStream_t st) {

@@ -142,14 +142,15 @@ static void release_system(hfx_ctx* c) {
         dfree(L.d_q);
         dfree(L.d_soa);
         dfree(L.d_soa32);
-        dfree(L.d_wket);
         dfree(L.d_kbf);
         dfree(L.d_kpos);
-        dfree(L.d_dket);
-        dfree(L.d_dket_multi);
-        dfree(L.d_wket_multi);
-        L.dket_multi_cap = 0;
     }
+    dfree(c->d_kelem);
+    dfree(c->d_dket);
+    dfree(c->d_wket);
+    dfree(c->d_dket_multi);
+    dfree(c->d_wket_multi);
+    c->nket = 0;
     c->ketlists.clear();
     c->host_bra.clear();
     c->host_pos.clear();
@@ -175,7 +176,7 @@ static void release_system(hfx_ctx* c) {
     dfree(c->d_W);
     dfree(c->d_Wrep);
     dfree(c->d_multi);
-    c->multi_cap = 0;
+    c->multi_cap = c->multi_ket_cap = 0;
     dfree(c->d_multi_work);
     c->multi_work_cap = 0;
     dfree(c->d_Dp);
@@ -995,8 +996,8 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
             HIPCK(dalloc(&KL.d_q, n));
             HIPCK(dalloc(&KL.d_soa, soa.size()));
             KL.ncd = ncart(kPairL[K][0]) * ncart(kPairL[K][1]);
-            HIPCK(dalloc(&KL.d_wket, (size_t)KL.ncd * n));
-            HIPCK(dalloc(&KL.d_dket, (size_t)KL.ncd * n));
+            KL.koff = c->nket;
+            c->nket += ((size_t)KL.ncd * n + 31) / 32 * 32;   // lists begin on 256 bytes
             HIPCK(dalloc(&KL.d_kbf, n));
             HIPCK(hipMemcpy(KL.d_kbf, kbf.data(), n * sizeof(int4), hipMemcpyHostToDevice));
             {
@@ -1021,6 +1022,13 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
             c->kwcode.push_back(std::move(wcode));
         }
     }
+    HIPCK(dalloc(&c->d_kelem, c->nket));
+    HIPCK(dalloc(&c->d_dket, c->nket));
+    HIPCK(dalloc(&c->d_wket, c->nket));
+    HIPCK(hipMemset(c->d_kelem, 0xff, c->nket * sizeof(KetElem)));   // padding: idx < 0
+    for (const auto& KL : c->ketlists)
+        HIPCK(hfx_ket_elems(KL.d_pairs, KL.n, ncart(kPairL[KL.K][0]), ncart(kPairL[KL.K][1]), c->d_moff, c->d_mboff,
+                            c->d_cscale, c->d_kelem + KL.koff, 0));
     c->host_bra.assign(all.begin(), all.end());
     c->host_pos = pos;
     c->host_ket = std::move(klist);
@@ -1298,22 +1306,24 @@ hfx_status hfx_build_with(hfx_ctx* c, const BuildBufs& bufs, const double* dD, d
     const bool mixed = c->opt.precision == HFX_PREC_MIXED;
     auto t0 = std::chrono::steady_clock::now();
     if (c->timing) collect_timing(c);
-    HIPCK(hfx_fill_u64(bufs.dmax, 1, st));
-    HIPCK(hfx_fill_u64(bufs.counters, HFX_CNT_WORDS + 1, st));   // quartet counters + the non-finite flag
-    HIPCK(hfx_prepare_density(dD, c->d_cscale, c->nmol, c->d_moff, c->d_mdim, c->d_mboff, c->max_ld, bufs.Dp,
-                              bufs.dmax, st));
-    HIPCK(hfx_fill(bufs.W, nn, 0.0, st));
-    for (auto& KL : c->ketlists) {
-        HIPCK(hfx_fill(KL.d_wket, (size_t)KL.ncd * KL.n, 0.0, st));
-        HIPCK(hfx_gather_ket(KL.d_pairs, KL.n, ncart(kPairL[KL.K][0]), ncart(kPairL[KL.K][1]), bufs.Dp, c->d_moff,
-                             KL.d_dket, st));
-    }
     bool any_persist = false, any_priv = false;
     for (const auto& P : c->plans) {
         any_persist |= P.persist;
         any_priv |= P.priv;
     }
-    if (any_persist) HIPCK(hfx_fill_u64(bufs.work, 16 * (int)c->plans.size(), st));
+    if (mixed) HIPCK(hfx_fill_u64(bufs.dmax, 1, st));
+    // quartet counters + the non-finite flag; queues of persistent launches
+    const StartBufs start{bufs.Dp,
+                          bufs.W,
+                          c->d_dket,
+                          c->d_wket,
+                          mixed ? bufs.dmax : nullptr,
+                          bufs.counters,
+                          HFX_CNT_WORDS + 1,
+                          bufs.work,
+                          any_persist ? 16 * (int)c->plans.size() : 0};
+    HIPCK(hfx_start_build(dD, c->d_cscale, c->nmol, c->d_moff, c->d_mdim, c->d_mboff, c->max_ld, c->d_kelem, c->nket,
+                          &start, st));
     if (any_priv) {
         if (!c->d_Wrep) return hfx_fail(c, HFX_ERR_STATE, "build: private digestion without its copies of W");
         HIPCK(hfx_fill(c->d_Wrep, kXcds * nn, 0.0, st));
@@ -1333,7 +1343,7 @@ hfx_status hfx_build_with(hfx_ctx* c, const BuildBufs& bufs, const double* dD, d
         a.bra = c->d_pairs[P.B];
         a.ket = KL.d_pairs;
         a.kbf = KL.d_kbf;
-        a.dket = KL.d_dket;
+        a.dket = c->d_dket + KL.koff;
         a.prim = c->d_prim;
         a.kprim = KL.d_soa;
         a.prim32 = c->d_prim32;
@@ -1351,7 +1361,7 @@ hfx_status hfx_build_with(hfx_ctx* c, const BuildBufs& bufs, const double* dD, d
         a.D = bufs.Dp;
         a.W = P.priv ? c->d_Wrep : bufs.W;
         a.wrep = P.priv ? (long long)nn : 0;
-        a.wket = KL.d_wket;
+        a.wket = c->d_wket + KL.koff;
         a.counters = bufs.counters + (size_t)cid * HFX_CNT_CLASS;
         a.cj = cj;
         a.ck = ck;
@@ -1392,9 +1402,7 @@ hfx_status hfx_build_with(hfx_ctx* c, const BuildBufs& bufs, const double* dD, d
     }
     HIPCK(join_streams(c, ns, st));
     if (any_priv) HIPCK(hfx_reduce_replicas(c->d_Wrep, kXcds, nn, bufs.W, st));
-    for (auto& KL : c->ketlists)
-        HIPCK(hfx_scatter_ket(KL.d_pairs, KL.n, ncart(kPairL[KL.K][0]), ncart(kPairL[KL.K][1]), KL.d_wket, c->d_moff, bufs.W,
-                              st));
+    HIPCK(hfx_scatter_kets(c->d_kelem, c->nket, c->d_wket, bufs.W, st));
     HIPCK(hfx_assemble(dH, bufs.W, c->d_cscale, c->nmol, c->d_moff, c->d_mdim, c->d_mboff, c->max_ld, dOut, bufs.bad,
                        st));
     c->last_stream = st;
@@ -1468,15 +1476,14 @@ extern "C" hfx_status hfx_build_jk_multi_dev(hfx_ctx* c, int ndens, const double
         HIPCK(dalloc(&c->d_multi, 3 * (size_t)ndens * nn));
         c->multi_cap = ndens;
     }
-    for (auto& KL : c->ketlists)
-        if (KL.dket_multi_cap < ndens) {
-            dfree(KL.d_dket_multi);
-            dfree(KL.d_wket_multi);
-            KL.dket_multi_cap = 0;
-            HIPCK(dalloc(&KL.d_dket_multi, (size_t)ndens * KL.ncd * KL.n));
-            HIPCK(dalloc(&KL.d_wket_multi, (size_t)ndens * KL.ncd * KL.n));
-            KL.dket_multi_cap = ndens;
-        }
+    if (c->multi_ket_cap < ndens) {
+        dfree(c->d_dket_multi);
+        dfree(c->d_wket_multi);
+        c->multi_ket_cap = 0;
+        HIPCK(dalloc(&c->d_dket_multi, (size_t)ndens * c->nket));
+        HIPCK(dalloc(&c->d_wket_multi, (size_t)ndens * c->nket));
+        c->multi_ket_cap = ndens;
+    }
     // densities per launch of a plan: as many LDS row sets as fit beside the
     // Boys rows (MODE 0), else all of them with global atomics (MODE 1)
     std::vector<int> group(c->plans.size()), gmode(c->plans.size());
@@ -1509,19 +1516,20 @@ extern "C" hfx_status hfx_build_jk_multi_dev(hfx_ctx* c, int ndens, const double
     double* Dp = c->d_multi;
     double* WJ = Dp + (size_t)ndens * nn;
     double* WK = WJ + (size_t)ndens * nn;
-    HIPCK(hfx_fill_u64(c->d_dmax, 1, st));
-    HIPCK(hfx_fill_u64(c->d_counters, HFX_CNT_WORDS + 1, st));
-    for (int d = 0; d < ndens; ++d)
-        HIPCK(hfx_prepare_density(dD + (size_t)d * nn, c->d_cscale, c->nmol, c->d_moff, c->d_mdim, c->d_mboff,
-                                  c->max_ld, Dp + (size_t)d * nn, c->d_dmax, st));
-    HIPCK(hfx_fill(WJ, 2 * (size_t)ndens * nn, 0.0, st));
-    for (auto& KL : c->ketlists) {
-        HIPCK(hfx_fill(KL.d_wket_multi, (size_t)ndens * KL.ncd * KL.n, 0.0, st));
-        for (int d = 0; d < ndens; ++d)
-            HIPCK(hfx_gather_ket(KL.d_pairs, KL.n, ncart(kPairL[KL.K][0]), ncart(kPairL[KL.K][1]),
-                                 Dp + (size_t)d * nn, c->d_moff, KL.d_dket_multi + (size_t)d * KL.ncd * KL.n, st));
+    for (int d = 0; d < ndens; ++d) {   // the first launch also clears the counters and queues
+        const StartBufs start{Dp + (size_t)d * nn,
+                              WJ + (size_t)d * nn,
+                              c->d_dket_multi + (size_t)d * c->nket,
+                              c->d_wket_multi + (size_t)d * c->nket,
+                              nullptr,
+                              c->d_counters,
+                              d == 0 ? HFX_CNT_WORDS + 1 : 0,
+                              c->d_multi_work,
+                              d == 0 ? (int)nwork : 0};
+        HIPCK(hfx_start_build(dD + (size_t)d * nn, c->d_cscale, c->nmol, c->d_moff, c->d_mdim, c->d_mboff, c->max_ld,
+                              c->d_kelem, c->nket, &start, st));
     }
-    HIPCK(hfx_fill_u64(c->d_multi_work, (int)nwork, st));
+    HIPCK(hfx_fill(WK, (size_t)ndens * nn, 0.0, st));
     size_t wofs = 0;
     const int ns = build_streams(c);
     HIPCK(fork_streams(c, ns, st));
@@ -1545,7 +1553,7 @@ extern "C" hfx_status hfx_build_jk_multi_dev(hfx_ctx* c, int ndens, const double
         a.D = Dp;
         a.W = WJ;
         a.WK = WK;
-        a.dket = KL.d_dket_multi;
+        a.dket = c->d_dket_multi + KL.koff;
         a.counters = c->d_counters + (size_t)P.cid * HFX_CNT_CLASS;
         a.cj = 1.0;    // J updates into W: (W + W^T)/8 = J
         a.ck = -1.0;   // K updates into WK: (WK + WK^T)/8 = K
@@ -1558,7 +1566,7 @@ extern "C" hfx_status hfx_build_jk_multi_dev(hfx_ctx* c, int ndens, const double
         a.win = c->win;
         a.rs = c->rs;
         a.dstride = (long long)nn;
-        a.kstride = (long long)KL.ncd * KL.n;
+        a.kstride = (long long)c->nket;
         const int nblocks = ((std::min(P.ntask, 2048) + 7) / 8) * 8;   // resident or queued: queues drain either way
         for (int d0 = 0; d0 < ndens; d0 += group[pi]) {
             ClassArgs b = a;
@@ -1566,8 +1574,8 @@ extern "C" hfx_status hfx_build_jk_multi_dev(hfx_ctx* c, int ndens, const double
             b.D = Dp + (size_t)d0 * nn;
             b.W = WJ + (size_t)d0 * nn;
             b.WK = WK + (size_t)d0 * nn;
-            b.dket = KL.d_dket_multi + (size_t)d0 * a.kstride;
-            b.wket = KL.d_wket_multi + (size_t)d0 * a.kstride;
+            b.dket = c->d_dket_multi + KL.koff + (size_t)d0 * a.kstride;
+            b.wket = c->d_wket_multi + KL.koff + (size_t)d0 * a.kstride;
             b.work = c->d_multi_work + wofs;
             wofs += 8;
             const size_t rows = gmode[pi] == 0 ? (size_t)b.ndens * P.lds_bytes : 0;
@@ -1579,10 +1587,8 @@ extern "C" hfx_status hfx_build_jk_multi_dev(hfx_ctx* c, int ndens, const double
         }
     }
     HIPCK(join_streams(c, ns, st));
-    for (auto& KL : c->ketlists)   // each density's ket-block J sums into its J accumulator
-        for (int d = 0; d < ndens; ++d)
-            HIPCK(hfx_scatter_ket(KL.d_pairs, KL.n, ncart(kPairL[KL.K][0]), ncart(kPairL[KL.K][1]),
-                                  KL.d_wket_multi + (size_t)d * KL.ncd * KL.n, c->d_moff, WJ + (size_t)d * nn, st));
+    for (int d = 0; d < ndens; ++d)   // each density's ket-block J sums into its J accumulator
+        HIPCK(hfx_scatter_kets(c->d_kelem, c->nket, c->d_wket_multi + (size_t)d * c->nket, WJ + (size_t)d * nn, st));
     for (int d = 0; d < ndens; ++d) {
         if (dJ)
             HIPCK(hfx_assemble(nullptr, WJ + (size_t)d * nn, c->d_cscale, c->nmol, c->d_moff, c->d_mdim, c->d_mboff,

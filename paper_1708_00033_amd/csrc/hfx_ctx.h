@@ -24,11 +24,7 @@ struct KetList {
     double* d_q = nullptr;
     double* d_soa = nullptr;
     float* d_soa32 = nullptr;   // its FP32 copy (the FP32 evaluation of mixed builds)
-    double* d_wket = nullptr;   // ket-block J accumulator, ncart(l_c) ncart(l_d) x n
-    double* d_dket = nullptr;   // D'_cd of every ket, gathered per build, same layout
-    double* d_dket_multi = nullptr;   // the same for each density of a multi-density build
-    double* d_wket_multi = nullptr;   // and the ket-block J accumulators
-    int dket_multi_cap = 0;           // densities they hold
+    size_t koff = 0;            // its ket-block elements, ncart(l_c) ncart(l_d) x n, in the context's arrays of them
     int4* d_kbf = nullptr;      // per ket: (bfa, bfb, a, b)
     int* d_kpos = nullptr;      // per ket: position in its pair class's Q-sorted list
     int ncd = 1;
@@ -122,6 +118,12 @@ struct hfx_ctx {
     PairInfo* d_pairs[6] = {nullptr};   // significant pairs per pair class, Q descending (bras)
     int npair[6] = {0};
     std::vector<KetList> ketlists;      // per pair class and primitive count (kets)
+    // the ket lists' blocks one after the other (KetList::koff): elements, D'
+    // gathered per build, J accumulators; nket per density of a multi-density build
+    size_t nket = 0;
+    KetElem* d_kelem = nullptr;
+    double *d_dket = nullptr, *d_wket = nullptr;
+    double *d_dket_multi = nullptr, *d_wket_multi = nullptr;
     std::vector<SubPlan> plans;         // launches, grouped by class id
     ClassTotals totals[21];
     // host copies of the Q-sorted lists (for re-planning) and per-class tuning
@@ -146,7 +148,7 @@ struct hfx_ctx {
     double* d_Wrep = nullptr;   // private digestion: 8 per-XCD copies of W (allocated by plans that use it)
     // multi-density builds: D' and the J and K accumulators of each density
     double* d_multi = nullptr;
-    int multi_cap = 0;
+    int multi_cap = 0, multi_ket_cap = 0;   // densities that these and the ket arrays hold
     unsigned long long* d_multi_work = nullptr;   // queue counters: 8 per (plan, density group)
     size_t multi_work_cap = 0;
     double* d_Dp = nullptr;
@@ -203,17 +205,17 @@ hfx_status hfx_build_with(hfx_ctx* c, const BuildBufs& b, const double* dD, doub
 
 // implemented in misc_kernels.hip
 extern "C" {
-hipError_t hfx_prepare_density(const double* D, const double* cs, int nmol, const long long* moff, const int* mdim,
-                               const int* mboff, int max_ld, double* Dp, unsigned long long* dmax_bits, hipStream_t st);
+hipError_t hfx_start_build(const double* D, const double* cs, int nmol, const long long* moff, const int* mdim,
+                           const int* mboff, int max_ld, const KetElem* ke, size_t nke, const StartBufs* b,
+                           hipStream_t st);
 hipError_t hfx_fill(double* p, size_t n, double v, hipStream_t st);
 hipError_t hfx_reduce_replicas(const double* rep, int nrep, size_t n, double* W, hipStream_t st);
 hipError_t hfx_fill_u64(unsigned long long* p, int n, hipStream_t st);
 hipError_t hfx_split(const PairInfo* bra, const double* ketq, const int4* tasks, int ntask, double fp32_tau,
                      const unsigned long long* dmax_bits, int* split, hipStream_t st);
-hipError_t hfx_gather_ket(const PairInfo* kets, int n, int nc, int nd, const double* D, const long long* moff,
-                          double* dket, hipStream_t st);
-hipError_t hfx_scatter_ket(const PairInfo* kets, int n, int nc, int nd, const double* wket, const long long* moff,
-                           double* W, hipStream_t st);
+hipError_t hfx_ket_elems(const PairInfo* kets, int n, int nc, int nd, const long long* moff, const int* mboff,
+                         const double* cs, KetElem* out, hipStream_t st);
+hipError_t hfx_scatter_kets(const KetElem* ke, size_t nke, const double* wket, double* W, hipStream_t st);
 hipError_t hfx_assemble(const double* H, const double* W, const double* cs, int nmol, const long long* moff,
                         const int* mdim, const int* mboff, int max_ld, double* F, int* bad, hipStream_t st);
 hipError_t hfx_one_electron(int nmol, const OneElMol* hmols, const OneElMol* mols, const int* order,

@@ -35,6 +35,23 @@ struct PairInfo {
     int ld;            // its basis size (leading dimension of its blocks)
 };
 
+// An element of a ket list's blocks: its place in the ragged matrices (< 0:
+// padding between lists) and the product of its component factors.
+struct KetElem {
+    long long idx;
+    double s;
+};
+
+// What the start of a build writes (misc_kernels.hip, k_start_build).
+struct StartBufs {
+    double *Dp, *W, *dket, *wket;
+    unsigned long long* dmax_bits;   // null: max |D| not needed (FP64 builds)
+    unsigned long long* counters;
+    int ncounters;
+    unsigned long long* work;
+    int nwork;
+};
+
 // Arguments of one class kernel launch.  The kets of a launch all have the
 // same number of primitive pairs (knprim), so the primitive loop trip count
 // is uniform across a wave.  Ket primitive data are a structure of arrays:

@@ -15,31 +15,58 @@
 // mboff[m] .. mboff[m] + nbf_m - 1 (component factors cs[]).  Elementwise
 // kernels run on a (gx, nmol) grid, row y = molecule.
 
-// D' = s_m s_n D (component normalisation moved onto the density),
-// dmax = max |D| (bit pattern of a non-negative double is order preserving).
-__global__ void k_prepare_density(const double* __restrict__ D, const double* __restrict__ cs,
-                                  const long long* __restrict__ moff, const int* __restrict__ mdim,
-                                  const int* __restrict__ mboff, double* __restrict__ Dp,
-                                  unsigned long long* __restrict__ dmax_bits) {
+// The start of a build in one launch.  A small molecule's build is bound by its
+// launches: fills, density and a fill, a gather and a scatter per ket list, 23
+// beside the class kernels of a water dimer, are now this, one scatter and the
+// assembly: 183 -> 134 us (five waters as a replayed graph 566 -> 455 us).
+// The first gx columns of the grid, row y = molecule: D' = s_m s_n D (component
+// normalisation moved onto the density), W = 0, and, where dmax_bits is given
+// (zeroed before), dmax = max |D| (the bit pattern of a non-negative double is
+// order preserving).  The other columns: per element of the ket lists' blocks
+// D'_cd in list order, from D itself, so that the class kernels read it
+// coalesced by ket position, and the zeroed J accumulator.  Workgroup 0 clears
+// the counters and the queues.
+__global__ void k_start_build(const double* __restrict__ D, const double* __restrict__ cs,
+                              const long long* __restrict__ moff, const int* __restrict__ mdim,
+                              const int* __restrict__ mboff, int gx, const KetElem* __restrict__ ke, size_t nke,
+                              const StartBufs b) {
+    if ((int)blockIdx.x >= gx) {
+        const size_t kx = gridDim.x - gx, step = kx * gridDim.y * MISC_WG;
+        for (size_t i = ((size_t)blockIdx.y * kx + blockIdx.x - gx) * MISC_WG + threadIdx.x; i < nke; i += step) {
+            const KetElem e = ke[i];
+            if (e.idx < 0) continue;   // between two lists
+            b.dket[i] = e.s * D[e.idx];
+            b.wket[i] = 0.0;
+        }
+        return;
+    }
     const int mol = blockIdx.y;
     const int n = mdim[mol];
     const size_t nn = (size_t)n * n, base = (size_t)moff[mol];
     const double* __restrict__ c = cs + mboff[mol];
     double mx = 0.0;
-    for (size_t i = (size_t)blockIdx.x * MISC_WG + threadIdx.x; i < nn; i += (size_t)gridDim.x * MISC_WG) {
+    for (size_t i = (size_t)blockIdx.x * MISC_WG + threadIdx.x; i < nn; i += (size_t)gx * MISC_WG) {
         const double d = D[base + i];
-        Dp[base + i] = c[i / n] * c[i % n] * d;
+        b.Dp[base + i] = c[i / n] * c[i % n] * d;
+        b.W[base + i] = 0.0;
         const double ad = fabs(d);
         mx = (ad > mx || ad != ad) ? ad : mx;   // NaN propagates
     }
+    if (b.dmax_bits) {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const double o = __shfl_xor(mx, off, 64);
-        mx = (o > mx || o != o) ? o : mx;
+        for (int off = 32; off >= 1; off >>= 1) {
+            const double o = __shfl_xor(mx, off, 64);
+            mx = (o > mx || o != o) ? o : mx;
+        }
+        if ((threadIdx.x & 63) == 0) {
+            const unsigned long long u =
+                mx != mx ? 0x7ff8000000000000ull : (unsigned long long)__double_as_longlong(mx);
+            atomicMax(b.dmax_bits, u);
+        }
     }
-    if ((threadIdx.x & 63) == 0 && dmax_bits) {
-        unsigned long long b = mx != mx ? 0x7ff8000000000000ull : (unsigned long long)__double_as_longlong(mx);
-        atomicMax(dmax_bits, b);
+    if (blockIdx.x == 0 && mol == 0) {
+        for (int i = threadIdx.x; i < b.ncounters; i += MISC_WG) b.counters[i] = 0ull;
+        for (int i = threadIdx.x; i < b.nwork; i += MISC_WG) b.work[i] = 0ull;
     }
 }
 
@@ -102,30 +129,29 @@ __global__ void k_reduce_replicas(const double* __restrict__ rep, int nrep, size
     }
 }
 
-// dket[comp][s] = D'_cd of ket pair s of one list (component comp of its
-// block), so that the class kernels read it coalesced by ket position.
-__global__ void k_gather_ket(const PairInfo* __restrict__ kets, int n, int nc, int nd, const double* __restrict__ D,
-                             const long long* __restrict__ moff, double* __restrict__ dket) {
-    const int i = blockIdx.x * MISC_WG + threadIdx.x;
-    if (i >= n * nc * nd) return;
-    const int s = i % n, comp = i / n;
+// The elements of one list's ket blocks, component comp of pair s at comp n + s:
+// their places in the matrices and the products of their component factors.
+__global__ void k_ket_elems(const PairInfo* __restrict__ kets, int n, int nc, int nd, const long long* __restrict__ moff,
+                            const int* __restrict__ mboff, const double* __restrict__ cs, KetElem* __restrict__ out) {
+    const long long i = (long long)blockIdx.x * MISC_WG + threadIdx.x;
+    if (i >= (long long)n * nc * nd) return;
+    const int s = (int)(i % n), comp = (int)(i / n);
     const PairInfo p = kets[s];
-    dket[i] = D[(size_t)moff[p.mol] + (size_t)(p.bfa + comp / nd) * p.ld + p.bfb + comp % nd];
+    const int r = p.bfa + comp / nd, c = p.bfb + comp % nd;
+    const double* m = cs + mboff[p.mol];
+    out[i] = KetElem{moff[p.mol] + (long long)r * p.ld + c, m[r] * m[c]};
 }
 
-// W_cd += wket[comp][s] for every ket pair s of one list: each pair owns its
-// W block, so plain read-modify-write (no atomics) after the class kernels.
-__global__ void k_scatter_ket(const PairInfo* __restrict__ kets, int n, int nc, int nd,
-                              const double* __restrict__ wket, const long long* __restrict__ moff,
-                              double* __restrict__ W) {
-    const int i = blockIdx.x * MISC_WG + threadIdx.x;
-    if (i >= n * nc * nd) return;
-    const int s = i % n, comp = i / n;
-    const double v = wket[i];
-    if (v == 0.0) return;
-    const PairInfo p = kets[s];
-    const size_t idx = (size_t)moff[p.mol] + (size_t)(p.bfa + comp / nd) * p.ld + p.bfb + comp % nd;
-    W[idx] += v;
+// W += the ket lists' J sums: each pair owns its W block, so plain
+// read-modify-write (no atomics) after the class kernels.
+__global__ void k_scatter_kets(const KetElem* __restrict__ ke, size_t nke, const double* __restrict__ wket,
+                               double* __restrict__ W) {
+    for (size_t i = (size_t)blockIdx.x * MISC_WG + threadIdx.x; i < nke; i += (size_t)gridDim.x * MISC_WG) {
+        const long long idx = ke[i].idx;
+        if (idx < 0) continue;
+        const double v = wket[i];
+        if (v != 0.0) W[idx] += v;
+    }
 }
 
 // ---- SCF helpers ------------------------------------------------------------------
@@ -249,11 +275,13 @@ static dim3 ragged_grid(int max_ld, int nmol) {
     if (g > 4096) g = 4096;
     return dim3((unsigned)(g ? g : 1), (unsigned)nmol);
 }
-hipError_t hfx_prepare_density(const double* D, const double* cs, int nmol, const long long* moff, const int* mdim,
-                               const int* mboff, int max_ld, double* Dp, unsigned long long* dmax_bits,
-                               hipStream_t st) {
-    hipLaunchKernelGGL(k_prepare_density, ragged_grid(max_ld, nmol), dim3(MISC_WG), 0, st, D, cs, moff, mdim, mboff, Dp,
-                       dmax_bits);
+hipError_t hfx_start_build(const double* D, const double* cs, int nmol, const long long* moff, const int* mdim,
+                           const int* mboff, int max_ld, const KetElem* ke, size_t nke, const StartBufs* b,
+                           hipStream_t st) {
+    dim3 g = ragged_grid(max_ld, nmol);
+    const int gx = (int)g.x;
+    g.x += (unsigned)std::min<size_t>((nke + (size_t)MISC_WG * nmol - 1) / ((size_t)MISC_WG * nmol), 4096);
+    hipLaunchKernelGGL(k_start_build, g, dim3(MISC_WG), 0, st, D, cs, moff, mdim, mboff, gx, ke, nke, *b);
     return hipGetLastError();
 }
 hipError_t hfx_fill(double* p, size_t n, double v, hipStream_t st) {
@@ -278,20 +306,17 @@ hipError_t hfx_split(const PairInfo* bra, const double* ketq, const int4* tasks,
                        ntask, fp32_tau, dmax_bits, split);
     return hipGetLastError();
 }
-hipError_t hfx_gather_ket(const PairInfo* kets, int n, int nc, int nd, const double* D, const long long* moff,
-                          double* dket, hipStream_t st) {
-    const int tot = n * nc * nd;
+hipError_t hfx_ket_elems(const PairInfo* kets, int n, int nc, int nd, const long long* moff, const int* mboff,
+                         const double* cs, KetElem* out, hipStream_t st) {
+    const long long tot = (long long)n * nc * nd;
     if (tot <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gather_ket, dim3((tot + MISC_WG - 1) / MISC_WG), dim3(MISC_WG), 0, st, kets, n, nc, nd, D, moff,
-                       dket);
+    hipLaunchKernelGGL(k_ket_elems, dim3((unsigned)((tot + MISC_WG - 1) / MISC_WG)), dim3(MISC_WG), 0, st, kets, n, nc,
+                       nd, moff, mboff, cs, out);
     return hipGetLastError();
 }
-hipError_t hfx_scatter_ket(const PairInfo* kets, int n, int nc, int nd, const double* wket, const long long* moff,
-                           double* W, hipStream_t st) {
-    const int tot = n * nc * nd;
-    if (tot <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scatter_ket, dim3((tot + MISC_WG - 1) / MISC_WG), dim3(MISC_WG), 0, st, kets, n, nc, nd, wket,
-                       moff, W);
+hipError_t hfx_scatter_kets(const KetElem* ke, size_t nke, const double* wket, double* W, hipStream_t st) {
+    if (nke == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_scatter_kets, dim3(grid_for(nke)), dim3(MISC_WG), 0, st, ke, nke, wket, W);
     return hipGetLastError();
 }
 hipError_t hfx_assemble(const double* H, const double* W, const double* cs, int nmol, const long long* moff,

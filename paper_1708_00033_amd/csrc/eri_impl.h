@@ -297,12 +297,13 @@ __device__ __forceinline__ void flush_counts(const ClassArgs& a, unsigned c64, u
 // before digestion, both in the same launch and into the same LDS rows).
 //
 // LDS of a class kernel: the class's FP64 Boys rows (the FP32 evaluation
-// rounds their coefficients), then
-// (MODE 0) the bra rows F_I, F_J of the current task.
+// rounds their coefficients), the J sums of the current task's bra block, then
+// (MODE 0) its bra rows F_I, F_J.
 template <class E>
 struct LdsLayout {
     static constexpr int L = E::LA + E::LB + E::LC + E::LD;
-    static constexpr int ROWS = boys_rows(L) * BOYS_ROW;   // offset of the bra rows, doubles
+    static constexpr int JSUM = boys_rows(L) * BOYS_ROW;   // offsets in doubles
+    static constexpr int ROWS = JSUM + hfx_jsum_doubles(hfx_ncart(E::LA) * hfx_ncart(E::LB));
 };
 
 // Uniform per workgroup: padding tasks (XCD striping) and other shards' bras do nothing.
@@ -315,7 +316,7 @@ __device__ __forceinline__ void load_boys_lds(const ClassArgs& a, double* t64) {
     using LL = LdsLayout<E>;
     const double2* __restrict__ g = reinterpret_cast<const double2*>(a.boys64 + boys_block(LL::L));
     double2* t = reinterpret_cast<double2*>(t64);
-    for (int i = threadIdx.x; i < LL::ROWS / 2; i += E::WGS) t[i] = g[i];
+    for (int i = threadIdx.x; i < LL::JSUM / 2; i += E::WGS) t[i] = g[i];
     __syncthreads();
 }
 
@@ -335,6 +336,7 @@ __device__ __forceinline__ void task_sync() {
 struct BraTask {
     PairInfo bra;
     int s0, split, send;   // kets [s0, split) in FP64, [split, send) in FP32
+    int w;                 // its windows and list
     int N;                 // leading dimension of the molecule's blocks, which start at element mo
     // LDS bra rows of length RS: whole rows, or (column windows) the task's
     // window of shell c at [0, RS/2) and of shell d at [RS/2, RS) (one region
@@ -352,21 +354,22 @@ __device__ __forceinline__ BraTask load_task(const ClassArgs& a, const int ti) {
     t.on = false;
     t.RS = 0;
     if (ti < 0) return t;
-    const int4 task = a.tasks[ti];
+    const int4 task = uniform_task(a.tasks, ti);
     if (!task_active(a, task)) return t;
     t.on = true;
-    t.bra = a.bra[task.x];
+    t.bra = uniform_pair(a.bra, task.x);
     t.s0 = task.y;
     t.send = task.z;
-    t.split = FP32 ? min(max(a.split[ti], t.s0), t.send) : t.send;
+    t.w = task.w;
+    t.split = FP32 ? min(max(((const HFX_CONST_AS int*)a.split)[ti], t.s0), t.send) : t.send;
     t.N = t.RS = t.half = t.bra.ld;
     t.cb = t.db = 0;
-    t.mo = (size_t)a.moff[t.bra.mol];
+    t.mo = (size_t)((const HFX_CONST_AS long long*)a.moff)[t.bra.mol];
     t.wo = t.mo + (a.wrep ? (size_t)hfx_xcc_id() * a.wrep : 0);
     if (a.win) {
         t.RS = a.rs;
         t.half = t.RS / 2;
-        const int wc = task.w & 0xffff, wd = task.w >> 16;
+        const int wc = hfx_task_wc(task.w), wd = hfx_task_wd(task.w);
         t.cb = wc * a.win;
         t.db = wd == wc ? t.cb : wd * a.win - t.half;
     }
@@ -406,26 +409,28 @@ struct BraRun {
     static constexpr int NT = WAVE ? 64 : E::WGS;   // lanes of the task
     static constexpr int nda = (DST & 1) ? NA : 0, ndb = (DST & 2) ? NB : 0;
     static_assert(DST == 0 || (MODE == 0 && NI <= HFX_STAGE_D_MAX_NI), "no staged D' rows");
-    const ClassArgs& a;
+    const ClassArgs& args;
     const double* t64;
     int tid;
-    double *F, *DR;          // F_I and F_J; staged rows
+    double *JS, *F, *DR;     // the bra block's J sums (zero between tasks); F_I and F_J; staged rows
     double dab[NAB];
     unsigned n64 = 0, n32 = 0;
 
-    __device__ __forceinline__ BraRun(const ClassArgs& args, double* lds)
-        : a(args), t64(lds), tid(WAVE ? (int)(threadIdx.x & 63) : (int)threadIdx.x) {
-        F = lds + LdsLayout<E>::ROWS + (WAVE ? (int)(threadIdx.x >> 6) * (NA + NB + nda + ndb) * a.rs : 0);
-        DR = F + (NA + NB) * a.rs;
+    __device__ __forceinline__ BraRun(const ClassArgs& launch, double* lds)
+        : args(launch), t64(lds), tid(WAVE ? (int)(threadIdx.x & 63) : (int)threadIdx.x) {
+        JS = lds + LdsLayout<E>::JSUM;
+        F = lds + LdsLayout<E>::ROWS + (WAVE ? (int)(threadIdx.x >> 6) * (NA + NB + nda + ndb) * args.rs : 0);
+        DR = F + (NA + NB) * args.rs;
     }
     __device__ __forceinline__ void clear_rows() {
+        if (!WAVE && tid < NAB) JS[tid] = 0.0;
         if constexpr (MODE == 0)
-            for (int i = tid; i < (NA + NB) * a.rs; i += NT) F[i] = 0.0;
+            for (int i = tid; i < (NA + NB) * args.rs; i += NT) F[i] = 0.0;
     }
     // D'_ab and the staged rows of a task, over the same columns as F_I / F_J
     // (zero past the molecule's last column).
     __device__ __forceinline__ void stage(const BraTask& t) {
-        const double* __restrict__ Dm = a.D + t.mo;
+        const double* __restrict__ Dm = args.D + t.mo;
 #pragma unroll
         for (int m = 0; m < NA; ++m)
 #pragma unroll
@@ -442,11 +447,16 @@ struct BraRun {
     }
     __device__ __forceinline__ void flush(const BraTask& t) {
         if constexpr (MODE == 0)
-            flush_rows<NA, NB, NT>(F, tid, t.RS, t.half, t.cb, t.db, t.N, t.bra.bfa, t.bra.bfb, a.W + t.wo);
+            flush_rows<NA, NB, NT>(F, tid, t.RS, t.half, t.cb, t.db, t.N, t.bra.bfa, t.bra.bfb, args.W + t.wo);
+        if (!WAVE && tid < NAB) {
+            atomicAdd(args.W + t.wo + (size_t)(t.bra.bfa + tid / NB) * t.N + t.bra.bfb + tid % NB, JS[tid]);
+            JS[tid] = 0.0;
+        }
     }
     // The task's kets: evaluation, digestion into the LDS rows (MODE 0) and
     // W, then the bra block's J.
     __device__ __forceinline__ void kets(const BraTask& t) {
+        const ClassArgs a = of_list(args, t.w);
         const PairInfo& bra = t.bra;
         const double* __restrict__ Dm = a.D + t.mo;
         double* __restrict__ Wm = a.W + t.wo;
@@ -503,13 +513,13 @@ struct BraRun {
             digest<NA, NB, NC, ND, MODE, DST>(I, g, a, bra, kb.x, kb.y, s, dab, jab, FI, FJ, Dm, Wm, N, RS, cb, db, dcd,
                                               Wm, a.wket, DI, DJ);
         }
-        // bra J block: wave reduction, one global add per wave (column bfb may lie
-        // outside the task's windows)
+        // bra J block: summed over each wave, then over the workgroup in LDS, so
+        // that a task adds once to W (column bfb may lie outside its windows)
 #pragma unroll
         for (int mn = 0; mn < NAB; ++mn) {
             const double v = wave_sum(jab[mn]);
             if ((threadIdx.x & 63) == 0)
-                atomicAdd(Wm + (size_t)(bra.bfa + mn / NB) * N + bra.bfb + mn % NB, 2.0 * a.cj * v);
+                atomicAdd(WAVE ? Wm + (size_t)(bra.bfa + mn / NB) * N + bra.bfb + mn % NB : JS + mn, 2.0 * a.cj * v);
         }
     }
 };
@@ -545,14 +555,15 @@ struct QueueReader {
 // ket block's J sum over the block goes out in one atomic per component; each
 // bra has its own LDS rows F_I, F_J (MODE 0).  FP64 only.
 template <class E, int MODE, int KP, int NBL>
-__device__ __forceinline__ void class_task_kr(const ClassArgs& a, const int ti, const double* t64, unsigned& cnt64) {
+__device__ __forceinline__ void class_task_kr(const ClassArgs& args, const int ti, const double* t64, unsigned& cnt64) {
     constexpr int NA = hfx_ncart(E::LA), NB = hfx_ncart(E::LB), NC = hfx_ncart(E::LC), ND = hfx_ncart(E::LD);
     constexpr int NAB = NA * NB, NCD = NC * ND, NI = NAB * NCD;
     constexpr int NT = E::WGS;
     const int tid = (int)threadIdx.x;
     extern __shared__ __align__(16) double lds[];
-    const int4 task = a.tasks[ti];
+    const int4 task = uniform_task(args.tasks, __builtin_amdgcn_readfirstlane(ti));
     if (task.x < 0) return;
+    const ClassArgs a = of_list(args, task.w);
     const int r0 = task.x & 0x0fffffff;
     const int nb = (task.x >> 28) + 1;
     const int s0 = task.y, send = task.z;
@@ -561,7 +572,7 @@ __device__ __forceinline__ void class_task_kr(const ClassArgs& a, const int ti, 
 #pragma unroll
     for (int i = 0; i < NBL; ++i) {
         on[i] = i < nb && (a.nshards <= 1 || (r0 + i) % a.nshards == a.shard);
-        bra[i] = a.bra[r0 + (i < nb ? i : 0)];
+        bra[i] = uniform_pair(a.bra, r0 + (i < nb ? i : 0));
     }
     bool any = false;
 #pragma unroll
@@ -575,7 +586,7 @@ __device__ __forceinline__ void class_task_kr(const ClassArgs& a, const int ti, 
     if (a.win) {
         RS = a.rs;
         half = RS / 2;
-        const int wc = task.w & 0xffff, wd = task.w >> 16;
+        const int wc = hfx_task_wc(task.w), wd = hfx_task_wd(task.w);
         cb = wc * a.win;
         db = wd == wc ? cb : wd * a.win - half;
     }
@@ -701,22 +712,23 @@ __global__ __launch_bounds__(E::WGS) void k_class_kr(const ClassArgs a) {
 // plans): each bra keeps the kets of its own screened prefix, the test the
 // planner used.
 template <class E, int MODE>
-__device__ __forceinline__ void class_task_multi(const ClassArgs& a, const int ti, const double* t64,
+__device__ __forceinline__ void class_task_multi(const ClassArgs& args, const int ti, const double* t64,
                                                  unsigned& cnt64) {
     constexpr int NA = hfx_ncart(E::LA), NB = hfx_ncart(E::LB), NC = hfx_ncart(E::LC), ND = hfx_ncart(E::LD);
     constexpr int NAB = NA * NB, NI = NAB * NC * ND;
     constexpr int NT = E::WGS;
     extern __shared__ __align__(16) double lds[];
     const int tid = (int)threadIdx.x, lane = tid & 63;
-    const int4 task = a.tasks[ti];
+    const int4 task = uniform_task(args.tasks, __builtin_amdgcn_readfirstlane(ti));
     if (task.x < 0) return;
+    const ClassArgs a = of_list(args, task.w);
     const int r0 = task.x & 0x0fffffff, nb = (task.x >> 28) + 1;
     const int s0 = task.y, nq = task.z - task.y;
     unsigned n64 = 0;
     for (int i = 0; i < nb; ++i) {
         const int r = r0 + i;
         if (a.nshards > 1 && r % a.nshards != a.shard) continue;   // uniform
-        const PairInfo bra = a.bra[r];
+        const PairInfo bra = uniform_pair(a.bra, r);
         const int N = bra.ld;
         const size_t moff = (size_t)a.moff[bra.mol];
         const double sbra = bra.a != bra.b ? 2.0 : 1.0;
@@ -725,7 +737,7 @@ __device__ __forceinline__ void class_task_multi(const ClassArgs& a, const int t
         if (a.win) {
             RS = a.rs;
             half = RS / 2;
-            const int wc = task.w & 0xffff, wd = task.w >> 16;
+            const int wc = hfx_task_wc(task.w), wd = hfx_task_wd(task.w);
             cb = wc * a.win;
             db = wd == wc ? cb : wd * a.win - half;
         }

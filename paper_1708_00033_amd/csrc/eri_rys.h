@@ -401,16 +401,17 @@ struct RysSteps {
 // One task (one bra, a range of its kets) on the workgroup.  Counts the
 // evaluated quartets of the workgroup on lane 0.
 template <class E, int MODE, int FP32, bool MULTI>
-__device__ __forceinline__ void class_task_rys(const ClassArgs& a, const int ti, unsigned& cnt64, unsigned& cnt32) {
+__device__ __forceinline__ void class_task_rys(const ClassArgs& args, const int ti, unsigned& cnt64, unsigned& cnt32) {
     using X = RysDims<E>;
     constexpr int NA = X::NA, NB = X::NB, NC = X::NC, ND = X::ND, NCD = X::NCD, NK = X::NK, NT = E::WGS;
     extern __shared__ __align__(16) double lds[];
-    const int4 task = a.tasks[ti];
+    const int4 task = uniform_task(args.tasks, __builtin_amdgcn_readfirstlane(ti));
     const int r = task.x;
-    if (!task_active(a, task)) return;
+    if (!task_active(args, task)) return;
+    const ClassArgs a = of_list(args, task.w);
     const int s0 = task.y, send = task.z;
     const int split = FP32 ? min(max(a.split[ti], s0), send) : send;
-    const PairInfo bra = a.bra[r];
+    const PairInfo bra = uniform_pair(a.bra, r);
     const int N = bra.ld, tid = (int)threadIdx.x;
     const size_t mo = (size_t)a.moff[bra.mol] + (a.wrep ? (size_t)hfx_xcc_id() * a.wrep : 0);
     const int ndens = MULTI ? a.ndens : 1;
@@ -423,7 +424,7 @@ __device__ __forceinline__ void class_task_rys(const ClassArgs& a, const int ti,
     if (a.win) {
         RS = a.rs;
         half = RS / 2;
-        const int wc = task.w & 0xffff, wd = task.w >> 16;
+        const int wc = hfx_task_wc(task.w), wd = hfx_task_wd(task.w);
         cb = wc * a.win;
         db = wd == wc ? cb : wd * a.win - half;
     }

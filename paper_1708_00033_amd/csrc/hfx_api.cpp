@@ -137,14 +137,13 @@ static void release_system(hfx_ctx* c) {
         dfree(c->d_pairs[k]);
         c->npair[k] = 0;
     }
-    for (auto& L : c->ketlists) {
-        dfree(L.d_pairs);
-        dfree(L.d_q);
-        dfree(L.d_soa);
-        dfree(L.d_soa32);
-        dfree(L.d_kbf);
-        dfree(L.d_kpos);
-    }
+    dfree(c->d_lists);
+    dfree(c->d_kets);
+    dfree(c->d_kbf);
+    dfree(c->d_ketq);
+    dfree(c->d_kpos);
+    dfree(c->d_soa);
+    dfree(c->d_soa32);
     dfree(c->d_kelem);
     dfree(c->d_dket);
     dfree(c->d_wket);
@@ -157,12 +156,14 @@ static void release_system(hfx_ctx* c) {
     c->host_ket.clear();
     c->host_kpos.clear();
     for (auto& p : c->plans) {
-        dfree(p.d_split);
-        dfree(p.d_tasks);
         if (p.ev0) (void)hipEventDestroy(p.ev0);
         if (p.ev1) (void)hipEventDestroy(p.ev1);
     }
     c->plans.clear();
+    c->launches.clear();
+    c->classes.clear();
+    dfree(c->d_tasks);
+    dfree(c->d_split);
     for (auto& t : c->totals) t = ClassTotals();
     dfree(c->d_cscale);
     dfree(c->d_moff);
@@ -401,7 +402,9 @@ static hfx_status plan_sub(hfx_ctx* c, int B, int li, const std::vector<PairInfo
     P.lds_bytes = (size_t)(ncart(kPairL[B][0]) + ncart(kPairL[B][1])) * c->rs * sizeof(double);
     P.fp64_only = nint >= 600;   // a d-d bra with a d-d or d-p ket: no FP32 kernels
     // FP64 rows (the mixed kernels' FP32 part reads them too); the cooperative kernels read their table from memory
-    P.lds_tab = P.rys ? (size_t)hfx_class_rys_lds(P.cid, 0, 1) : (size_t)boys_lds_bytes(class_L(P.cid));
+    P.lds_tab = P.rys ? (size_t)hfx_class_rys_lds(P.cid, 0, 1)
+                      : boys_lds_bytes(class_L(P.cid)) +
+                            sizeof(double) * hfx_jsum_doubles(ncart(kPairL[B][0]) * ncart(kPairL[B][1]));
     const int digest = c->tune_digest[P.cid] >= 0 ? c->tune_digest[P.cid] : c->opt.digest;
     // 160 KiB of LDS per workgroup, less room for the persistent kernel's static counter
     constexpr size_t kLdsBudget = 160 * 1024 - 256;
@@ -501,7 +504,7 @@ static hfx_status plan_sub(hfx_ctx* c, int B, int li, const std::vector<PairInfo
     }
     size_t qmax = 0;
     for (auto& q : queue) qmax = std::max(qmax, q.size());
-    std::vector<int4> tasks;
+    std::vector<int4>& tasks = P.tasks;
     tasks.reserve(qmax * NX);
     for (size_t k = 0; k < qmax; ++k)
         for (int j = 0; j < NX; ++j) tasks.push_back(k < queue[j].size() ? queue[j][k] : make_int4(-1, 0, 0, 0));
@@ -517,27 +520,22 @@ static hfx_status plan_sub(hfx_ctx* c, int B, int li, const std::vector<PairInfo
         if (P.lds() > 160 * 1024 - 256) P.wave = 0;   // does not fit: one task per workgroup
     }
     if (P.kr) {
-        int nb = hfx_class_resident_blocks_kr(P.cid, P.mode, KL.kp, P.nbl, P.lds());
+        const int nb = hfx_class_resident_blocks_kr(P.cid, P.mode, KL.kp, P.nbl, P.lds());
         if (nb <= 0) return hfx_fail(c, HFX_ERR_DEVICE, "occupancy query of a register-tiled class kernel failed");
-        nb = std::min(nb, P.ntask);
-        P.nblocks[0] = P.nblocks[1] = ((nb + 7) / 8) * 8;
+        P.resident[0] = P.resident[1] = nb;
     }
     for (int mx = 0; mx < (P.kr ? 0 : (P.fp64_only ? 1 : 2)); ++mx) {
-        int nb = P.rys ? hfx_class_resident_blocks_rys(P.cid, P.mode, mx, P.lds())
+        const int nb = P.rys ? hfx_class_resident_blocks_rys(P.cid, P.mode, mx, P.lds())
                        : hfx_class_resident_blocks(P.cid, P.alt, P.wave > 0, P.mode, mx, P.dstage, P.lds());
         if (nb <= 0) return hfx_fail(c, HFX_ERR_DEVICE, "occupancy query of a class kernel failed");
-        nb = std::min(nb, P.ntask);
-        P.nblocks[mx] = ((nb + 7) / 8) * 8;   // whole rounds over the 8 XCDs
+        P.resident[mx] = nb;
     }
-    HIPCK(dalloc(&P.d_split, tasks.size()));
-    HIPCK(dalloc(&P.d_tasks, tasks.size()));
-    HIPCK(hipMemcpy(P.d_tasks, tasks.data(), tasks.size() * sizeof(int4), hipMemcpyHostToDevice));
     ClassTotals& T = c->totals[P.cid];
     T.quartets += P.quartets;
     T.integrals += P.integrals;
     T.prim += P.prim;
     T.ntask += P.ntask;
-    c->plans.push_back(P);
+    c->plans.push_back(std::move(P));
     return HFX_OK;
 }
 
@@ -547,12 +545,14 @@ static hfx_status replan(hfx_ctx* c) {
     drop_graph(c);
     dfree(c->d_work);
     for (auto& p : c->plans) {
-        dfree(p.d_split);
-        dfree(p.d_tasks);
         if (p.ev0) (void)hipEventDestroy(p.ev0);
         if (p.ev1) (void)hipEventDestroy(p.ev1);
     }
     c->plans.clear();
+    c->launches.clear();
+    c->classes.clear();
+    dfree(c->d_tasks);
+    dfree(c->d_split);
     for (auto& t : c->totals) t = ClassTotals();
     for (int B = 0; B < 6; ++B)
         for (size_t li = 0; li < c->ketlists.size(); ++li) {
@@ -566,6 +566,52 @@ static hfx_status replan(hfx_ctx* c) {
     for (int i = 0; i < 21; ++i) rank[order[i]] = i;
     std::stable_sort(c->plans.begin(), c->plans.end(),
                      [&](const SubPlan& x, const SubPlan& y) { return rank[x.cid] < rank[y.cid]; });
+    // One task array, class by class.  A class's plans go in one launch (but
+    // register-tiled ones, with a kernel per primitive count): a water dimer's
+    // 14 launches become 6 (134 -> 86 us), five waters' 68 become 21 (455 -> 288
+    // us as a replayed graph), and there are fewer idle ends (a 44-atom sheet
+    // 101.7 -> 93.8 ms); the lists with the most primitives first, so that the
+    // last workgroups have short tasks.  Classes beyond 2^14 tasks, 8 for every
+    // workgroup on the chip, keep a launch per plan: start and end no longer show
+    // there (64 waters 92.6 ms either way), and one launch, running beside
+    // another class's on the second stream, rounded W's sums more (64 waters:
+    // rms error 6.4e-15 against 4.8e-15).
+    constexpr long long kJoinTasks = 1 << 14;
+    size_t nt = 0;
+    for (size_t i = 0; i < c->plans.size();) {
+        size_t e = i;
+        long long total = 0;
+        for (; e < c->plans.size() && c->plans[e].cid == c->plans[i].cid; ++e) total += c->plans[e].ntask;
+        const bool one = total <= kJoinTasks;
+        std::vector<size_t> by(e - i);
+        for (size_t k = 0; k < by.size(); ++k) by[k] = i + k;
+        if (one)
+            std::stable_sort(by.begin(), by.end(), [&](size_t x, size_t y) {
+                const SubPlan &u = c->plans[x], &v = c->plans[y];
+                if (u.kr != v.kr) return v.kr;
+                return c->ketlists[u.list].kp > c->ketlists[v.list].kp;
+            });
+        for (size_t q = 0; q < by.size(); ++q) {
+            SubPlan& p = c->plans[by[q]];
+            p.toff = nt;
+            if (!(one && q > 0)) c->classes.push_back(ClassLaunch{by[q], nt, 0});
+            if (!(one && q > 0 && !p.kr)) c->launches.push_back(ClassLaunch{by[q], nt, 0});
+            c->classes.back().ntask += p.ntask;
+            c->launches.back().ntask += p.ntask;
+            nt += p.tasks.size();
+        }
+        i = e;
+    }
+    {
+        std::vector<int4> tasks(nt);
+        for (auto& p : c->plans) {
+            std::copy(p.tasks.begin(), p.tasks.end(), tasks.begin() + p.toff);
+            std::vector<int4>().swap(p.tasks);
+        }
+        HIPCK(dalloc(&c->d_split, nt));
+        HIPCK(dalloc(&c->d_tasks, nt));
+        if (nt) HIPCK(hipMemcpy(c->d_tasks, tasks.data(), nt * sizeof(int4), hipMemcpyHostToDevice));
+    }
     HIPCK(dalloc(&c->d_work, 16 * std::max<size_t>(c->plans.size(), 1)));   // 8 queue counters per plan, 16 apart
     bool any_priv = false;
     for (const auto& p : c->plans) any_priv |= p.priv;
@@ -932,6 +978,10 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
     c->kgroup.clear();
     c->kmolg.clear();
     c->kwcode.clear();
+    std::vector<PairInfo> kets;   // of all lists, as their other data
+    std::vector<int4> kbf;
+    std::vector<int> kpos_int;
+    std::vector<double> q, soa;
     for (int K = 0; K < 6; ++K) {
         std::vector<int> nps;
         for (auto& p : all[K])
@@ -972,7 +1022,7 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
             }
             std::vector<int> gstart, molg(nmol + 1, 0), wcode;
             for (size_t s = 0; s < n; ++s) {
-                const int w = wc_of(sub[s]) | (wd_of(sub[s]) << 16);
+                const int w = hfx_task_code(wc_of(sub[s]), wd_of(sub[s]), (int)c->ketlists.size());
                 if (s == 0 || sub[s].mol != sub[s - 1].mol || w != wcode.back()) {
                     gstart.push_back((int)s);
                     wcode.push_back(w);
@@ -981,39 +1031,22 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
             }
             gstart.push_back((int)n);
             for (int m = 0; m < nmol; ++m) molg[m + 1] = std::max(molg[m + 1], molg[m]);   // molecules without kets
-            std::vector<double> q(n), soa((size_t)9 * kp * n);
-            std::vector<int4> kbf(n);
+            KL.s0 = kets.size();
+            KL.soa = soa.size();
+            KL.koff = c->nket;
+            c->nket += ((size_t)ncart(kPairL[K][0]) * ncart(kPairL[K][1]) * n + 31) / 32 * 32;   // 256 bytes
+            soa.resize(KL.soa + (size_t)9 * kp * n);
             for (size_t s = 0; s < n; ++s) {
-                q[s] = sub[s].Q;
-                kbf[s] = make_int4(sub[s].bfa, sub[s].bfb, sub[s].a, sub[s].b);
+                q.push_back(sub[s].Q);
+                kbf.push_back(make_int4(sub[s].bfa, sub[s].bfb, sub[s].a, sub[s].b));
+                kpos_int.push_back((int)sp[s]);
                 for (int k = 0; k < kp; ++k) {
                     const PrimPair& pp = prim[sub[s].prim_off + k];
                     const double f[9] = {pp.p, pp.inv2p, pp.P[0], pp.P[1], pp.P[2], pp.PA[0], pp.PA[1], pp.PA[2], pp.K};
-                    for (int fi = 0; fi < 9; ++fi) soa[((size_t)fi * kp + k) * n + s] = f[fi];
+                    for (int fi = 0; fi < 9; ++fi) soa[KL.soa + ((size_t)fi * kp + k) * n + s] = f[fi];
                 }
             }
-            HIPCK(dalloc(&KL.d_pairs, n));
-            HIPCK(dalloc(&KL.d_q, n));
-            HIPCK(dalloc(&KL.d_soa, soa.size()));
-            KL.ncd = ncart(kPairL[K][0]) * ncart(kPairL[K][1]);
-            KL.koff = c->nket;
-            c->nket += ((size_t)KL.ncd * n + 31) / 32 * 32;   // lists begin on 256 bytes
-            HIPCK(dalloc(&KL.d_kbf, n));
-            HIPCK(hipMemcpy(KL.d_kbf, kbf.data(), n * sizeof(int4), hipMemcpyHostToDevice));
-            {
-                std::vector<int> kp_int(n);
-                for (size_t i = 0; i < n; ++i) kp_int[i] = (int)sp[i];
-                HIPCK(dalloc(&KL.d_kpos, n));
-                HIPCK(hipMemcpy(KL.d_kpos, kp_int.data(), n * sizeof(int), hipMemcpyHostToDevice));
-            }
-            HIPCK(hipMemcpy(KL.d_pairs, sub.data(), n * sizeof(PairInfo), hipMemcpyHostToDevice));
-            HIPCK(hipMemcpy(KL.d_q, q.data(), n * sizeof(double), hipMemcpyHostToDevice));
-            HIPCK(hipMemcpy(KL.d_soa, soa.data(), soa.size() * sizeof(double), hipMemcpyHostToDevice));
-            {
-                const std::vector<float> soa32(soa.begin(), soa.end());
-                HIPCK(dalloc(&KL.d_soa32, soa32.size()));
-                HIPCK(hipMemcpy(KL.d_soa32, soa32.data(), soa32.size() * sizeof(float), hipMemcpyHostToDevice));
-            }
+            kets.insert(kets.end(), sub.begin(), sub.end());
             c->ketlists.push_back(KL);
             klist.push_back(std::move(sub));
             kpos.push_back(std::move(sp));
@@ -1022,13 +1055,32 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
             c->kwcode.push_back(std::move(wcode));
         }
     }
+    // a task names its windows and its list in one word
+    if ((int)c->ketlists.size() > HFX_TASK_MAX_LISTS ||
+        (c->win && c->max_ld / c->win >= (1 << HFX_TASK_WIN_BITS)))
+        return hfx_fail(c, HFX_ERR_INVALID_ARG, "too many ket lists or column windows");
+    auto upload = [&](auto*& d, const auto& h) -> hipError_t {
+        const hipError_t e = dalloc(&d, h.size());
+        return e != hipSuccess || h.empty() ? e
+                                            : hipMemcpy(d, h.data(), h.size() * sizeof(h[0]), hipMemcpyHostToDevice);
+    };
+    HIPCK(upload(c->d_kets, kets));
+    HIPCK(upload(c->d_kbf, kbf));
+    HIPCK(upload(c->d_ketq, q));
+    HIPCK(upload(c->d_kpos, kpos_int));
+    HIPCK(upload(c->d_soa, soa));
+    HIPCK(upload(c->d_soa32, std::vector<float>(soa.begin(), soa.end())));
     HIPCK(dalloc(&c->d_kelem, c->nket));
     HIPCK(dalloc(&c->d_dket, c->nket));
     HIPCK(dalloc(&c->d_wket, c->nket));
     HIPCK(hipMemset(c->d_kelem, 0xff, c->nket * sizeof(KetElem)));   // padding: idx < 0
-    for (const auto& KL : c->ketlists)
-        HIPCK(hfx_ket_elems(KL.d_pairs, KL.n, ncart(kPairL[KL.K][0]), ncart(kPairL[KL.K][1]), c->d_moff, c->d_mboff,
-                            c->d_cscale, c->d_kelem + KL.koff, 0));
+    std::vector<KetListDev> lists;
+    for (const auto& KL : c->ketlists) {
+        lists.push_back(KetListDev{(long long)KL.soa, (long long)KL.koff, (int)KL.s0, KL.n, KL.kp, 0});
+        HIPCK(hfx_ket_elems(c->d_kets + KL.s0, KL.n, ncart(kPairL[KL.K][0]), ncart(kPairL[KL.K][1]), c->d_moff,
+                            c->d_mboff, c->d_cscale, c->d_kelem + KL.koff, 0));
+    }
+    HIPCK(upload(c->d_lists, lists));
     c->host_bra.assign(all.begin(), all.end());
     c->host_pos = pos;
     c->host_ket = std::move(klist);
@@ -1232,7 +1284,7 @@ extern "C" hfx_status hfx_plan_info(hfx_ctx* c, int i, long long* info, double* 
     info[7] = p.priv ? HFX_DIGEST_PRIVATE : p.mode == 1 ? HFX_DIGEST_GLOBAL : p.dstage ? HFX_DIGEST_LDS_D : HFX_DIGEST_LDS;
     info[8] = hfx_class_wgs(p.cid, p.alt);
     info[9] = p.kr ? c->tune_persist[p.cid] : (p.persist ? (p.wave ? 2 : 1) : 0);
-    info[10] = p.persist ? p.nblocks[0] : p.ntask;   // the FP64 kernel's grid
+    info[10] = p.persist ? p.nblocks(0, p.ntask) : p.ntask;   // the FP64 kernel's grid
     info[11] = p.nbl;
     info[12] = p.dstage;
     if (ms) *ms = p.ms;
@@ -1330,67 +1382,73 @@ hfx_status hfx_build_with(hfx_ctx* c, const BuildBufs& bufs, const double* dD, d
     }
     const int ns = build_streams(c);
     HIPCK(fork_streams(c, ns, st));
-    for (size_t pi = 0; pi < c->plans.size(); ++pi) {
+    // one launch per class (the fewer, the shorter its idle ends and a small
+    // build's launch overhead), one per plan when each is timed
+    const size_t nl = c->timing ? c->plans.size() : c->launches.size();
+    for (size_t li = 0; li < nl; ++li) {
+        const size_t pi = c->timing ? li : c->launches[li].plan;
         SubPlan& P = c->plans[pi];
-        const KetList& KL = c->ketlists[P.list];
+        const size_t toff = c->timing ? P.toff : c->launches[li].toff;
+        const long long ntask = c->timing ? P.ntask : c->launches[li].ntask;
+        const int kp = c->ketlists[P.list].kp;
         const int cid = P.cid;
         const bool mx = mixed && !P.fp64_only && c->tune_fp32[cid] && !P.kr;
-        const hipStream_t ps = plan_stream(c, ns, pi, st);
+        const hipStream_t ps = plan_stream(c, ns, li, st);
         if (mx)
-            HIPCK(hfx_split(c->d_pairs[P.B], KL.d_q, P.d_tasks, P.ntask, c->opt.fp32_tau, bufs.dmax, P.d_split,
-                            ps));
+            HIPCK(hfx_split(c->d_pairs[P.B], c->d_lists, c->d_ketq, c->d_tasks + toff, (int)ntask, c->opt.fp32_tau,
+                            bufs.dmax, c->d_split + toff, ps));
         ClassArgs a;
         a.bra = c->d_pairs[P.B];
-        a.ket = KL.d_pairs;
-        a.kbf = KL.d_kbf;
-        a.dket = c->d_dket + KL.koff;
+        a.ket = c->d_kets;
+        a.kbf = c->d_kbf;
+        a.dket = c->d_dket;
         a.prim = c->d_prim;
-        a.kprim = KL.d_soa;
+        a.kprim = c->d_soa;
         a.prim32 = c->d_prim32;
-        a.kprim32 = KL.d_soa32;
-        a.nket_list = KL.n;
-        a.knprim = KL.kp;
-        a.split = mx ? P.d_split : nullptr;
+        a.kprim32 = c->d_soa32;
+        a.lists = c->d_lists;
+        a.nket_list = a.knprim = 0;
+        a.split = mx ? c->d_split + toff : nullptr;
         a.win = c->win;
         a.rs = c->rs;
         a.dstage = P.dstage;
         a.moff = c->d_moff;
-        a.tasks = P.d_tasks;
+        a.tasks = c->d_tasks + toff;
         a.boys64 = c->d_boys64;
         a.rys = rys_block_of(c, cid);
         a.D = bufs.Dp;
         a.W = P.priv ? c->d_Wrep : bufs.W;
         a.wrep = P.priv ? (long long)nn : 0;
-        a.wket = c->d_wket + KL.koff;
+        a.wket = c->d_wket;
         a.counters = bufs.counters + (size_t)cid * HFX_CNT_CLASS;
         a.cj = cj;
         a.ck = ck;
         a.shard = shard;
         a.nshards = nshards;
-        a.work = P.persist ? bufs.work + 16 * pi : nullptr;
-        a.ketq = KL.d_q;
-        a.kpos = KL.d_kpos;
+        a.work = P.persist ? bufs.work + 16 * li : nullptr;
+        a.ketq = c->d_ketq;
+        a.kpos = c->d_kpos;
         a.tau = c->opt.schwarz_tau;
         a.same = P.B == P.K;
-        a.qlen = P.ntask / 8;
+        a.qlen = (int)(ntask / 8);
         a.task_off = 0;
         // a static grid of ntask workgroups is cut into launches of at most
         // kMaxGroups (2^20 x 1024 lanes < 2^32 work-items; a multiple of 8
         // keeps workgroup i on XCD i mod 8 in step with the task queues)
         constexpr int kMaxGroups = 1 << 20;
         if (c->timing && P.ev0) HIPCK(hipEventRecord(P.ev0, ps));
-        // one launch per plan; a mixed build's kernel evaluates each task's
+        // a mixed build's kernel evaluates each task's
         // kets before its split in FP64 and the rest in FP32
         const int m = mx ? 1 : 0;
         if (P.kr) {
-            HIPCK(hfx_launch_class_kr(cid, P.mode, KL.kp, P.nbl, P.nblocks[0], P.lds(), ps, &a));
+            HIPCK(hfx_launch_class_kr(cid, P.mode, kp, P.nbl, P.nblocks(0, ntask), P.lds(), ps, &a));
         } else if (P.persist) {
-            if (P.rys) HIPCK(hfx_launch_class_rys(cid, P.mode, m, 0, P.nblocks[m], P.lds(), ps, &a));
-            else HIPCK(hfx_launch_class(cid, P.alt, P.wave > 0, P.mode, m, P.nblocks[m], P.lds(), ps, &a));
+            if (P.rys) HIPCK(hfx_launch_class_rys(cid, P.mode, m, 0, P.nblocks(m, ntask), P.lds(), ps, &a));
+            else HIPCK(hfx_launch_class(cid, P.alt, P.wave > 0, P.mode, m, P.nblocks(m, ntask), P.lds(), ps, &a));
         } else {
-            for (int off = 0; off < P.ntask; off += kMaxGroups) {
-                a.task_off = off;
-                const int nb = std::min(kMaxGroups, P.ntask - off);
+            for (long long off = 0; off < ntask; off += kMaxGroups) {
+                a.task_off = (int)off;
+                const int nb = (int)std::min<long long>(kMaxGroups, ntask - off);
                 if (P.rys) HIPCK(hfx_launch_class_rys(cid, P.mode, m, 0, nb, P.lds(), ps, &a));
                 else HIPCK(hfx_launch_class(cid, P.alt, 0, P.mode, m, nb, P.lds(), ps, &a));
             }
@@ -1486,10 +1544,10 @@ extern "C" hfx_status hfx_build_jk_multi_dev(hfx_ctx* c, int ndens, const double
     }
     // densities per launch of a plan: as many LDS row sets as fit beside the
     // Boys rows (MODE 0), else all of them with global atomics (MODE 1)
-    std::vector<int> group(c->plans.size()), gmode(c->plans.size());
+    std::vector<int> group(c->classes.size()), gmode(c->classes.size());
     size_t nwork = 0;
-    for (size_t pi = 0; pi < c->plans.size(); ++pi) {
-        const SubPlan& P = c->plans[pi];
+    for (size_t pi = 0; pi < c->classes.size(); ++pi) {
+        const SubPlan& P = c->plans[c->classes[pi].plan];
         const size_t budget = 160 * 1024 - 256;
         if (P.rys) {   // small sums per density in both modes, row sets in MODE 0
             gmode[pi] = P.mode == 0 && !P.priv ? 0 : 1;
@@ -1533,49 +1591,47 @@ extern "C" hfx_status hfx_build_jk_multi_dev(hfx_ctx* c, int ndens, const double
     size_t wofs = 0;
     const int ns = build_streams(c);
     HIPCK(fork_streams(c, ns, st));
-    for (size_t pi = 0; pi < c->plans.size(); ++pi) {
-        const SubPlan& P = c->plans[pi];
-        const KetList& KL = c->ketlists[P.list];
+    for (size_t pi = 0; pi < c->classes.size(); ++pi) {
+        const SubPlan& P = c->plans[c->classes[pi].plan];
+        const long long ntask = c->classes[pi].ntask;
         const hipStream_t ps = plan_stream(c, ns, pi, st);
         ClassArgs a;
         std::memset(&a, 0, sizeof(a));
         a.bra = c->d_pairs[P.B];
-        a.ket = KL.d_pairs;
-        a.kbf = KL.d_kbf;
+        a.ket = c->d_kets;
+        a.kbf = c->d_kbf;
         a.prim = c->d_prim;
-        a.kprim = KL.d_soa;
-        a.nket_list = KL.n;
-        a.knprim = KL.kp;
-        a.tasks = P.d_tasks;
+        a.kprim = c->d_soa;
+        a.lists = c->d_lists;
+        a.tasks = c->d_tasks + c->classes[pi].toff;
         a.moff = c->d_moff;
         a.boys64 = c->d_boys64;
         a.rys = rys_block_of(c, P.cid);
         a.D = Dp;
         a.W = WJ;
         a.WK = WK;
-        a.dket = c->d_dket_multi + KL.koff;
         a.counters = c->d_counters + (size_t)P.cid * HFX_CNT_CLASS;
         a.cj = 1.0;    // J updates into W: (W + W^T)/8 = J
         a.ck = -1.0;   // K updates into WK: (WK + WK^T)/8 = K
         a.nshards = 1;
-        a.qlen = P.ntask / 8;
-        a.ketq = KL.d_q;
-        a.kpos = KL.d_kpos;
+        a.qlen = (int)(ntask / 8);
+        a.ketq = c->d_ketq;
+        a.kpos = c->d_kpos;
         a.tau = c->opt.schwarz_tau;
         a.same = P.B == P.K;
         a.win = c->win;
         a.rs = c->rs;
         a.dstride = (long long)nn;
         a.kstride = (long long)c->nket;
-        const int nblocks = ((std::min(P.ntask, 2048) + 7) / 8) * 8;   // resident or queued: queues drain either way
+        const int nblocks = (int)((std::min(ntask, 2048ll) + 7) / 8 * 8);   // resident or queued: queues drain either way
         for (int d0 = 0; d0 < ndens; d0 += group[pi]) {
             ClassArgs b = a;
             b.ndens = std::min(group[pi], ndens - d0);
             b.D = Dp + (size_t)d0 * nn;
             b.W = WJ + (size_t)d0 * nn;
             b.WK = WK + (size_t)d0 * nn;
-            b.dket = c->d_dket_multi + KL.koff + (size_t)d0 * a.kstride;
-            b.wket = c->d_wket_multi + KL.koff + (size_t)d0 * a.kstride;
+            b.dket = c->d_dket_multi + (size_t)d0 * a.kstride;
+            b.wket = c->d_wket_multi + (size_t)d0 * a.kstride;
             b.work = c->d_multi_work + wofs;
             wofs += 8;
             const size_t rows = gmode[pi] == 0 ? (size_t)b.ndens * P.lds_bytes : 0;

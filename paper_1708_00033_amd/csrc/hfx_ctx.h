@@ -17,26 +17,21 @@ struct ShellHost {
 };
 
 // Significant pairs of one pair class that share one primitive count, sorted
-// by Schwarz bound (descending); ket primitives as a structure of arrays.
+// by Schwarz bound (descending): a range of the context's ket arrays.
 struct KetList {
     int K = 0, kp = 0, n = 0;
-    PairInfo* d_pairs = nullptr;
-    double* d_q = nullptr;
-    double* d_soa = nullptr;
-    float* d_soa32 = nullptr;   // its FP32 copy (the FP32 evaluation of mixed builds)
-    size_t koff = 0;            // its ket-block elements, ncart(l_c) ncart(l_d) x n, in the context's arrays of them
-    int4* d_kbf = nullptr;      // per ket: (bfa, bfb, a, b)
-    int* d_kpos = nullptr;      // per ket: position in its pair class's Q-sorted list
-    int ncd = 1;
+    size_t s0 = 0;              // first ket
+    size_t soa = 0;             // first ket primitive element, 9 kp n of them
+    size_t koff = 0;            // first ket-block element, ncart(l_c) ncart(l_d) x n of them
 };
 
-// One launch: class (B, K) against one ket list.
+// The tasks of class (B, K) against one ket list.
 struct SubPlan {
     int cid = 0, B = 0, K = 0, list = 0;
     int nbra = 0;             // bras with at least one ket
     int ntask = 0;
-    int* d_split = nullptr;   // per task: first ket evaluated in FP32 (mixed builds)
-    int4* d_tasks = nullptr;
+    std::vector<int4> tasks;  // host, until they are uploaded
+    size_t toff = 0;          // first task in the context's array
     long long quartets = 0, integrals = 0, prim = 0;
     size_t lds_bytes = 0;     // bra rows F_I, F_J (LDS digestion)
     size_t lds_dst = 0;       // the bra's staged D' rows (LDS digestion with D rows)
@@ -58,7 +53,18 @@ struct SubPlan {
     bool priv = false;        // private digestion: global atomics into the per-XCD copies of W
     int nbl = 1;              // bras per task (register-tiled blocks of Q-adjacent bras)
     int alt = 0;              // 1: the class's alternative workgroup size
-    int nblocks[2] = {0, 0};  // resident grid (multiple of 8) for the FP64 / the mixed kernel
+    int resident[2] = {0, 0}; // workgroups that fit on the device, for the FP64 / the mixed kernel
+    int nblocks(int mixed, long long nt) const {   // resident grid for nt tasks, whole rounds over the 8 XCDs
+        return (int)((std::min<long long>(resident[mixed], nt) + 7) / 8 * 8);
+    }
+};
+
+// One launch of a build: the tasks of a class's plans against several ket lists
+// (register-tiled plans: of one).  plan: any of them (they agree in all that a
+// launch needs).
+struct ClassLaunch {
+    size_t plan, toff;
+    long long ntask;
 };
 
 struct ClassTotals {
@@ -118,13 +124,27 @@ struct hfx_ctx {
     PairInfo* d_pairs[6] = {nullptr};   // significant pairs per pair class, Q descending (bras)
     int npair[6] = {0};
     std::vector<KetList> ketlists;      // per pair class and primitive count (kets)
-    // the ket lists' blocks one after the other (KetList::koff): elements, D'
+    // the ket lists one after the other: pairs, first basis functions and
+    // shells (bfa, bfb, a, b), Q, positions in the pair class's Q-sorted list,
+    // primitives as a structure of arrays and their FP32 copy
+    KetListDev* d_lists = nullptr;
+    PairInfo* d_kets = nullptr;
+    int4* d_kbf = nullptr;
+    double* d_ketq = nullptr;
+    int* d_kpos = nullptr;
+    double* d_soa = nullptr;
+    float* d_soa32 = nullptr;
+    // and their blocks (KetList::koff): elements, D'
     // gathered per build, J accumulators; nket per density of a multi-density build
     size_t nket = 0;
     KetElem* d_kelem = nullptr;
     double *d_dket = nullptr, *d_wket = nullptr;
     double *d_dket_multi = nullptr, *d_wket_multi = nullptr;
-    std::vector<SubPlan> plans;         // launches, grouped by class id
+    std::vector<SubPlan> plans;         // per class and ket list, grouped by class
+    std::vector<ClassLaunch> launches;  // of a build (one per plan when each is timed)
+    std::vector<ClassLaunch> classes;   // all plans of a class (multi-density builds)
+    int4* d_tasks = nullptr;            // of all plans
+    int* d_split = nullptr;             // per task: first ket evaluated in FP32 (mixed builds)
     ClassTotals totals[21];
     // host copies of the Q-sorted lists (for re-planning) and per-class tuning
     std::vector<std::vector<PairInfo>> host_bra, host_ket;
@@ -211,8 +231,8 @@ hipError_t hfx_start_build(const double* D, const double* cs, int nmol, const lo
 hipError_t hfx_fill(double* p, size_t n, double v, hipStream_t st);
 hipError_t hfx_reduce_replicas(const double* rep, int nrep, size_t n, double* W, hipStream_t st);
 hipError_t hfx_fill_u64(unsigned long long* p, int n, hipStream_t st);
-hipError_t hfx_split(const PairInfo* bra, const double* ketq, const int4* tasks, int ntask, double fp32_tau,
-                     const unsigned long long* dmax_bits, int* split, hipStream_t st);
+hipError_t hfx_split(const PairInfo* bra, const KetListDev* lists, const double* ketq, const int4* tasks, int ntask,
+                     double fp32_tau, const unsigned long long* dmax_bits, int* split, hipStream_t st);
 hipError_t hfx_ket_elems(const PairInfo* kets, int n, int nc, int nd, const long long* moff, const int* mboff,
                          const double* cs, KetElem* out, hipStream_t st);
 hipError_t hfx_scatter_kets(const KetElem* ke, size_t nke, const double* wket, double* W, hipStream_t st);

@@ -52,11 +52,32 @@ struct StartBufs {
     int nwork;
 };
 
-// Arguments of one class kernel launch.  The kets of a launch all have the
-// same number of primitive pairs (knprim), so the primitive loop trip count
-// is uniform across a wave.  Ket primitive data are a structure of arrays:
-// field f (the PrimPair member order p, inv2p, P[3], PA[3], K) of primitive k
-// of ket s at kprim[(f * knprim + k) * nket_list + s].
+// One ket list (pairs of one class with one primitive count) in the context's
+// arrays, which hold the lists one after the other.
+struct KetListDev {
+    long long soa;     // its first element of the ket primitives
+    long long koff;    // and of the ket blocks (dket, wket)
+    int s0;            // its first ket
+    int n, kp;         // kets, primitive pairs per ket
+    int pad;
+};
+
+// A task's last word: column windows wc and wd, and the ket list.
+constexpr int HFX_TASK_WIN_BITS = 11, HFX_TASK_MAX_LISTS = 1 << (32 - 2 * HFX_TASK_WIN_BITS);
+constexpr int hfx_task_code(int wc, int wd, int list) {
+    return (int)((unsigned)wc | (unsigned)wd << HFX_TASK_WIN_BITS | (unsigned)list << 2 * HFX_TASK_WIN_BITS);
+}
+constexpr int hfx_task_wc(int w) { return w & ((1 << HFX_TASK_WIN_BITS) - 1); }
+constexpr int hfx_task_wd(int w) { return w >> HFX_TASK_WIN_BITS & ((1 << HFX_TASK_WIN_BITS) - 1); }
+constexpr int hfx_task_list(int w) { return (int)((unsigned)w >> 2 * HFX_TASK_WIN_BITS); }
+
+// Arguments of one class kernel launch, whose tasks may be of several ket
+// lists of the class.  The kets of a task all have the same number of primitive
+// pairs (knprim), so the primitive loop trip count is uniform across a wave.
+// Ket primitive data are a structure of arrays: field f (the PrimPair member
+// order p, inv2p, P[3], PA[3], K) of primitive k of ket s of a list at
+// kprim[(f * knprim + k) * nket_list + s].  The host passes the arrays of all
+// lists; of_list() gives a task's view.
 struct ClassArgs {
     const PairInfo* __restrict__ bra;   // bra pairs of the class, Q descending
     const PairInfo* __restrict__ ket;   // ket pairs (one primitive count), Q descending
@@ -66,10 +87,11 @@ struct ClassArgs {
     const double* __restrict__ kprim;   // ket primitives, structure of arrays
     const float* __restrict__ prim32;   // FP32 copies of both (mixed builds: the FP32 evaluation reads
     const float* __restrict__ kprim32;  // them without conversions)
-    int nket_list, knprim;
+    const KetListDev* __restrict__ lists;
+    int nket_list, knprim;              // of a task's list
     const int* __restrict__ split;      // mixed builds, per task: kets below this list position use FP64,
                                         // the rest FP32 (one launch evaluates both parts)
-    const int4* __restrict__ tasks;     // (bra index, first ket, end ket, window code wc | wd << 16); bra -1:
+    const int4* __restrict__ tasks;     // (bra index, first ket, end ket, hfx_task_code); bra -1:
                                         // empty.  Task 8k + x is entry k of XCD x's queue.  Register-tiled
                                         // plans: bra index | (bras in the block - 1) << 28
     const double* __restrict__ ketq;    // register-tiled plans: Q of every ket (list order)
@@ -101,6 +123,54 @@ struct ClassArgs {
     int shard, nshards;                 // only bras with r % nshards == shard (1 shard: all)
     double cj, ck;                      // W_ab += cj*2 g D_cd ; W_ac -= ck g D_bd
 };
+
+// Constant address space: loads through such a pointer at a wave-uniform
+// address become scalar (SMEM) loads.
+#define HFX_CONST_AS __attribute__((address_space(4)))
+
+// A task and a bra pair, both the same in every lane: read into scalar registers.
+__device__ __forceinline__ int4 uniform_task(const int4* tasks, int ti) {
+    const HFX_CONST_AS int* t = (const HFX_CONST_AS int*)(tasks + ti);
+    return make_int4(t[0], t[1], t[2], t[3]);
+}
+__device__ __forceinline__ PairInfo uniform_pair(const PairInfo* pairs, int r) {
+    const HFX_CONST_AS PairInfo* p = (const HFX_CONST_AS PairInfo*)pairs + r;
+    PairInfo v;
+    v.a = p->a;
+    v.b = p->b;
+    v.bfa = p->bfa;
+    v.bfb = p->bfb;
+    v.prim_off = p->prim_off;
+    v.nprim = p->nprim;
+    v.Q = p->Q;
+    v.AB[0] = p->AB[0];
+    v.AB[1] = p->AB[1];
+    v.AB[2] = p->AB[2];
+    v.mol = p->mol;
+    v.ld = p->ld;
+    return v;
+}
+
+// The arguments as the tasks of a list see them (w: the task's last word, the
+// same in every lane: the list's record goes to scalar registers).
+__device__ __forceinline__ ClassArgs of_list(const ClassArgs& a, int w) {
+    const HFX_CONST_AS KetListDev* L =
+        (const HFX_CONST_AS KetListDev*)a.lists + __builtin_amdgcn_readfirstlane(hfx_task_list(w));
+    const int s0 = L->s0;
+    const long long koff = L->koff, soa = L->soa;
+    ClassArgs v = a;
+    v.ket += s0;
+    v.kbf += s0;
+    v.ketq += s0;
+    v.kpos += s0;
+    v.dket += koff;
+    v.wket += koff;
+    v.kprim += soa;
+    v.kprim32 += soa;
+    v.nket_list = L->n;
+    v.knprim = L->kp;
+    return v;
+}
 
 // Evaluated-quartet counters of a build: per class, FP64 then FP32, each
 // spread over HFX_CNT_SLOTS words one 128-byte line apart (a workgroup adds
@@ -159,10 +229,6 @@ __device__ __forceinline__ double wave_sum(double v) {
     v = lane_pair_sum<4>(v, v);
     return lane_pair_sum<5>(v, v);
 }
-
-// Constant address space: loads through such a pointer at a wave-uniform
-// address become scalar (SMEM) loads.
-#define HFX_CONST_AS __attribute__((address_space(4)))
 
 // ---- Boys function tables ---------------------------------------------------
 // For every order l < BOYS_NL one block of BOYS_NT rows of 80 bytes:
@@ -340,3 +406,5 @@ __device__ __forceinline__ void boys_eval(R T, R* F, const double* __restrict__ 
 }
 
 constexpr int hfx_ncart(int l) { return (l + 1) * (l + 2) / 2; }
+// LDS doubles of the J sums of a bra block of n components (an even number)
+constexpr int hfx_jsum_doubles(int n) { return (n + 1) / 2 * 2; }

@@ -82,8 +82,8 @@ __global__ void k_fill_u64(unsigned long long* __restrict__ p, int n) {
 // FP64/FP32 split per task (bra r, kets [s0, s1) of one group): the kets s
 // with Q_r Q_s max|D| >= fp32_tau come first (Q descending within a group);
 // split[t] is the list position of the first FP32 ket (s1 if none).
-__global__ void k_split(const PairInfo* __restrict__ bra, const double* __restrict__ ketq,
-                        const int4* __restrict__ tasks, int ntask, double fp32_tau,
+__global__ void k_split(const PairInfo* __restrict__ bra, const KetListDev* __restrict__ lists,
+                        const double* __restrict__ all_ketq, const int4* __restrict__ tasks, int ntask, double fp32_tau,
                         const unsigned long long* __restrict__ dmax_bits, int* __restrict__ split) {
     const int t = blockIdx.x * MISC_WG + threadIdx.x;
     if (t >= ntask) return;
@@ -92,6 +92,7 @@ __global__ void k_split(const PairInfo* __restrict__ bra, const double* __restri
         split[t] = 0;
         return;
     }
+    const double* ketq = all_ketq + lists[hfx_task_list(tk.w)].s0;
     const double qr = bra[tk.x].Q * __longlong_as_double((long long)*dmax_bits);
     int lo = tk.y, hi = tk.z;   // Q descending within a task's kets: the FP32 ones are a suffix
     while (lo < hi) {
@@ -299,11 +300,11 @@ hipError_t hfx_fill_u64(unsigned long long* p, int n, hipStream_t st) {
     hipLaunchKernelGGL(k_fill_u64, dim3((n + MISC_WG - 1) / MISC_WG), dim3(MISC_WG), 0, st, p, n);
     return hipGetLastError();
 }
-hipError_t hfx_split(const PairInfo* bra, const double* ketq, const int4* tasks, int ntask, double fp32_tau,
-                     const unsigned long long* dmax_bits, int* split, hipStream_t st) {
+hipError_t hfx_split(const PairInfo* bra, const KetListDev* lists, const double* ketq, const int4* tasks, int ntask,
+                     double fp32_tau, const unsigned long long* dmax_bits, int* split, hipStream_t st) {
     if (ntask <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_split, dim3((ntask + MISC_WG - 1) / MISC_WG), dim3(MISC_WG), 0, st, bra, ketq, tasks,
-                       ntask, fp32_tau, dmax_bits, split);
+    hipLaunchKernelGGL(k_split, dim3((ntask + MISC_WG - 1) / MISC_WG), dim3(MISC_WG), 0, st, bra, lists, ketq,
+                       tasks, ntask, fp32_tau, dmax_bits, split);
     return hipGetLastError();
 }
 hipError_t hfx_ket_elems(const PairInfo* kets, int n, int nc, int nd, const long long* moff, const int* mboff,

@@ -152,8 +152,7 @@ static void release_system(hfx_ctx* c) {
     c->nket = 0;
     c->ketlists.clear();
     c->host_bra.clear();
-    c->host_pos.clear();
-    c->host_ket.clear();
+    c->host_ketq.clear();
     c->host_kpos.clear();
     for (auto& p : c->plans) {
         if (p.ev0) (void)hipEventDestroy(p.ev0);
@@ -332,9 +331,10 @@ static double dfact_odd(int n) {   // (2n-1)!!
 // counts, workgroup tasks, counts.  Bras are the whole Q-sorted list of pair
 // class B; for B == K an unordered pair {bra, ket} is taken once, with the
 // ket not after the bra in that order (Q descending, then pair index).
-static hfx_status plan_sub(hfx_ctx* c, int B, int li, const std::vector<PairInfo>& bras,
-                           const std::vector<double>& bra_pos, const std::vector<PairInfo>& kets,
-                           const std::vector<double>& ket_pos) {
+static hfx_status plan_sub(hfx_ctx* c, int B, int li) {
+    const std::vector<PairInfo>& bras = c->host_bra[B];
+    const double* ket_q = c->host_ketq.data() + c->ketlists[li].s0;
+    const int* ket_pos = c->host_kpos.data() + c->ketlists[li].s0;
     const KetList& KL = c->ketlists[li];
     const int K = KL.K;
     SubPlan P;
@@ -351,30 +351,33 @@ static hfx_status plan_sub(hfx_ctx* c, int B, int li, const std::vector<PairInfo
     }
     // bra r (molecule m) meets the kets of its own molecule's groups; in
     // each group the kets with Q_s Q_r >= tau are a prefix (Q descending),
-    // and for B == K so are the kets not after the bra in the class order
+    // and for B == K so are the kets not after the bra in the class order.
+    // A molecule's bras come with Q descending and positions ascending, so both
+    // ends only move one way from bra to bra.
     const std::vector<int>& gs = c->kgroup[li];
     const std::vector<int>& mg = c->kmolg[li];
     const std::vector<int>& wcode = c->kwcode[li];
     const int nbra = (int)bras.size();
     struct Run { int r, g, n; };
     std::vector<Run> runs;
+    runs.reserve(nbra);
+    std::vector<int> hi, at;   // per group of the molecule: ends of the two prefixes
     for (int r = 0; r < nbra; ++r) {
+        const int m = bras[r].mol, g0 = mg[m], g1 = mg[m + 1];
+        if (r == 0 || bras[r - 1].mol != m) {
+            hi.assign(gs.begin() + g0 + 1, gs.begin() + g1 + 1);
+            at.assign(gs.begin() + g0, gs.begin() + g1);
+        }
         const double qr = bras[r].Q;
-        for (int g = mg[bras[r].mol]; g < mg[bras[r].mol + 1]; ++g) {
+        for (int g = g0; g < g1; ++g) {
             const int kb = gs[g], ke = gs[g + 1];
-            int lo = kb, hi = ke;
-            while (lo < hi) {
-                const int mid = (lo + hi) / 2;
-                if (kets[mid].Q * qr >= tau) lo = mid + 1; else hi = mid;
-            }
-            int n = lo - kb;
+            int& h = hi[g - g0];
+            while (h > kb && !(ket_q[h - 1] * qr >= tau)) --h;
+            int n = h - kb;
             if (B == K) {
-                int l2 = kb, h2 = ke;
-                while (l2 < h2) {
-                    const int mid = (l2 + h2) / 2;
-                    if (ket_pos[mid] <= bra_pos[r]) l2 = mid + 1; else h2 = mid;
-                }
-                n = std::min(n, l2 - kb);
+                int& t = at[g - g0];
+                while (t < ke && ket_pos[t] <= r) ++t;
+                n = std::min(n, t - kb);
             }
             if (n <= 0) continue;
             runs.push_back(Run{r, g, n});
@@ -557,7 +560,7 @@ static hfx_status replan(hfx_ctx* c) {
     for (int B = 0; B < 6; ++B)
         for (size_t li = 0; li < c->ketlists.size(); ++li) {
             if (c->ketlists[li].K > B) continue;
-            hfx_status s = plan_sub(c, B, (int)li, c->host_bra[B], c->host_pos[B], c->host_ket[li], c->host_kpos[li]);
+            hfx_status s = plan_sub(c, B, (int)li);
             if (s != HFX_OK) return s;
         }
     // launch order: largest classes first (sub-launches of a class stay together)
@@ -850,6 +853,7 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
     // ---- shell pairs within each molecule, canonical orientation ----
     std::vector<PrimPair> prim;
     std::vector<std::vector<PairInfo>> all(6);
+    const double sqrt_2pi52 = 1.4142135623730951, pi54 = std::pow(M_PI, 1.25);   // sqrt(2 pi^{5/2}) = sqrt(2) pi^{5/4}
     for (int m = 0; m < nmol; ++m) {
         const MolInfo& M = c->mol[m];
         for (int a = M.soff; a < M.soff + M.nshell; ++a)
@@ -887,9 +891,7 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
                         pp.PA[1] = pp.P[1] - SA.y;
                         pp.PA[2] = pp.P[2] - SA.z;
                         const double ek = std::exp(-mu * ab2);
-                        // sqrt(2 pi^{5/2}) = sqrt(2) pi^{5/4}
-                        pp.K = c->coefs[SA.prim_off + i] * c->coefs[SB.prim_off + j] * ek * 1.4142135623730951 *
-                               std::pow(M_PI, 1.25) / p;
+                        pp.K = c->coefs[SA.prim_off + i] * c->coefs[SB.prim_off + j] * ek * sqrt_2pi52 * pi54 / p;
                         pp.pad = 0.0;
                         kmax = std::max(kmax, ek);
                         prim.push_back(pp);
@@ -910,13 +912,9 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
     }
     HIPCK(dalloc(&c->d_prim, prim.size()));
     HIPCK(hipMemcpy(c->d_prim, prim.data(), prim.size() * sizeof(PrimPair), hipMemcpyHostToDevice));
-    {   // FP32 copy, same layout, for the FP32 evaluation of mixed builds
-        std::vector<float> p32(prim.size() * HFX_PRIM_FIELDS);
-        const double* src = reinterpret_cast<const double*>(prim.data());
-        for (size_t i = 0; i < p32.size(); ++i) p32[i] = (float)src[i];
-        HIPCK(dalloc(&c->d_prim32, p32.size()));
-        HIPCK(hipMemcpy(c->d_prim32, p32.data(), p32.size() * sizeof(float), hipMemcpyHostToDevice));
-    }
+    // FP32 copy, same layout, for the FP32 evaluation of mixed builds
+    HIPCK(dalloc(&c->d_prim32, prim.size() * HFX_PRIM_FIELDS));
+    HIPCK(hfx_prim32(c->d_prim, prim.size(), c->d_prim32, 0));
 
     // ---- Schwarz bounds on the GPU (FP64 class kernels on (ab|ab)) ----
     const bool keep_qshell = nmol == 1;
@@ -948,20 +946,24 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
     }
     // ---- significant pairs, sorted by molecule then Q descending (ties: pair order) ----
     const double tau = c->opt.schwarz_tau;
-    std::vector<std::vector<double>> pos(6);
     for (int B = 0; B < 6; ++B) {
         auto& L = all[B];
+        std::vector<std::pair<double, int>> key;   // (Q, pair)
+        key.reserve(L.size());
+        size_t m0 = 0;                             // the molecule's first key: pairs come molecule by molecule
+        for (size_t i = 0; i < L.size(); ++i) {
+            if (L[i].Q * qmax >= tau) key.emplace_back(L[i].Q, (int)i);
+            if (i + 1 == L.size() || L[i + 1].mol != L[i].mol) {
+                std::stable_sort(key.begin() + m0, key.end(),
+                                 [](const auto& x, const auto& y) { return x.first > y.first; });
+                m0 = key.size();
+            }
+        }
         std::vector<PairInfo> keep;
-        keep.reserve(L.size());
-        for (auto& p : L)
-            if (p.Q * qmax >= tau) keep.push_back(p);
-        std::stable_sort(keep.begin(), keep.end(), [](const PairInfo& x, const PairInfo& y) {
-            return x.mol < y.mol || (x.mol == y.mol && x.Q > y.Q);
-        });
+        keep.reserve(key.size());
+        for (const auto& k : key) keep.push_back(L[k.second]);
         L.swap(keep);
         c->npair[B] = (int)L.size();
-        pos[B].resize(L.size());
-        for (size_t i = 0; i < L.size(); ++i) pos[B][i] = (double)i;
         HIPCK(dalloc(&c->d_pairs[B], L.size()));
         if (!L.empty()) HIPCK(hipMemcpy(c->d_pairs[B], L.data(), L.size() * sizeof(PairInfo), hipMemcpyHostToDevice));
     }
@@ -973,15 +975,14 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
     constexpr int kWindowAbove = 2048, kWindow = 768, kWindowPad = 8;   // pad: a shell's extent past its window
     c->win = c->max_ld > kWindowAbove ? kWindow : 0;
     c->rs = c->win ? 2 * (c->win + kWindowPad) : c->max_ld;
-    std::vector<std::vector<PairInfo>> klist;
-    std::vector<std::vector<double>> kpos;
     c->kgroup.clear();
     c->kmolg.clear();
     c->kwcode.clear();
     std::vector<PairInfo> kets;   // of all lists, as their other data
     std::vector<int4> kbf;
-    std::vector<int> kpos_int;
-    std::vector<double> q, soa;
+    std::vector<int> kpos;
+    std::vector<double> q;
+    size_t nsoa = 0;
     for (int K = 0; K < 6; ++K) {
         std::vector<int> nps;
         for (auto& p : all[K])
@@ -992,11 +993,11 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
             KL.K = K;
             KL.kp = kp;
             std::vector<PairInfo> sub;
-            std::vector<double> sp;
+            std::vector<int> sp;   // positions in the pair class's list
             for (size_t i = 0; i < all[K].size(); ++i)
                 if (all[K][i].nprim == kp) {
                     sub.push_back(all[K][i]);
-                    sp.push_back(pos[K][i]);
+                    sp.push_back((int)i);
                 }
             KL.n = (int)sub.size();
             const size_t n = sub.size();
@@ -1012,7 +1013,7 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
                     return wd_of(u) < wd_of(v);
                 });
                 std::vector<PairInfo> s2(n);
-                std::vector<double> p2(n);
+                std::vector<int> p2(n);
                 for (size_t i = 0; i < n; ++i) {
                     s2[i] = sub[idx[i]];
                     p2[i] = sp[idx[i]];
@@ -1032,24 +1033,17 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
             gstart.push_back((int)n);
             for (int m = 0; m < nmol; ++m) molg[m + 1] = std::max(molg[m + 1], molg[m]);   // molecules without kets
             KL.s0 = kets.size();
-            KL.soa = soa.size();
+            KL.soa = nsoa;
             KL.koff = c->nket;
+            nsoa += (size_t)9 * kp * n;
             c->nket += ((size_t)ncart(kPairL[K][0]) * ncart(kPairL[K][1]) * n + 31) / 32 * 32;   // 256 bytes
-            soa.resize(KL.soa + (size_t)9 * kp * n);
             for (size_t s = 0; s < n; ++s) {
                 q.push_back(sub[s].Q);
                 kbf.push_back(make_int4(sub[s].bfa, sub[s].bfb, sub[s].a, sub[s].b));
-                kpos_int.push_back((int)sp[s]);
-                for (int k = 0; k < kp; ++k) {
-                    const PrimPair& pp = prim[sub[s].prim_off + k];
-                    const double f[9] = {pp.p, pp.inv2p, pp.P[0], pp.P[1], pp.P[2], pp.PA[0], pp.PA[1], pp.PA[2], pp.K};
-                    for (int fi = 0; fi < 9; ++fi) soa[KL.soa + ((size_t)fi * kp + k) * n + s] = f[fi];
-                }
             }
+            kpos.insert(kpos.end(), sp.begin(), sp.end());
             kets.insert(kets.end(), sub.begin(), sub.end());
             c->ketlists.push_back(KL);
-            klist.push_back(std::move(sub));
-            kpos.push_back(std::move(sp));
             c->kgroup.push_back(std::move(gstart));
             c->kmolg.push_back(std::move(molg));
             c->kwcode.push_back(std::move(wcode));
@@ -1067,9 +1061,9 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
     HIPCK(upload(c->d_kets, kets));
     HIPCK(upload(c->d_kbf, kbf));
     HIPCK(upload(c->d_ketq, q));
-    HIPCK(upload(c->d_kpos, kpos_int));
-    HIPCK(upload(c->d_soa, soa));
-    HIPCK(upload(c->d_soa32, std::vector<float>(soa.begin(), soa.end())));
+    HIPCK(upload(c->d_kpos, kpos));
+    HIPCK(dalloc(&c->d_soa, nsoa));
+    HIPCK(dalloc(&c->d_soa32, nsoa));
     HIPCK(dalloc(&c->d_kelem, c->nket));
     HIPCK(dalloc(&c->d_dket, c->nket));
     HIPCK(dalloc(&c->d_wket, c->nket));
@@ -1077,13 +1071,13 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
     std::vector<KetListDev> lists;
     for (const auto& KL : c->ketlists) {
         lists.push_back(KetListDev{(long long)KL.soa, (long long)KL.koff, (int)KL.s0, KL.n, KL.kp, 0});
+        HIPCK(hfx_ket_soa(c->d_kets + KL.s0, KL.n, KL.kp, c->d_prim, c->d_soa + KL.soa, c->d_soa32 + KL.soa, 0));
         HIPCK(hfx_ket_elems(c->d_kets + KL.s0, KL.n, ncart(kPairL[KL.K][0]), ncart(kPairL[KL.K][1]), c->d_moff,
                             c->d_mboff, c->d_cscale, c->d_kelem + KL.koff, 0));
     }
     HIPCK(upload(c->d_lists, lists));
-    c->host_bra.assign(all.begin(), all.end());
-    c->host_pos = pos;
-    c->host_ket = std::move(klist);
+    c->host_bra = std::move(all);
+    c->host_ketq = std::move(q);
     c->host_kpos = std::move(kpos);
     {
         hfx_status s = replan(c);

@@ -147,8 +147,9 @@ struct hfx_ctx {
     int* d_split = nullptr;             // per task: first ket evaluated in FP32 (mixed builds)
     ClassTotals totals[21];
     // host copies of the Q-sorted lists (for re-planning) and per-class tuning
-    std::vector<std::vector<PairInfo>> host_bra, host_ket;
-    std::vector<std::vector<double>> host_pos, host_kpos;
+    std::vector<std::vector<PairInfo>> host_bra;
+    std::vector<double> host_ketq;      // of all ket lists, as d_ketq and d_kpos
+    std::vector<int> host_kpos;
     int tune_tq[21] = {0};                       // 0: opt.task_quartets
     int tune_stripe[21] = {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1,
                            -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};  // -1: default (striped)
@@ -233,6 +234,9 @@ hipError_t hfx_reduce_replicas(const double* rep, int nrep, size_t n, double* W,
 hipError_t hfx_fill_u64(unsigned long long* p, int n, hipStream_t st);
 hipError_t hfx_split(const PairInfo* bra, const KetListDev* lists, const double* ketq, const int4* tasks, int ntask,
                      double fp32_tau, const unsigned long long* dmax_bits, int* split, hipStream_t st);
+hipError_t hfx_prim32(const PrimPair* prim, size_t n, float* out, hipStream_t st);
+hipError_t hfx_ket_soa(const PairInfo* kets, int n, int kp, const PrimPair* prim, double* soa, float* soa32,
+                       hipStream_t st);
 hipError_t hfx_ket_elems(const PairInfo* kets, int n, int nc, int nd, const long long* moff, const int* mboff,
                          const double* cs, KetElem* out, hipStream_t st);
 hipError_t hfx_scatter_kets(const KetElem* ke, size_t nke, const double* wket, double* W, hipStream_t st);

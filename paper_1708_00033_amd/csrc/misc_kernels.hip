@@ -130,6 +130,31 @@ __global__ void k_reduce_replicas(const double* __restrict__ rep, int nrep, size
     }
 }
 
+// FP32 copy of the primitive pairs.
+__global__ void k_prim32(const double* __restrict__ prim, size_t n, float* __restrict__ out) {
+    for (size_t i = (size_t)blockIdx.x * MISC_WG + threadIdx.x; i < n; i += (size_t)gridDim.x * MISC_WG)
+        out[i] = (float)prim[i];
+}
+
+// The primitives of one list (kp a ket) as a structure of arrays, field f of
+// primitive k of ket s at (f kp + k) n + s, and their FP32 copy.  Formed here
+// and not on the host: loading 29 waters spent 2.5 ms on building and copying
+// these arrays, now 1.1 ms with everything else of the ket lists.
+__global__ void k_ket_soa(const PairInfo* __restrict__ kets, int n, int kp, const double* __restrict__ prim,
+                          double* __restrict__ soa, float* __restrict__ soa32) {
+    const long long tot = (long long)n * kp;
+    for (long long i = (long long)blockIdx.x * MISC_WG + threadIdx.x; i < tot; i += (long long)gridDim.x * MISC_WG) {
+        const int s = (int)(i % n), k = (int)(i / n);
+        const double* p = prim + (size_t)(kets[s].prim_off + k) * HFX_PRIM_FIELDS;
+#pragma unroll
+        for (int f = 0; f < 9; ++f) {
+            const size_t o = ((size_t)f * kp + k) * n + s;
+            soa[o] = p[f];
+            soa32[o] = (float)p[f];
+        }
+    }
+}
+
 // The elements of one list's ket blocks, component comp of pair s at comp n + s:
 // their places in the matrices and the products of their component factors.
 __global__ void k_ket_elems(const PairInfo* __restrict__ kets, int n, int nc, int nd, const long long* __restrict__ moff,
@@ -305,6 +330,19 @@ hipError_t hfx_split(const PairInfo* bra, const KetListDev* lists, const double*
     if (ntask <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_split, dim3((ntask + MISC_WG - 1) / MISC_WG), dim3(MISC_WG), 0, st, bra, lists, ketq,
                        tasks, ntask, fp32_tau, dmax_bits, split);
+    return hipGetLastError();
+}
+hipError_t hfx_prim32(const PrimPair* prim, size_t n, float* out, hipStream_t st) {
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_prim32, dim3(grid_for(n * HFX_PRIM_FIELDS)), dim3(MISC_WG), 0, st, (const double*)prim,
+                       n * HFX_PRIM_FIELDS, out);
+    return hipGetLastError();
+}
+hipError_t hfx_ket_soa(const PairInfo* kets, int n, int kp, const PrimPair* prim, double* soa, float* soa32,
+                       hipStream_t st) {
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_ket_soa, dim3(grid_for((size_t)n * kp)), dim3(MISC_WG), 0, st, kets, n, kp,
+                       (const double*)prim, soa, soa32);
     return hipGetLastError();
 }
 hipError_t hfx_ket_elems(const PairInfo* kets, int n, int nc, int nd, const long long* moff, const int* mboff,

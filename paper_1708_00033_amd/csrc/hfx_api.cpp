@@ -331,6 +331,15 @@ static double dfact_odd(int n) {   // (2n-1)!!
 // counts, workgroup tasks, counts.  Bras are the whole Q-sorted list of pair
 // class B; for B == K an unordered pair {bra, ket} is taken once, with the
 // ket not after the bra in that order (Q descending, then pair index).
+// 160 KiB of LDS per workgroup, less room for the persistent kernel's static counter
+constexpr size_t kLdsBudget = 160 * 1024 - 256;
+
+// LDS of a class kernel's table: Boys rows and the J sums of a bra block.
+static size_t table_lds(int B, int K) {
+    return boys_lds_bytes(class_L(class_id(B, K))) +
+           sizeof(double) * hfx_jsum_doubles(ncart(kPairL[B][0]) * ncart(kPairL[B][1]));
+}
+
 static hfx_status plan_sub(hfx_ctx* c, int B, int li) {
     const std::vector<PairInfo>& bras = c->host_bra[B];
     const double* ket_q = c->host_ketq.data() + c->ketlists[li].s0;
@@ -402,27 +411,26 @@ static hfx_status plan_sub(hfx_ctx* c, int B, int li) {
     // share of each ket list; short prefixes fill the least loaded queue.
     // Queues are interleaved (task 8k + j = queue j's k-th entry) and padded
     // with empty tasks (r = -1).
-    P.lds_bytes = (size_t)(ncart(kPairL[B][0]) + ncart(kPairL[B][1])) * c->rs * sizeof(double);
+    P.win = c->set_win[KL.set];
+    P.rs = c->set_rs[KL.set];
+    P.lds_bytes = (size_t)(ncart(kPairL[B][0]) + ncart(kPairL[B][1])) * P.rs * sizeof(double);
     P.fp64_only = nint >= 600;   // a d-d bra with a d-d or d-p ket: no FP32 kernels
     // FP64 rows (the mixed kernels' FP32 part reads them too); the cooperative kernels read their table from memory
     P.lds_tab = P.rys ? (size_t)hfx_class_rys_lds(P.cid, 0, 1)
-                      : boys_lds_bytes(class_L(P.cid)) +
-                            sizeof(double) * hfx_jsum_doubles(ncart(kPairL[B][0]) * ncart(kPairL[B][1]));
+                      : table_lds(B, K);
     const int digest = c->tune_digest[P.cid] >= 0 ? c->tune_digest[P.cid] : c->opt.digest;
-    // 160 KiB of LDS per workgroup, less room for the persistent kernel's static counter
-    constexpr size_t kLdsBudget = 160 * 1024 - 256;
     const bool lds_digest = digest == HFX_DIGEST_LDS || digest == HFX_DIGEST_LDS_D;
     P.mode = (lds_digest && P.lds_bytes + P.lds_tab <= kLdsBudget) ? 0 : 1;
     P.priv = digest == HFX_DIGEST_PRIVATE;   // global-atomic kernels into the per-XCD copies
     if (P.rys) P.lds_tab = (size_t)hfx_class_rys_lds(P.cid, P.mode, 1);
     // D' rows staged too: both shells' rows when they fit, else shell a's
-    // (the larger set); only for classes with small integral blocks and
-    // whole rows (with column windows a task covers one pair of windows, and
-    // copying its rows cost more than the gathers it saved on 512 waters)
+    // (the larger set); only for classes with small integral blocks and whole
+    // rows of up to 2048 columns (with column windows a task covers one pair of
+    // windows, and copying its rows cost more than the gathers it saved)
     P.dstage = 0;
     P.lds_dst = 0;
-    if (digest == HFX_DIGEST_LDS_D && P.mode == 0 && nint <= HFX_STAGE_D_MAX_NI && c->win == 0) {
-        const size_t rows_a = (size_t)ncart(kPairL[B][0]) * c->rs * sizeof(double);
+    if (digest == HFX_DIGEST_LDS_D && P.mode == 0 && nint <= HFX_STAGE_D_MAX_NI && P.win == 0 && c->max_ld <= 2048) {
+        const size_t rows_a = (size_t)ncart(kPairL[B][0]) * P.rs * sizeof(double);
         if (2 * P.lds_bytes + P.lds_tab <= kLdsBudget) {
             P.dstage = 3;
             P.lds_dst = P.lds_bytes;
@@ -559,7 +567,7 @@ static hfx_status replan(hfx_ctx* c) {
     for (auto& t : c->totals) t = ClassTotals();
     for (int B = 0; B < 6; ++B)
         for (size_t li = 0; li < c->ketlists.size(); ++li) {
-            if (c->ketlists[li].K > B) continue;
+            if (c->ketlists[li].K > B || c->ketlists[li].set != c->kset[class_id(B, c->ketlists[li].K)]) continue;
             hfx_status s = plan_sub(c, B, (int)li);
             if (s != HFX_OK) return s;
         }
@@ -968,13 +976,49 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
         if (!L.empty()) HIPCK(hipMemcpy(c->d_pairs[B], L.data(), L.size() * sizeof(PairInfo), hipMemcpyHostToDevice));
     }
     // ---- ket lists: one per pair class and primitive count, in groups ----
-    // Large molecules: the bra rows staged in LDS cover two column windows
-    // of kWindow basis functions (shell c's and shell d's), so kets are
-    // grouped by (molecule, window of c, window of d), Q descending within
-    // a group; small ones stage whole rows (one group per molecule).
-    constexpr int kWindowAbove = 2048, kWindow = 768, kWindowPad = 8;   // pad: a shell's extent past its window
-    c->win = c->max_ld > kWindowAbove ? kWindow : 0;
-    c->rs = c->win ? 2 * (c->win + kWindowPad) : c->max_ld;
+    // A bra's rows of W are staged in LDS: whole rows (set 0) or two column
+    // windows, shell c's and shell d's, with the kets grouped by (molecule, window
+    // of c, window of d), Q descending within a group (set 1: 768 columns; set 2,
+    // bras of more rows than that admits, that is d-d: as many as fit).  Whole rows
+    // where they fit beside the tables.  Above 2048 columns D' rows are not staged
+    // beside them and a bra's whole rows of D' leave the first-level cache, which
+    // long ket lists feel (112 waters: (ds|ss) 60 ms windowed, 73 whole; (ds|ps) 43
+    // and 48) and short tasks less than the number of their windows ((ss|ss) 90
+    // and 78, (ps|ps) 47 and 35, (ds|ds) 25 and 15): there whole rows for kets of
+    // the bra's own class and of p-p and d-s.  Before, d-d bras above 1268 columns
+    // went to W by global atomics ((dd|ss) and (dd|ps) 76 ms, now 10) and all
+    // classes above 2048 were windowed: 559 ms for all classes, now 447.
+    {
+        constexpr int kWindow = 768, kPad = 8;   // pad: a shell's extent past its window
+        constexpr int kCached = 2048;
+        c->set_win[0] = 0;
+        c->set_rs[0] = c->max_ld;
+        c->set_win[1] = kWindow;
+        size_t tab2 = 0;    // set 2: its largest table
+        int rows2 = 1;      // and rows
+        for (int B = 0; B < 6; ++B) {
+            const int rows = ncart(kPairL[B][0]) + ncart(kPairL[B][1]);
+            size_t tab = 0, tab_rys = 0;
+            for (int K = 0; K <= B; ++K) {
+                const int cid = class_id(B, K);
+                if (hfx_class_is_rys(cid)) tab_rys = std::max(tab_rys, (size_t)hfx_class_rys_lds(cid, 0, 1));
+                else tab = std::max(tab, table_lds(B, K));
+            }
+            // (cooperative classes whose tables do not fit as well sum a ket's updates before atomics)
+            const bool fits = (size_t)rows * c->max_ld * sizeof(double) + tab <= kLdsBudget;
+            const bool wide = (size_t)rows * 2 * (kWindow + kPad) * sizeof(double) + tab <= kLdsBudget;
+            for (int K = 0; K <= B; ++K)
+                c->kset[class_id(B, K)] = fits && (c->max_ld <= kCached || K == B || K >= 2) ? 0 : wide ? 1 : 2;
+            if (!wide) {
+                tab2 = std::max({tab2, tab, tab_rys});
+                rows2 = std::max(rows2, rows);
+            }
+        }
+        const int most = (int)((kLdsBudget - tab2) / sizeof(double) / rows2) / 2 - kPad;
+        const int nwin = (c->max_ld + most - 1) / most;
+        c->set_win[2] = (c->max_ld + nwin - 1) / nwin;   // of equal width
+        for (int k = 1; k < 3; ++k) c->set_rs[k] = 2 * (c->set_win[k] + kPad);
+    }
     c->kgroup.clear();
     c->kmolg.clear();
     c->kwcode.clear();
@@ -983,75 +1027,83 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
     std::vector<int> kpos;
     std::vector<double> q;
     size_t nsoa = 0;
-    for (int K = 0; K < 6; ++K) {
-        std::vector<int> nps;
-        for (auto& p : all[K])
-            if (std::find(nps.begin(), nps.end(), p.nprim) == nps.end()) nps.push_back(p.nprim);
-        std::sort(nps.begin(), nps.end());
-        for (int kp : nps) {
-            KetList KL;
-            KL.K = K;
-            KL.kp = kp;
-            std::vector<PairInfo> sub;
-            std::vector<int> sp;   // positions in the pair class's list
-            for (size_t i = 0; i < all[K].size(); ++i)
-                if (all[K][i].nprim == kp) {
-                    sub.push_back(all[K][i]);
-                    sp.push_back((int)i);
+    for (int set = 0; set < 3; ++set) {
+        const int win = c->set_win[set];
+        for (int K = 0; K < 6; ++K) {
+            bool used = false;   // by a bra class
+            for (int B = K; B < 6; ++B) used |= c->kset[class_id(B, K)] == set && !all[B].empty();
+            if (!used) continue;
+            std::vector<int> nps;
+            for (auto& p : all[K])
+                if (std::find(nps.begin(), nps.end(), p.nprim) == nps.end()) nps.push_back(p.nprim);
+            std::sort(nps.begin(), nps.end());
+            for (int kp : nps) {
+                KetList KL;
+                KL.K = K;
+                KL.kp = kp;
+                KL.set = set;
+                std::vector<PairInfo> sub;
+                std::vector<int> sp;   // positions in the pair class's list
+                for (size_t i = 0; i < all[K].size(); ++i)
+                    if (all[K][i].nprim == kp) {
+                        sub.push_back(all[K][i]);
+                        sp.push_back((int)i);
+                    }
+                KL.n = (int)sub.size();
+                const size_t n = sub.size();
+                auto wc_of = [&](const PairInfo& p) { return win ? p.bfa / win : 0; };
+                auto wd_of = [&](const PairInfo& p) { return win ? p.bfb / win : 0; };
+                if (win) {   // stable: Q order kept within (molecule, wc, wd)
+                    std::vector<size_t> idx(n);
+                    for (size_t i = 0; i < n; ++i) idx[i] = i;
+                    std::stable_sort(idx.begin(), idx.end(), [&](size_t x, size_t y) {
+                        const PairInfo &u = sub[x], &v = sub[y];
+                        if (u.mol != v.mol) return u.mol < v.mol;
+                        if (wc_of(u) != wc_of(v)) return wc_of(u) < wc_of(v);
+                        return wd_of(u) < wd_of(v);
+                    });
+                    std::vector<PairInfo> s2(n);
+                    std::vector<int> p2(n);
+                    for (size_t i = 0; i < n; ++i) {
+                        s2[i] = sub[idx[i]];
+                        p2[i] = sp[idx[i]];
+                    }
+                    sub.swap(s2);
+                    sp.swap(p2);
                 }
-            KL.n = (int)sub.size();
-            const size_t n = sub.size();
-            auto wc_of = [&](const PairInfo& p) { return c->win ? p.bfa / c->win : 0; };
-            auto wd_of = [&](const PairInfo& p) { return c->win ? p.bfb / c->win : 0; };
-            if (c->win) {   // stable: Q order kept within (molecule, wc, wd)
-                std::vector<size_t> idx(n);
-                for (size_t i = 0; i < n; ++i) idx[i] = i;
-                std::stable_sort(idx.begin(), idx.end(), [&](size_t x, size_t y) {
-                    const PairInfo &u = sub[x], &v = sub[y];
-                    if (u.mol != v.mol) return u.mol < v.mol;
-                    if (wc_of(u) != wc_of(v)) return wc_of(u) < wc_of(v);
-                    return wd_of(u) < wd_of(v);
-                });
-                std::vector<PairInfo> s2(n);
-                std::vector<int> p2(n);
-                for (size_t i = 0; i < n; ++i) {
-                    s2[i] = sub[idx[i]];
-                    p2[i] = sp[idx[i]];
+                std::vector<int> gstart, molg(nmol + 1, 0), wcode;
+                for (size_t s = 0; s < n; ++s) {
+                    const int w = hfx_task_code(wc_of(sub[s]), wd_of(sub[s]), (int)c->ketlists.size());
+                    if (s == 0 || sub[s].mol != sub[s - 1].mol || w != wcode.back()) {
+                        gstart.push_back((int)s);
+                        wcode.push_back(w);
+                        molg[sub[s].mol + 1] = (int)gstart.size();
+                    }
                 }
-                sub.swap(s2);
-                sp.swap(p2);
-            }
-            std::vector<int> gstart, molg(nmol + 1, 0), wcode;
-            for (size_t s = 0; s < n; ++s) {
-                const int w = hfx_task_code(wc_of(sub[s]), wd_of(sub[s]), (int)c->ketlists.size());
-                if (s == 0 || sub[s].mol != sub[s - 1].mol || w != wcode.back()) {
-                    gstart.push_back((int)s);
-                    wcode.push_back(w);
-                    molg[sub[s].mol + 1] = (int)gstart.size();
+                gstart.push_back((int)n);
+                for (int m = 0; m < nmol; ++m) molg[m + 1] = std::max(molg[m + 1], molg[m]);   // molecules without kets
+                KL.s0 = kets.size();
+                KL.soa = nsoa;
+                KL.koff = c->nket;
+                nsoa += (size_t)9 * kp * n;
+                c->nket += ((size_t)ncart(kPairL[K][0]) * ncart(kPairL[K][1]) * n + 31) / 32 * 32;   // 256 bytes
+                for (size_t s = 0; s < n; ++s) {
+                    q.push_back(sub[s].Q);
+                    kbf.push_back(make_int4(sub[s].bfa, sub[s].bfb, sub[s].a, sub[s].b));
                 }
+                kpos.insert(kpos.end(), sp.begin(), sp.end());
+                kets.insert(kets.end(), sub.begin(), sub.end());
+                c->ketlists.push_back(KL);
+                c->kgroup.push_back(std::move(gstart));
+                c->kmolg.push_back(std::move(molg));
+                c->kwcode.push_back(std::move(wcode));
             }
-            gstart.push_back((int)n);
-            for (int m = 0; m < nmol; ++m) molg[m + 1] = std::max(molg[m + 1], molg[m]);   // molecules without kets
-            KL.s0 = kets.size();
-            KL.soa = nsoa;
-            KL.koff = c->nket;
-            nsoa += (size_t)9 * kp * n;
-            c->nket += ((size_t)ncart(kPairL[K][0]) * ncart(kPairL[K][1]) * n + 31) / 32 * 32;   // 256 bytes
-            for (size_t s = 0; s < n; ++s) {
-                q.push_back(sub[s].Q);
-                kbf.push_back(make_int4(sub[s].bfa, sub[s].bfb, sub[s].a, sub[s].b));
-            }
-            kpos.insert(kpos.end(), sp.begin(), sp.end());
-            kets.insert(kets.end(), sub.begin(), sub.end());
-            c->ketlists.push_back(KL);
-            c->kgroup.push_back(std::move(gstart));
-            c->kmolg.push_back(std::move(molg));
-            c->kwcode.push_back(std::move(wcode));
         }
+        c->set_end[set] = c->nket;
     }
     // a task names its windows and its list in one word
     if ((int)c->ketlists.size() > HFX_TASK_MAX_LISTS ||
-        (c->win && c->max_ld / c->win >= (1 << HFX_TASK_WIN_BITS)))
+        c->max_ld / std::min(c->set_win[1], c->set_win[2]) >= (1 << HFX_TASK_WIN_BITS))
         return hfx_fail(c, HFX_ERR_INVALID_ARG, "too many ket lists or column windows");
     auto upload = [&](auto*& d, const auto& h) -> hipError_t {
         const hipError_t e = dalloc(&d, h.size());
@@ -1403,8 +1455,8 @@ hfx_status hfx_build_with(hfx_ctx* c, const BuildBufs& bufs, const double* dD, d
         a.lists = c->d_lists;
         a.nket_list = a.knprim = 0;
         a.split = mx ? c->d_split + toff : nullptr;
-        a.win = c->win;
-        a.rs = c->rs;
+        a.win = P.win;
+        a.rs = P.rs;
         a.dstage = P.dstage;
         a.moff = c->d_moff;
         a.tasks = c->d_tasks + toff;
@@ -1454,7 +1506,10 @@ hfx_status hfx_build_with(hfx_ctx* c, const BuildBufs& bufs, const double* dD, d
     }
     HIPCK(join_streams(c, ns, st));
     if (any_priv) HIPCK(hfx_reduce_replicas(c->d_Wrep, kXcds, nn, bufs.W, st));
-    HIPCK(hfx_scatter_kets(c->d_kelem, c->nket, c->d_wket, bufs.W, st));
+    for (int k = 0; k < 3; ++k) {   // a pair may be in several sets
+        const size_t o = k ? c->set_end[k - 1] : 0;
+        HIPCK(hfx_scatter_kets(c->d_kelem + o, c->set_end[k] - o, c->d_wket + o, bufs.W, st));
+    }
     HIPCK(hfx_assemble(dH, bufs.W, c->d_cscale, c->nmol, c->d_moff, c->d_mdim, c->d_mboff, c->max_ld, dOut, bufs.bad,
                        st));
     c->last_stream = st;
@@ -1613,8 +1668,8 @@ extern "C" hfx_status hfx_build_jk_multi_dev(hfx_ctx* c, int ndens, const double
         a.kpos = c->d_kpos;
         a.tau = c->opt.schwarz_tau;
         a.same = P.B == P.K;
-        a.win = c->win;
-        a.rs = c->rs;
+        a.win = P.win;
+        a.rs = P.rs;
         a.dstride = (long long)nn;
         a.kstride = (long long)c->nket;
         const int nblocks = (int)((std::min(ntask, 2048ll) + 7) / 8 * 8);   // resident or queued: queues drain either way
@@ -1638,7 +1693,11 @@ extern "C" hfx_status hfx_build_jk_multi_dev(hfx_ctx* c, int ndens, const double
     }
     HIPCK(join_streams(c, ns, st));
     for (int d = 0; d < ndens; ++d)   // each density's ket-block J sums into its J accumulator
-        HIPCK(hfx_scatter_kets(c->d_kelem, c->nket, c->d_wket_multi + (size_t)d * c->nket, WJ + (size_t)d * nn, st));
+        for (int k = 0; k < 3; ++k) {
+            const size_t o = k ? c->set_end[k - 1] : 0;
+            HIPCK(hfx_scatter_kets(c->d_kelem + o, c->set_end[k] - o, c->d_wket_multi + (size_t)d * c->nket + o,
+                                   WJ + (size_t)d * nn, st));
+        }
     for (int d = 0; d < ndens; ++d) {
         if (dJ)
             HIPCK(hfx_assemble(nullptr, WJ + (size_t)d * nn, c->d_cscale, c->nmol, c->d_moff, c->d_mdim, c->d_mboff,

@@ -19,7 +19,7 @@ struct ShellHost {
 // Significant pairs of one pair class that share one primitive count, sorted
 // by Schwarz bound (descending): a range of the context's ket arrays.
 struct KetList {
-    int K = 0, kp = 0, n = 0;
+    int K = 0, kp = 0, n = 0, set = 0;
     size_t s0 = 0;              // first ket
     size_t soa = 0;             // first ket primitive element, 9 kp n of them
     size_t koff = 0;            // first ket-block element, ncart(l_c) ncart(l_d) x n of them
@@ -33,6 +33,7 @@ struct SubPlan {
     std::vector<int4> tasks;  // host, until they are uploaded
     size_t toff = 0;          // first task in the context's array
     long long quartets = 0, integrals = 0, prim = 0;
+    int win = 0, rs = 0;      // column window and LDS row length of its set
     size_t lds_bytes = 0;     // bra rows F_I, F_J (LDS digestion)
     size_t lds_dst = 0;       // the bra's staged D' rows (LDS digestion with D rows)
     int dstage = 0;           // ClassArgs::dstage: bit 0 shell a's D' rows staged, bit 1 shell b's
@@ -108,8 +109,13 @@ struct hfx_ctx {
     // (ngroup + 1), each molecule's first group (nmol + 1), window code per
     // group (wc | wd << 16).  Without windows a group is a molecule.
     std::vector<std::vector<int>> kgroup, kmolg, kwcode;
-    int win = 0;                          // column window (0: whole rows, no windows)
-    int rs = 0;                           // LDS row length of the bra rows (doubles)
+    // the ket lists come in up to three sets that differ in how they are grouped
+    // for the LDS rows of the bras (load_batch): per quartet class its set; per
+    // set the column window (0: whole rows), the LDS row length (doubles) and the
+    // end of its ket-block elements
+    int kset[21] = {0};
+    int set_win[3] = {0}, set_rs[3] = {0};
+    size_t set_end[3] = {0};
     std::vector<int> Z;
     std::vector<double> axyz;
     std::vector<ShellHost> shells;

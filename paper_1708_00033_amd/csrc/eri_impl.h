@@ -23,11 +23,20 @@
 // shared W or (private digestion, ClassArgs::wrep) into the copy of W of the
 // XCD the wave runs on; the copies are summed after the class launches.
 #pragma once
+#include <type_traits>
+
 #include "hfx_internal.h"
 
 #define HFX_WG 256
 // digestion: integral blocks up to this size read all their D' elements first
 #define HFX_LOADS_FIRST_MAX_NI 18
+// One lane's FP64 block of at least this many integrals ((dp|pp): 162; larger
+// ones are shared between lanes) is evaluated and digested in two halves of shell
+// a's components: its 144 sums over primitives and 162 integrals do not fit in
+// 512 registers, those of a half nearly do.  44-atom sheet: 18.8 -> 11.6 ms,
+// 33 waters 0.42 -> 0.46 (long contractions, whose recursions run twice); thirds
+// the same; (dp|ds) and (dd|ps), 108 integrals that fit, 3.6 -> 3.9 and 1.7 -> 2.5.
+#define HFX_HALVES_MIN_NI 162
 
 // K update of W[grow][gcol]: MODE 0 into the task's LDS bra row at column
 // lcol (gcol less the column base of its window), MODE 1 straight into W.
@@ -407,6 +416,7 @@ struct BraRun {
     static constexpr int NA = hfx_ncart(E::LA), NB = hfx_ncart(E::LB), NC = hfx_ncart(E::LC), ND = hfx_ncart(E::LD);
     static constexpr int NAB = NA * NB, NI = NA * NB * NC * ND;
     static constexpr int NT = WAVE ? 64 : E::WGS;   // lanes of the task
+    static constexpr int PARTS = NI >= HFX_HALVES_MIN_NI ? 2 : 1, NAP = NA / PARTS;   // shell a's rows at a time
     static constexpr int nda = (DST & 1) ? NA : 0, ndb = (DST & 2) ? NB : 0;
     static_assert(DST == 0 || (MODE == 0 && NI <= HFX_STAGE_D_MAX_NI), "no staged D' rows");
     const ClassArgs& args;
@@ -493,25 +503,43 @@ struct BraRun {
                 for (int i = 0; i < NC * ND; ++i) dcd[i] = a.dket[(size_t)i * a.nket_list + s];
             };
             if constexpr (NI <= HFX_LOADS_FIRST_MAX_NI) load_ket();
-            double I[NI];
+            const double* kab = a.ket[s].AB;
+            double g;
+            auto factor = [&]() {
+                if constexpr (NI > HFX_LOADS_FIRST_MAX_NI) load_ket();
+                g = sbra * (kb.z != kb.w ? 2.0 : 1.0) * ((kb.z == bra.a && kb.w == bra.b) ? 1.0 : 2.0);
+            };
+            // FP64: half p of PARTS of the block's rows evaluated and digested (all
+            // indexes are constants, so what only the other half needs is not computed)
+            auto part = [&](auto p) {
+                constexpr int m0 = decltype(p)::value * NAP;
+                double I[NI];
+                E::template run<double>((const double*)(a.prim + bra.prim_off), bra.nprim, a.kprim + s, kfs, kps,
+                                        a.knprim, bra.AB, kab, t64, I);
+                if constexpr (m0 == 0) factor();
+                PairInfo rows = bra;
+                rows.bfa += m0;
+                digest<NAP, NB, NC, ND, MODE, DST>(I + m0 * (NI / NA), g, a, rows, kb.x, kb.y, s, dab + m0 * NB,
+                                                   jab + m0 * NB, FI + m0 * RS, FJ, Dm, Wm, N, RS, cb, db, dcd, Wm,
+                                                   a.wket, DI + m0 * RS, DJ);
+            };
             if (!FP32 || lo) {
-                E::template run<double>((const double*)(a.prim + bra.prim_off), bra.nprim, a.kprim + s,
-                                        kfs, kps, a.knprim, bra.AB, a.ket[s].AB, t64, I);
+                part(std::integral_constant<int, 0>());
+                if constexpr (PARTS > 1) part(std::integral_constant<int, 1>());
                 ++n64;
             } else if constexpr (FP32) {
-                // FP32 primitive copies, the FP64 Boys rows rounded
+                // FP32 primitive copies, the FP64 Boys rows rounded; the block digested in FP64
                 float If[NI];
+                double I[NI];
                 E::template run<float>(a.prim32 + (size_t)bra.prim_off * HFX_PRIM_FIELDS, bra.nprim,
-                                       a.kprim32 + s, kfs, kps, a.knprim, bra.AB, a.ket[s].AB, t64, If);
+                                       a.kprim32 + s, kfs, kps, a.knprim, bra.AB, kab, t64, If);
 #pragma unroll
                 for (int i = 0; i < NI; ++i) I[i] = (double)If[i];
+                factor();
+                digest<NA, NB, NC, ND, MODE, DST>(I, g, a, bra, kb.x, kb.y, s, dab, jab, FI, FJ, Dm, Wm, N, RS, cb, db,
+                                                  dcd, Wm, a.wket, DI, DJ);
                 ++n32;
             }
-            // the block (either precision) digested in FP64
-            if constexpr (NI > HFX_LOADS_FIRST_MAX_NI) load_ket();
-            const double g = sbra * (kb.z != kb.w ? 2.0 : 1.0) * ((kb.z == bra.a && kb.w == bra.b) ? 1.0 : 2.0);
-            digest<NA, NB, NC, ND, MODE, DST>(I, g, a, bra, kb.x, kb.y, s, dab, jab, FI, FJ, Dm, Wm, N, RS, cb, db, dcd,
-                                              Wm, a.wket, DI, DJ);
         }
         // bra J block: summed over each wave, then over the workgroup in LDS, so
         // that a task adds once to W (column bfb may lie outside its windows)

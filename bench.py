@@ -452,9 +452,10 @@ def main():
             autotune.apply(ctx, autotune.load(args.tuning))
         else:
             ctx.set_class_tuning(-1, *autotune.PREFERRED)
-        # launches in order on one stream, as in the builds the per-launch
+        # a launch per plan, in order on one stream, as in the builds the per-launch
         # times come from: a dispatch's trace interval and counters are then its own
         ctx.set_streams(1)
+        ctx.kernel_timing(True)
         for _ in range(args.warmup + args.steps):
             ctx.build_fock_dev(D.data_ptr(), F.data_ptr(), sptr)
         torch.cuda.synchronize()

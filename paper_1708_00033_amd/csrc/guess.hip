@@ -11,9 +11,10 @@
 //    neighbours), one 32-block per element), B's environment].
 // Network: 164 -> 256 -> 256 -> 256 (SiLU) -> one linear head per pair type
 // (O-O 225, O-H 30, H-H 4 outputs = the 15 x 15, 15 x 2, 2 x 2 blocks).
-// Layers run as MFMA GEMMs (v_mfma_f32_16x16x32_bf16): BF16 operands, FP32
-// accumulation; pre-activations and gradients are kept in FP32, Adam
-// updates FP32 master weights.
+// Layers run on the matrix units (v_mfma_f32_16x16x32_bf16): BF16 operands, FP32
+// accumulation; a workgroup takes 32 rows through the whole network, with
+// pre-activations and gradients in FP32 registers, Adam updates FP32 master
+// weights.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

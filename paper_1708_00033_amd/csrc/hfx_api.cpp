@@ -327,10 +327,6 @@ static double dfact_odd(int n) {   // (2n-1)!!
     return r;
 }
 
-// Plan one launch (class (B, K) against ket list li): per-bra screened ket
-// counts, workgroup tasks, counts.  Bras are the whole Q-sorted list of pair
-// class B; for B == K an unordered pair {bra, ket} is taken once, with the
-// ket not after the bra in that order (Q descending, then pair index).
 // 160 KiB of LDS per workgroup, less room for the persistent kernel's static counter
 constexpr size_t kLdsBudget = 160 * 1024 - 256;
 
@@ -340,6 +336,10 @@ static size_t table_lds(int B, int K) {
            sizeof(double) * hfx_jsum_doubles(ncart(kPairL[B][0]) * ncart(kPairL[B][1]));
 }
 
+// Plan the tasks of class (B, K) against ket list li: per-bra screened ket
+// counts, workgroup tasks, counts.  Bras are the whole Q-sorted list of pair
+// class B; for B == K an unordered pair {bra, ket} is taken once, with the
+// ket not after the bra in that order (Q descending, then pair index).
 static hfx_status plan_sub(hfx_ctx* c, int B, int li) {
     const std::vector<PairInfo>& bras = c->host_bra[B];
     const double* ket_q = c->host_ketq.data() + c->ketlists[li].s0;

@@ -732,7 +732,7 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
             if (q.atom < 0 || q.atom >= natom_m[m]) return hfx_fail(c, HFX_ERR_INVALID_ARG, "hfx_load: shell atom index");
             if (q.l < 0 || q.l > 2)
                 return hfx_fail(c, HFX_ERR_INVALID_ARG, "hfx_load: only s, p, d and SP shells (l in -1..2)");
-            if (q.nprim < 1 || q.nprim > 16 || !q.exps || !q.coefs)
+            if (q.nprim < 1 || q.nprim > HFX_MAX_NPRIM || !q.exps || !q.coefs)
                 return hfx_fail(c, HFX_ERR_INVALID_ARG, "hfx_load: nprim must be in [1, 16]");
             for (int k = 0; k < q.nprim; ++k)
                 if (!(q.exps[k] > 0.0) || !std::isfinite(q.exps[k]) || !std::isfinite(q.coefs[k]))
@@ -1101,7 +1101,7 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
         }
         c->set_end[set] = c->nket;
     }
-    // a task names its windows and its list in one word
+    // a task names its windows and its list in one word (hfx_task_code: no system that fits the card gets here)
     if ((int)c->ketlists.size() > HFX_TASK_MAX_LISTS ||
         c->max_ld / std::min(c->set_win[1], c->set_win[2]) >= (1 << HFX_TASK_WIN_BITS))
         return hfx_fail(c, HFX_ERR_INVALID_ARG, "too many ket lists or column windows");

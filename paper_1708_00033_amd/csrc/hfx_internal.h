@@ -62,8 +62,12 @@ struct KetListDev {
     int pad;
 };
 
-// A task's last word: column windows wc and wd, and the ket list.
-constexpr int HFX_TASK_WIN_BITS = 11, HFX_TASK_MAX_LISTS = 1 << (32 - 2 * HFX_TASK_WIN_BITS);
+// A task's last word: column windows wc and wd, and the ket list.  Contractions
+// of 1 to HFX_MAX_NPRIM = 16 primitives have 97 primitive-pair counts, so a context
+// has at most 97 x 6 pair classes x 3 sets = 1746 lists; 2^10 windows, none narrower
+// than 300 columns, are 3e5 functions, whose matrices take 720 GB each.
+constexpr int HFX_MAX_NPRIM = 16;
+constexpr int HFX_TASK_WIN_BITS = 10, HFX_TASK_MAX_LISTS = 1 << (32 - 2 * HFX_TASK_WIN_BITS);
 constexpr int hfx_task_code(int wc, int wd, int list) {
     return (int)((unsigned)wc | (unsigned)wd << HFX_TASK_WIN_BITS | (unsigned)list << 2 * HFX_TASK_WIN_BITS);
 }

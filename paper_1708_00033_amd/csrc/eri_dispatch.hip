@@ -1,4 +1,6 @@
 // Launch helpers for the per-class kernels (one translation unit per class).
+#include <algorithm>
+
 #include "hfx_internal.h"
 #include "generated/eri_classes.h"
 
@@ -203,8 +205,15 @@ extern "C" hipError_t hfx_launch_schwarz(int cid, const PairInfo* pairs, int npa
     const void* fn = kSchwarzLookup[cid]();
     if (!fn) return hipErrorInvalidValue;
     if (kEriClassInfo[cid].rys) {   // one workgroup per pair
-        void* kargs[] = {(void*)&pairs, (void*)&prim, (void*)&rys, (void*)&Q};
-        return hipLaunchKernel(fn, dim3(npairs), dim3(kEriClassInfo[cid].wgs), kargs, 0, stream);
+        for (int off = 0; off < npairs; off += HFX_MAX_GROUPS) {
+            const PairInfo* p = pairs + off;
+            double* q = Q + off;
+            void* kargs[] = {(void*)&p, (void*)&prim, (void*)&rys, (void*)&q};
+            const hipError_t e = hipLaunchKernel(fn, dim3(std::min(HFX_MAX_GROUPS, npairs - off)),
+                                                 dim3(kEriClassInfo[cid].wgs), kargs, 0, stream);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
     }
     void* kargs[] = {(void*)&pairs, (void*)&npairs, (void*)&prim, (void*)&boys, (void*)&Q};
     return hipLaunchKernel(fn, dim3((npairs + HFX_WG - 1) / HFX_WG), dim3(HFX_WG), kargs, 0, stream);

@@ -1479,9 +1479,7 @@ hfx_status hfx_build_with(hfx_ctx* c, const BuildBufs& bufs, const double* dD, d
         a.qlen = (int)(ntask / 8);
         a.task_off = 0;
         // a static grid of ntask workgroups is cut into launches of at most
-        // kMaxGroups (2^20 x 1024 lanes < 2^32 work-items; a multiple of 8
-        // keeps workgroup i on XCD i mod 8 in step with the task queues)
-        constexpr int kMaxGroups = 1 << 20;
+        // HFX_MAX_GROUPS
         if (c->timing && P.ev0) HIPCK(hipEventRecord(P.ev0, ps));
         // a mixed build's kernel evaluates each task's
         // kets before its split in FP64 and the rest in FP32
@@ -1492,9 +1490,9 @@ hfx_status hfx_build_with(hfx_ctx* c, const BuildBufs& bufs, const double* dD, d
             if (P.rys) HIPCK(hfx_launch_class_rys(cid, P.mode, m, 0, P.nblocks(m, ntask), P.lds(), ps, &a));
             else HIPCK(hfx_launch_class(cid, P.alt, P.wave > 0, P.mode, m, P.nblocks(m, ntask), P.lds(), ps, &a));
         } else {
-            for (long long off = 0; off < ntask; off += kMaxGroups) {
+            for (long long off = 0; off < ntask; off += HFX_MAX_GROUPS) {
                 a.task_off = (int)off;
-                const int nb = (int)std::min<long long>(kMaxGroups, ntask - off);
+                const int nb = (int)std::min<long long>(HFX_MAX_GROUPS, ntask - off);
                 if (P.rys) HIPCK(hfx_launch_class_rys(cid, P.mode, m, 0, nb, P.lds(), ps, &a));
                 else HIPCK(hfx_launch_class(cid, P.alt, 0, P.mode, m, nb, P.lds(), ps, &a));
             }

@@ -35,6 +35,11 @@ struct PairInfo {
     int ld;            // its basis size (leading dimension of its blocks)
 };
 
+// Workgroups of one launch at most: 2^20 x 1024 lanes stay below the grid limit of
+// 2^32 work-items; a multiple of 8 keeps workgroup i on XCD i mod 8 in step with
+// the task queues.
+constexpr int HFX_MAX_GROUPS = 1 << 20;
+
 // An element of a ket list's blocks: its place in the ragged matrices (< 0:
 // padding between lists) and the product of its component factors.
 struct KetElem {

@@ -393,7 +393,11 @@ hfx_status hfx_guess_assemble_dev(hfx_ctx *ctx, const float *dT, const double *d
  * H0[225x256] c0 H1[30x256] c1 H2[4x256] c2 (W: out x in, row-major), then
  * the feature mean[164], feature scale[164] and target scales[3]: input
  * (x - mean) / scale clipped to [-4, 4], block = output x target scale of
- * the pair's type. */
+ * the pair's type.
+ * Forward passes only read the network and may run on several streams at
+ * once: new parameters are in place when hfx_guess_set_params returns, and
+ * when the stream of hfx_guess_adam gets there.  A gradient uses scratch of
+ * the network: one at a time. */
 hfx_status hfx_guess_create(int device, hfx_guess **out);
 void hfx_guess_destroy(hfx_guess *g);
 long long hfx_guess_param_count(void);

@@ -1037,14 +1037,13 @@ struct hfx_guess {
     std::string err;
     std::vector<float> hp;
     float *p = nullptr, *gr = nullptr, *m = nullptr, *v = nullptr;
-    bf16_t* pk = nullptr;      // packed weights
+    bf16_t* pk = nullptr;      // packed weights: packed where p changes, so that passes only read them
     // gradient scratch for cap row blocks and pcap chunks
     long long cap = 0, pcap = 0;
     bf16_t *fx = nullptr, *fh[3] = {}, *fg[3] = {}, *fy = nullptr;
     float *csum = nullptr, *part = nullptr;
     double *esum = nullptr, *d_loss = nullptr;
     long long step = 0;
-    bool wdirty = true;
 };
 
 static hfx_status gfail(hfx_guess* g, hfx_status s, const std::string& msg) {
@@ -1085,6 +1084,19 @@ extern "C" void hfx_guess_destroy(hfx_guess* g) {
 
 extern "C" long long hfx_guess_param_count(void) { return PL.total; }
 
+static NetParams net_params(const hfx_guess* g) {
+    return NetParams{g->p,
+                     PL.off[P_W1], PL.off[P_B1], PL.off[P_W2], PL.off[P_B2], PL.off[P_W3], PL.off[P_B3],
+                     {PL.off[P_H0], PL.off[P_H1], PL.off[P_H2]},
+                     {PL.off[P_C0], PL.off[P_C1], PL.off[P_C2]},
+                     PL.off[P_FMEAN], PL.off[P_FSCALE]};
+}
+
+static hipError_t pack_weights(const hfx_guess* g, hipStream_t st) {
+    hipLaunchKernelGGL(k_pack, dim3(blocks_for(PWTOT)), dim3(WG), 0, st, net_params(g), g->pk);
+    return hipGetLastError();
+}
+
 extern "C" hfx_status hfx_guess_create(int device, hfx_guess** out) {
     if (!out) return HFX_ERR_INVALID_ARG;
     *out = nullptr;
@@ -1106,7 +1118,7 @@ extern "C" hfx_status hfx_guess_create(int device, hfx_guess** out) {
     hipLaunchKernelGGL(k_fill_f, dim3(blocks_for(n)), dim3(WG), 0, nullptr, g->m, n, 0.0f);
     hipLaunchKernelGGL(k_fill_f, dim3(blocks_for(n)), dim3(WG), 0, nullptr, g->v, n, 0.0f);
     hipLaunchKernelGGL(k_fill_f, dim3(blocks_for(n)), dim3(WG), 0, nullptr, g->gr, n, 0.0f);
-    if (hipDeviceSynchronize() != hipSuccess) return fail(HFX_ERR_DEVICE);
+    if (pack_weights(g, nullptr) != hipSuccess || hipDeviceSynchronize() != hipSuccess) return fail(HFX_ERR_DEVICE);
     *out = g;
     return HFX_OK;
 }
@@ -1124,7 +1136,8 @@ extern "C" hfx_status hfx_guess_set_params(hfx_guess* g, const float* params) {
     NCK(hipSetDevice(g->device));
     g->hp.assign(params, params + PL.total);
     NCK(hipMemcpy(g->p, params, PL.total * 4, hipMemcpyHostToDevice));
-    g->wdirty = true;
+    NCK(pack_weights(g, nullptr));
+    NCK(hipStreamSynchronize(nullptr));   // passes may follow on any stream
     return HFX_OK;
 }
 
@@ -1165,11 +1178,7 @@ static hfx_status net_args(hfx_guess* g, const float* dX, const int* counts, Net
     for (int t = 0; t < NTYPE; ++t)
         if (counts[t] < 0) return gfail(g, HFX_ERR_INVALID_ARG, "guess: negative row count");
     a = NetArgs{};
-    a.w = NetParams{g->p,
-                    PL.off[P_W1], PL.off[P_B1], PL.off[P_W2], PL.off[P_B2], PL.off[P_W3], PL.off[P_B3],
-                    {PL.off[P_H0], PL.off[P_H1], PL.off[P_H2]},
-                    {PL.off[P_C0], PL.off[P_C1], PL.off[P_C2]},
-                    PL.off[P_FMEAN], PL.off[P_FSCALE]};
+    a.w = net_params(g);
     a.pk = g->pk;
     a.X = dX;
     long long M = 0;
@@ -1187,13 +1196,6 @@ static hfx_status net_args(hfx_guess* g, const float* dX, const int* counts, Net
     return HFX_OK;
 }
 
-static hipError_t pack_weights(hfx_guess* g, const NetParams& w, hipStream_t st) {
-    if (!g->wdirty) return hipSuccess;
-    hipLaunchKernelGGL(k_pack, dim3(blocks_for(PWTOT)), dim3(WG), 0, st, w, g->pk);
-    g->wdirty = false;
-    return hipGetLastError();
-}
-
 extern "C" hfx_status hfx_guess_forward_dev(hfx_guess* g, const float* dX, const int* counts, float* dT,
                                             void* stream) {
     if (!g || !counts || !dT || !dX) return HFX_ERR_INVALID_ARG;
@@ -1203,7 +1205,6 @@ extern "C" hfx_status hfx_guess_forward_dev(hfx_guess* g, const float* dX, const
     long long ny;
     hfx_status s = net_args(g, dX, counts, a, ny);
     if (s != HFX_OK) return s;
-    NCK(pack_weights(g, a.w, st));
     a.out = dT;
     if (a.blk0[NTYPE] > 0)
         hipLaunchKernelGGL(k_net<false>, dim3(a.blk0[NTYPE]), dim3(NET_WG), 0, st, a);
@@ -1228,7 +1229,6 @@ extern "C" hfx_status hfx_guess_grad_dev(hfx_guess* g, const float* dX, const in
     const int chunk = std::max(1, (nblk + want - 1) / want), nchunk = nblk <= 16 ? 1 : want;
     s = ensure_cap(g, nblk, nchunk);
     if (s != HFX_OK) return s;
-    NCK(pack_weights(g, a.w, st));
     if (ny == 0) return gfail(g, HFX_ERR_INVALID_ARG, "guess: empty batch");
     WGradArgs wg{};
     GradSumArgs gs{};
@@ -1281,7 +1281,7 @@ extern "C" hfx_status hfx_guess_adam(hfx_guess* g, double lr, void* stream) {
     hipLaunchKernelGGL(k_adam, dim3(blocks_for(n)), dim3(WG), 0, (hipStream_t)stream, g->p, g->gr, g->m, g->v, n,
                        (float)lr, (float)b1, (float)b2, 1e-8f, c1, c2);
     NCK(hipGetLastError());
-    g->wdirty = true;
+    NCK(pack_weights(g, (hipStream_t)stream));
     return HFX_OK;
 }
 

@@ -988,6 +988,9 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
     // the bra's own class and of p-p and d-s.  Before, d-d bras above 1268 columns
     // went to W by global atomics ((dd|ss) and (dd|ps) 76 ms, now 10) and all
     // classes above 2048 were windowed: 559 ms for all classes, now 447.
+    // A cooperative class is asked with its own table, the others of a bra class with
+    // their largest: at 1261 functions, where (dd|pp), (dd|ds) and (dd|dd) no longer
+    // fit whole, windows take 0.90, 3.7 and 0.29 ms, global updates 1.10, 4.9 and 0.30.
     {
         constexpr int kWindow = 768, kPad = 8;   // pad: a shell's extent past its window
         constexpr int kCached = 2048;
@@ -998,17 +1001,20 @@ static hfx_status load_batch(hfx_ctx* c, int nmol, const int* natom_m, const int
         int rows2 = 1;      // and rows
         for (int B = 0; B < 6; ++B) {
             const int rows = ncart(kPairL[B][0]) + ncart(kPairL[B][1]);
+            const size_t whole = (size_t)rows * c->max_ld * sizeof(double);
             size_t tab = 0, tab_rys = 0;
             for (int K = 0; K <= B; ++K) {
                 const int cid = class_id(B, K);
                 if (hfx_class_is_rys(cid)) tab_rys = std::max(tab_rys, (size_t)hfx_class_rys_lds(cid, 0, 1));
                 else tab = std::max(tab, table_lds(B, K));
             }
-            // (cooperative classes whose tables do not fit as well sum a ket's updates before atomics)
-            const bool fits = (size_t)rows * c->max_ld * sizeof(double) + tab <= kLdsBudget;
             const bool wide = (size_t)rows * 2 * (kWindow + kPad) * sizeof(double) + tab <= kLdsBudget;
-            for (int K = 0; K <= B; ++K)
-                c->kset[class_id(B, K)] = fits && (c->max_ld <= kCached || K == B || K >= 2) ? 0 : wide ? 1 : 2;
+            for (int K = 0; K <= B; ++K) {
+                const int cid = class_id(B, K);
+                const size_t own = hfx_class_is_rys(cid) ? (size_t)hfx_class_rys_lds(cid, 0, 1) : tab;
+                const bool fits = whole + own <= kLdsBudget;
+                c->kset[cid] = fits && (c->max_ld <= kCached || K == B || K >= 2) ? 0 : wide ? 1 : 2;
+            }
             if (!wide) {
                 tab2 = std::max({tab2, tab, tab_rys});
                 rows2 = std::max(rows2, rows);

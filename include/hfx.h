@@ -317,10 +317,18 @@ hfx_status hfx_set_class_precision(hfx_ctx *ctx, int cls, int fp32);
  * the order (ss|ss), (ps|ss), (ps|ps), (pp|ss), ..., (dd|dd). */
 hfx_status hfx_class_counts(const hfx_ctx *ctx, long long *counts);
 
-/* Kernel timing: when enabled, every class kernel launch is bracketed by HIP
- * events on its stream; hfx_kernel_times returns per class the summed
- * milliseconds of its launches and the number of timed builds since the last
- * reset (synchronises on the recorded events). */
+/* Kernel timing, off (0) or with HIP events in one of two ways; hfx_kernel_times
+ * returns per class the summed milliseconds and the number of timed builds
+ * since the last reset (synchronises on the recorded events).
+ *   HFX_TIME_PLANS     every plan's kernel (hfx_plan_info): plans that a build
+ *                      launches together are launched one by one while this is
+ *                      on, so that each has a time of its own;
+ *   HFX_TIME_LAUNCHES  the launches that a build makes, in mixed builds with the
+ *                      kernel that finds each task's first FP32 ket: joined
+ *                      plans have one time, given with the first of them.  The
+ *                      autotuner's way.
+ * Either way all launches run on the caller's stream, one after the other. */
+enum { HFX_TIME_PLANS = 1, HFX_TIME_LAUNCHES = 2 };
 hfx_status hfx_kernel_timing(hfx_ctx *ctx, int enable);
 hfx_status hfx_kernel_times(hfx_ctx *ctx, double *ms, long long *launches);
 
@@ -330,18 +338,21 @@ hfx_status hfx_kernel_times(hfx_ctx *ctx, double *ms, long long *launches);
  * caller's stream (also under HIP graph capture), so a launch starts on the
  * CUs that the previous one frees while its last tasks finish.  While kernel
  * timing is enabled every launch runs on the caller's stream, in order, so
- * that its events bracket only its own kernel.  Results are unchanged up to
+ * that its events bracket only its own work.  Results are unchanged up to
  * the order of floating-point sums. */
 hfx_status hfx_set_streams(hfx_ctx *ctx, int n);
 
-/* Launches of a build: one per (quartet class, ket primitive count).
+/* Plans of a loaded system: the tasks of one quartet class against the kets of
+ * one primitive count.  A build launches the plans of a class together, up to
+ * 2^14 tasks in all, or (larger classes, register-tiled plans, HFX_TIME_PLANS)
+ * each by itself.
  * info[13] = {class index, ket primitives per pair, workgroup tasks, unique
  * quartets, primitive quartets, integrals, timed launches, digestion used
  * (HFX_DIGEST_*),
  * work-items per workgroup, launch form (0..4 as in hfx_set_class_tuning),
- * workgroups of the FP64 kernel, bras per task, staged D' rows: 0 none, 1
- * shell a's, 3 both shells'}; *ms = summed event time of
- * the timed launches. */
+ * workgroups of the plan's FP64 kernel launched by itself, bras per task,
+ * staged D' rows: 0 none, 1 shell a's, 3 both shells'}; *ms = summed event
+ * time of the timed launches. */
 hfx_status hfx_plan_count(const hfx_ctx *ctx, int *n);
 hfx_status hfx_plan_info(hfx_ctx *ctx, int i, long long *info, double *ms);
 

@@ -14,6 +14,7 @@ events, keeps each class's fastest setting, applies it and returns the table
 from __future__ import annotations
 
 import json
+import time
 from typing import Dict, Iterable, Sequence, Tuple
 
 import numpy as np
@@ -40,6 +41,24 @@ def _full(c) -> Tuple[int, int, int, int]:
     return c + _PAD[len(c):]
 
 
+# whole builds closer than this are equal: timer and launch noise
+_SAME_S = 20e-6
+
+
+def _build_s(ctx, dD_ptr: int, dF_ptr: int, stream: int, sync, reps: int) -> float:
+    """Seconds of a build as a program runs it: the best of three means over reps builds."""
+    ctx.build_fock_dev(dD_ptr, dF_ptr, stream)   # warm-up
+    sync()
+    best = float("inf")
+    for _ in range(3):
+        t = time.perf_counter()
+        for _ in range(reps):
+            ctx.build_fock_dev(dD_ptr, dF_ptr, stream)
+        sync()
+        best = min(best, (time.perf_counter() - t) / reps)
+    return best
+
+
 def autotune(ctx: "hfx.Context", dD_ptr: int, dF_ptr: int, stream: int,
              candidates: Sequence[Tuple[int, ...]] = DEFAULT_CANDIDATES, reps: int = 2,
              sync=None, prefer: Tuple[int, ...] = PREFERRED, margin: float = 0.03) -> Dict[str, dict]:
@@ -48,7 +67,8 @@ def autotune(ctx: "hfx.Context", dD_ptr: int, dF_ptr: int, stream: int,
 
     A class keeps the ``prefer`` setting (when it is a candidate) unless another
     candidate is faster by more than ``margin`` (relative): timing noise then
-    does not flip the launch shape from one run to the next."""
+    does not flip the launch shape from one run to the next.  All classes get
+    it where the whole build is then faster than with the classes' own choices."""
     if sync is None:
         import torch
         sync = torch.cuda.synchronize
@@ -59,7 +79,7 @@ def autotune(ctx: "hfx.Context", dD_ptr: int, dF_ptr: int, stream: int,
         ctx.set_class_tuning(-1, tq, st, pe, dg)
         ctx.build_fock_dev(dD_ptr, dF_ptr, stream)   # warm-up
         sync()
-        ctx.kernel_timing(True)
+        ctx.kernel_timing(hfx.HFX_TIME_LAUNCHES)
         for _ in range(reps):
             ctx.build_fock_dev(dD_ptr, dF_ptr, stream)
         sync()
@@ -78,7 +98,16 @@ def autotune(ctx: "hfx.Context", dD_ptr: int, dF_ptr: int, stream: int,
                                       "digest": int(dg),
                                       "ms": float(times[best, k]),
                                       "candidates_ms": [round(float(x), 4) for x in times[:, k]]}
+    # the plain setting: the preferred one for every class, or the one that is best in sum
+    plain = cands.index(prefer) if prefer in cands else int(np.argmin(times.sum(axis=1)))
+    ctx.set_class_tuning(-1, *cands[plain])
+    together = _build_s(ctx, dD_ptr, dF_ptr, stream, sync, reps)
     apply(ctx, table)
+    if _build_s(ctx, dD_ptr, dF_ptr, stream, sync, reps) > together + _SAME_S:
+        for k, name in enumerate(hfx.CLASS_NAMES):
+            table[name].update(zip(("task_quartets", "xcd_stripe", "persistent", "digest"), cands[plain]),
+                               ms=float(times[plain, k]))
+        apply(ctx, table)
     return table
 
 
@@ -86,7 +115,8 @@ def autotune_precision(ctx: "hfx.Context", dD_ptr: int, dF_ptr: int, stream: int
                        margin: float = 0.02) -> Dict[str, dict]:
     """For a context configured for mixed builds: time every class with its
     FP32 kernel on and off, keep FP32 where it is faster by more than
-    ``margin`` (FP64 is never less accurate), apply and return
+    ``margin`` (FP64 is never less accurate) unless the whole build is faster
+    without any, apply and return
     {class name: {"fp32", "ms_fp32", "ms_fp64"}}."""
     if sync is None:
         import torch
@@ -96,7 +126,7 @@ def autotune_precision(ctx: "hfx.Context", dD_ptr: int, dF_ptr: int, stream: int
         ctx.set_class_precision(-1, on)
         ctx.build_fock_dev(dD_ptr, dF_ptr, stream)
         sync()
-        ctx.kernel_timing(True)
+        ctx.kernel_timing(hfx.HFX_TIME_LAUNCHES)
         for _ in range(reps):
             ctx.build_fock_dev(dD_ptr, dF_ptr, stream)
         sync()
@@ -108,6 +138,14 @@ def autotune_precision(ctx: "hfx.Context", dD_ptr: int, dF_ptr: int, stream: int
         on = int(times[1, k] < times[0, k] * (1.0 - margin))
         ctx.set_class_precision(k, on)
         table[hfx.CLASS_NAMES[k]] = {"fp32": on, "ms_fp32": float(times[1, k]), "ms_fp64": float(times[0, k])}
+    if any(v["fp32"] for v in table.values()):
+        chosen = _build_s(ctx, dD_ptr, dF_ptr, stream, sync, reps)
+        ctx.set_class_precision(-1, 0)
+        if chosen > _build_s(ctx, dD_ptr, dF_ptr, stream, sync, reps) + _SAME_S:
+            for v in table.values():
+                v["fp32"] = 0
+        for k, name in enumerate(hfx.CLASS_NAMES):
+            ctx.set_class_precision(k, table[name]["fp32"])
     return table
 
 

@@ -1279,7 +1279,8 @@ static void collect_timing(hfx_ctx* c) {
 extern "C" hfx_status hfx_kernel_timing(hfx_ctx* c, int enable) {
     if (!c) return HFX_ERR_INVALID_ARG;
     collect_timing(c);
-    c->timing = enable != 0;
+    if (enable < 0 || enable > HFX_TIME_LAUNCHES) enable = HFX_TIME_PLANS;
+    c->timing = enable;
     for (auto& p : c->plans) {
         p.ms = 0.0;
         p.launches = 0;
@@ -1436,16 +1437,19 @@ hfx_status hfx_build_with(hfx_ctx* c, const BuildBufs& bufs, const double* dD, d
     HIPCK(fork_streams(c, ns, st));
     // one launch per class (the fewer, the shorter its idle ends and a small
     // build's launch overhead), one per plan when each is timed
-    const size_t nl = c->timing ? c->plans.size() : c->launches.size();
+    const bool apart = c->timing == HFX_TIME_PLANS;
+    const size_t nl = apart ? c->plans.size() : c->launches.size();
     for (size_t li = 0; li < nl; ++li) {
-        const size_t pi = c->timing ? li : c->launches[li].plan;
+        const size_t pi = apart ? li : c->launches[li].plan;
         SubPlan& P = c->plans[pi];
-        const size_t toff = c->timing ? P.toff : c->launches[li].toff;
-        const long long ntask = c->timing ? P.ntask : c->launches[li].ntask;
+        const size_t toff = apart ? P.toff : c->launches[li].toff;
+        const long long ntask = apart ? P.ntask : c->launches[li].ntask;
         const int kp = c->ketlists[P.list].kp;
         const int cid = P.cid;
         const bool mx = mixed && !P.fp64_only && c->tune_fp32[cid] && !P.kr;
         const hipStream_t ps = plan_stream(c, ns, li, st);
+        // a launch as the build makes it is timed with its split, a plan's kernel alone
+        if (c->timing == HFX_TIME_LAUNCHES && P.ev0) HIPCK(hipEventRecord(P.ev0, ps));
         if (mx)
             HIPCK(hfx_split(c->d_pairs[P.B], c->d_lists, c->d_ketq, c->d_tasks + toff, (int)ntask, c->opt.fp32_tau,
                             bufs.dmax, c->d_split + toff, ps));
@@ -1486,7 +1490,7 @@ hfx_status hfx_build_with(hfx_ctx* c, const BuildBufs& bufs, const double* dD, d
         a.task_off = 0;
         // a static grid of ntask workgroups is cut into launches of at most
         // HFX_MAX_GROUPS
-        if (c->timing && P.ev0) HIPCK(hipEventRecord(P.ev0, ps));
+        if (apart && P.ev0) HIPCK(hipEventRecord(P.ev0, ps));
         // a mixed build's kernel evaluates each task's
         // kets before its split in FP64 and the rest in FP32
         const int m = mx ? 1 : 0;
@@ -1742,8 +1746,8 @@ extern "C" hfx_status hfx_graph_capture(hfx_ctx* c, const double* dD, double* dF
     HIPCK(hipSetDevice(c->opt.device));
     hipStream_t st = (hipStream_t)stream;
     drop_graph(c);
-    const bool timing = c->timing;
-    c->timing = false;
+    const int timing = c->timing;
+    c->timing = 0;
     hfx_status s = hfx_build_internal(c, dD, 2.0, 1.0, c->d_H, dF, st, nullptr, 0, 1);
     if (s != HFX_OK) {
         c->timing = timing;

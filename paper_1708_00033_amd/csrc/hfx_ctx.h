@@ -39,7 +39,8 @@ struct SubPlan {
     int dstage = 0;           // ClassArgs::dstage: bit 0 shell a's D' rows staged, bit 1 shell b's
     size_t lds_tab = 0;       // the class's FP64 Boys rows in LDS (rys: integrals and small sums)
     int mode = 0;             // digestion actually used (LDS may fall back to global)
-    // timing (when enabled): events around this launch, summed milliseconds
+    // timing (when enabled): events around the plan's kernel, or around the launch that it is the
+    // first plan of, summed milliseconds
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     bool pending = false;
     double ms = 0.0;
@@ -190,7 +191,7 @@ struct hfx_ctx {
     // SAD: atomic densities by element and basis (kept across loads)
     std::map<std::string, std::vector<double>> sad_cache;
     // timing
-    bool timing = false;
+    int timing = 0;   // HFX_TIME_*, 0: off
     hipStream_t last_stream = nullptr;
     // class launches of a build spread over the caller's stream and
     // nstreams - 1 side streams (created with the context, default

@@ -635,11 +635,11 @@ static hfx_status batch_scf_graph(hfx_ctx* c, const hfx_scf_options& o, hfx_scf_
     BLASCK(rocblas_set_stream(h, st));
     BLASCK(rocblas_set_pointer_mode(h, rocblas_pointer_mode_host));
     const double one = 1.0, zero = 0.0;
-    const bool timing = c->timing;
-    c->timing = false;   // no events inside captured work
+    const int timing = c->timing;
+    c->timing = 0;   // no events inside captured work
     struct TimingRestore {
         hfx_ctx* c;
-        bool t;
+        int t;
         ~TimingRestore() {
             c->timing = t;
             rocblas_set_stream(c->blas, 0);

@@ -41,6 +41,7 @@ STATUS_NAMES = {0: "HFX_OK", 1: "HFX_ERR_INVALID_ARG", 2: "HFX_ERR_OOM", 3: "HFX
                 4: "HFX_ERR_NOT_CONVERGED", 5: "HFX_ERR_NUMERICAL", 6: "HFX_ERR_STATE"}
 HFX_PREC_FP64, HFX_PREC_MIXED = 0, 1
 HFX_DIGEST_LDS, HFX_DIGEST_GLOBAL, HFX_DIGEST_PRIVATE, HFX_DIGEST_LDS_D = 0, 1, 2, 3
+HFX_TIME_PLANS, HFX_TIME_LAUNCHES = 1, 2
 HFX_GUESS_SAD, HFX_GUESS_CORE, HFX_GUESS_LEARNED = 0, 1, 2
 GUESS_NFEAT = 164
 GUESS_HEAD_OUT = (225, 30, 4)
@@ -460,14 +461,15 @@ class Context:
         self._check(hfx_class_counts(self.ptr, a.ctypes.data_as(C.POINTER(C.c_longlong))))
         return a.reshape(21, 4)
 
-    def kernel_timing(self, enable: bool = True):
+    def kernel_timing(self, enable: int = True):
+        """Off, HFX_TIME_PLANS (True) or HFX_TIME_LAUNCHES (include/hfx.h)."""
         self._check(hfx_kernel_timing(self.ptr, int(enable)))
 
     def set_streams(self, n: int):
         self._check(hfx_set_streams(self.ptr, int(n)))
 
     def plans(self):
-        """Per launch: dict(cls, ket_nprim, tasks, quartets, prim, integrals, launches, mode, wgs,
+        """Per plan: dict(cls, ket_nprim, tasks, quartets, prim, integrals, launches, mode, wgs,
         persistent, blocks, bras_per_task, dstage, ms)."""
         n = C.c_int()
         self._check(hfx_plan_count(self.ptr, C.byref(n)))

@@ -306,17 +306,20 @@ static int grid_for(size_t n) {
 }
 
 extern "C" {
+// Columns of a (columns, nmol) grid at most: below 2^32 work-items (the kernels stride).
+static size_t most_columns(int nmol) { return ((1ull << 32) - 1) / ((size_t)MISC_WG * nmol); }
 static dim3 ragged_grid(int max_ld, int nmol) {
-    size_t g = ((size_t)max_ld * max_ld + MISC_WG - 1) / MISC_WG;
-    if (g > 4096) g = 4096;
-    return dim3((unsigned)(g ? g : 1), (unsigned)nmol);
+    const size_t g = ((size_t)max_ld * max_ld + MISC_WG - 1) / MISC_WG;
+    return dim3((unsigned)std::max<size_t>(1, std::min({g, (size_t)4096, most_columns(nmol)})), (unsigned)nmol);
 }
 hipError_t hfx_start_build(const double* D, const double* cs, int nmol, const long long* moff, const int* mdim,
                            const int* mboff, int max_ld, const KetElem* ke, size_t nke, const StartBufs* b,
                            hipStream_t st) {
     dim3 g = ragged_grid(max_ld, nmol);
-    const int gx = (int)g.x;
-    g.x += (unsigned)std::min<size_t>((nke + (size_t)MISC_WG * nmol - 1) / ((size_t)MISC_WG * nmol), 4096);
+    const size_t most = std::max<size_t>(2, most_columns(nmol));
+    const size_t per = (size_t)MISC_WG * nmol, kx = std::min({(nke + per - 1) / per, (size_t)4096, most / 2});
+    const int gx = (int)std::min<size_t>(g.x, most - kx);
+    g.x = (unsigned)(gx + kx);
     hipLaunchKernelGGL(k_start_build, g, dim3(MISC_WG), 0, st, D, cs, moff, mdim, mboff, gx, ke, nke, *b);
     return hipGetLastError();
 }

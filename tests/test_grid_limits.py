@@ -1,8 +1,11 @@
 """Launches stay below the grid limit of 2^32 work-items (no GPU).
 
-A stand-in for hipLaunchKernel, loaded before the library, records the grids of
+Stand-ins for the launch calls, loaded before the library, records the grids of
 the Schwarz launches of every pair class for as many pairs as 13.5 million: one
-launch of a workgroup of 320 lanes per pair would be 4.3e9 work-items.
+launch of a workgroup of 320 lanes per pair would be 4.3e9 work-items; and of
+the first and last launch of a build for batches of up to 65,535 molecules
+(a grid's rows) beside one of up to 2,000 functions: a workgroup per 256
+elements of the largest molecule for each would be 2.6e11.
 """
 import json
 import os
@@ -13,6 +16,9 @@ STUB = r"""
 typedef struct { unsigned x, y, z; } dim3;
 unsigned long long n, grids[64], lanes[64];
 const void *args[64][2];
+static dim3 cg, cb;
+int __hipPushCallConfiguration(dim3 g, dim3 b, unsigned long m, void *t) { cg = g; cb = b; return 0; }
+int __hipPopCallConfiguration(dim3 *g, dim3 *b, unsigned long *m, void **t) { *g = cg; *b = cb; *m = 0; *t = 0; return 0; }
 int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **a, unsigned long s, void *t) {
     grids[n] = (unsigned long long)g.x * g.y * g.z;
     lanes[n] = (unsigned long long)b.x * b.y * b.z;
@@ -43,6 +49,23 @@ for cid, npairs in json.loads(sys.argv[3]):
 print(json.dumps(out))
 """
 
+RUN_BATCH = RUN[:RUN.index("lib.hfx_launch_schwarz.argtypes")] + r"""
+i, z = C.c_int, C.c_size_t
+lib.hfx_start_build.argtypes = [v, v, i, v, v, v, i, v, z, v, v]
+lib.hfx_assemble.argtypes = [v, v, v, i, v, v, v, i, v, v, v]
+n = C.c_ulonglong.in_dll(stub, "n")
+grids = (C.c_ulonglong * 64).in_dll(stub, "grids")
+lanes = (C.c_ulonglong * 64).in_dll(stub, "lanes")
+bufs = (C.c_ulonglong * 16)()
+out = []
+for nmol, ld, nke in json.loads(sys.argv[3]):
+    n.value = 0
+    lib.hfx_start_build(1, 1, nmol, 1, 1, 1, ld, 1, nke, C.addressof(bufs), None)
+    lib.hfx_assemble(1, 1, 1, nmol, 1, 1, 1, ld, 1, 1, None)
+    out.append([(grids[k], lanes[k]) for k in range(n.value)])
+print(json.dumps(out))
+"""
+
 
 def test_schwarz_launches(tmp_path):
     (tmp_path / "stub.c").write_text(STUB)
@@ -63,3 +86,20 @@ def test_schwarz_launches(tmp_path):
             assert done == npairs
         else:
             assert len(rows) == 1 and rows[0][0] * rows[0][1] >= npairs
+
+
+def test_build_launches_of_large_batches(tmp_path):
+    (tmp_path / "stub.c").write_text(STUB)
+    stub = str(tmp_path / "stub.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", stub, str(tmp_path / "stub.c")], check=True)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    cases = [(1, 26, 1000), (1, 9728, 10 ** 9), (256, 304, 10 ** 7), (40000, 304, 2 * 10 ** 9), (65535, 2000, 10 ** 9),
+             (65535, 2, 0), (65535, 2, 10 ** 10)]
+    res = subprocess.run([sys.executable, "-c", RUN_BATCH, stub, root, json.dumps(cases)], check=True, text=True,
+                         capture_output=True).stdout
+    for (nmol, ld, nke), rows in zip(cases, json.loads(res)):
+        assert len(rows) == 2
+        for g, b in rows:
+            assert g * b < 1 << 32 and g % nmol == 0, (nmol, ld, nke)
+        # columns for the matrices, and others for the ket elements where there are any
+        assert rows[0][0] // nmol >= 1 + (nke > 0) and rows[1][0] // nmol >= 1

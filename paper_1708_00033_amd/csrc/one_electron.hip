@@ -67,7 +67,7 @@ struct VrrTable {
 };
 
 struct PairPrim {   // one primitive pair in LDS
-    double p, i2p, x, y, z, pre;   // exponent, 1/(2p), centre P, -2 pi / p c_a c_b exp(-mu AB^2)
+    double p, i2p, x, y, z, pre;   // exponent, 1/(2p), P - A, -2 pi / p c_a c_b exp(-mu AB^2)
 };
 
 // One class (LA >= LB) of one molecule: pairs of its nla shells of LA with its
@@ -99,7 +99,6 @@ __global__ __launch_bounds__(64) void k_one_electron(const OneElMol* __restrict_
             j = (int)(pid % nlb);
         }
         const ShellHost A = sh[order[M.first[LA] + i]], B = sh[order[M.first[LB] + j]];
-        const double Ap[3] = {A.x, A.y, A.z}, Bp[3] = {B.x, B.y, B.z};
         const double AB[3] = {A.x - B.x, A.y - B.y, A.z - B.z};
         const double ab2 = AB[0] * AB[0] + AB[1] * AB[1] + AB[2] * AB[2];
         double s_acc[NA * NB], t_acc[NA * NB], v_acc[NE - E0];
@@ -115,15 +114,17 @@ __global__ __launch_bounds__(64) void k_one_electron(const OneElMol* __restrict_
                 const int ia = (base + lane) / B.nprim, ib = (base + lane) % B.nprim;
                 const double al = exps[A.prim_off + ia], be = exps[B.prim_off + ib];
                 const double p = al + be, i2p = 0.5 / p, mu = al * be / p;
-                const double P[3] = {(al * A.x + be * B.x) / p, (al * A.y + be * B.y) / p, (al * A.z + be * B.z) / p};
+                // P - A and P - B from A - B: as differences of coordinates they lose the
+                // digits that tight functions far from the origin need
+                const double fa = -be / p, fb = al / p;
                 const double k3 = coefs[A.prim_off + ia] * coefs[B.prim_off + ib] * exp(-mu * ab2);
-                pp[lane] = PairPrim{p, i2p, P[0], P[1], P[2], -2.0 * M_PI / p * k3};
+                pp[lane] = PairPrim{p, i2p, fa * AB[0], fa * AB[1], fa * AB[2], -2.0 * M_PI / p * k3};
                 // 1-D overlaps and kinetic integrals
                 double S1[3][LA + 1][LB + 3], T1[3][LA + 1][LB + 1];
                 const double s00 = sqrt(M_PI / p);
 #pragma unroll
                 for (int x = 0; x < 3; ++x) {
-                    const double PA = P[x] - Ap[x], PB = P[x] - Bp[x];
+                    const double PA = fa * AB[x], PB = fb * AB[x];
 #pragma unroll
                     for (int a = 0; a <= LA; ++a) {
                         S1[x][a][0] = a == 0 ? s00
@@ -159,8 +160,8 @@ __global__ __launch_bounds__(64) void k_one_electron(const OneElMol* __restrict_
             while (q < n) {
                 const PairPrim pr = pp[q];
                 const double* at = atoms + 4 * (size_t)(M.aoff + r);
-                const double PC[3] = {pr.x - at[0], pr.y - at[1], pr.z - at[2]};
-                const double PA[3] = {pr.x - Ap[0], pr.y - Ap[1], pr.z - Ap[2]};
+                const double PA[3] = {pr.x, pr.y, pr.z};
+                const double PC[3] = {PA[0] + (A.x - at[0]), PA[1] + (A.y - at[1]), PA[2] + (A.z - at[2])};
                 // a centre without charge adds zero, wherever it lies
                 const double T = at[3] != 0.0 ? pr.p * (PC[0] * PC[0] + PC[1] * PC[1] + PC[2] * PC[2]) : 0.0;
                 double F[L + 1];

@@ -39,7 +39,9 @@ def class_flop_model():
     """Algorithmic flops of each class: per primitive quartet (setup, Boys
     with downward recursion, vertical recurrence) and per quartet
     (horizontal recurrences, contraction sums, 6 updates x 2 flops per
-    integral for the digestion of eq. 2)."""
+    integral for the digestion of eq. 2).  A measure of work that stays the same
+    when kernels change: (dp|dp), (dd|pp), (dd|ds), (dd|dp) and (dd|dd), which run
+    a quadrature with other operations, are counted by their recurrences too."""
     sys.path.insert(0, os.path.join(ROOT, "paper_1708_00033_amd", "csrc"))
     import gen_eri
     out = []

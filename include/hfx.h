@@ -299,9 +299,9 @@ hfx_status hfx_configure(hfx_ctx *ctx, const hfx_options *opt);
  * fit), FP64 only -- a mixed build evaluates such a class in FP64; classes
  * or ket lists without register-tiled kernels fall back to 1; 4: as 3 with
  * one bra per task) and the digestion (-1: the context's
- * option; HFX_DIGEST_LDS, _GLOBAL, _PRIVATE or _LDS_D; LDS staging needs
- * (n_a + n_b) x nbf x 8 bytes <= 160 KiB and falls back to global
- * otherwise).  Re-plans a loaded system; results are unchanged up to the
+ * option; HFX_DIGEST_LDS, _GLOBAL, _PRIVATE or _LDS_D; bra rows of n_a + n_b
+ * times nbf doubles that do not fit in 160 KiB of LDS are staged as column
+ * windows).  Re-plans a loaded system; results are unchanged up to the
  * order of floating-point sums.  Set by the autotuner
  * (paper_1708_00033_amd/autotune.py). */
 hfx_status hfx_set_class_tuning(hfx_ctx *ctx, int cls, int task_quartets, int xcd_stripe, int persistent,

@@ -33,9 +33,13 @@
 // One lane's FP64 block of at least this many integrals ((dp|pp): 162; larger
 // ones are shared between lanes) is evaluated and digested in two halves of shell
 // a's components: its 144 sums over primitives and 162 integrals do not fit in
-// 512 registers, those of a half nearly do.  44-atom sheet: 18.8 -> 11.6 ms,
-// 33 waters 0.42 -> 0.46 (long contractions, whose recursions run twice); thirds
-// the same; (dp|ds) and (dd|ps), 108 integrals that fit, 3.6 -> 3.9 and 1.7 -> 2.5.
+// 512 registers, those of a half nearly do.  What spills is written and read once
+// per primitive quartet, so that halves gain with many of those to a quartet (44-atom
+// sheet, 17: 19.3 -> 11.6 ms) and pay for the recursions run twice with few (64
+// waters: 1.94 and 1.96 ms, resident grids 2.01 and 1.96).  Chosen per task by its
+// primitives, both forms in one kernel, the sheet took 12.4 to 12.7 ms and waters
+// 1.8 to 1.9.  Thirds the same; (dp|ds) and (dd|ps), 108 integrals that fit, 3.6 ->
+// 3.9 and 1.7 -> 2.5.
 #define HFX_HALVES_MIN_NI 162
 
 // K update of W[grow][gcol]: MODE 0 into the task's LDS bra row at column

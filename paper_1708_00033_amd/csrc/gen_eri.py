@@ -50,7 +50,7 @@ WG1024 = {1, 6}
 WG512 = {0, 2, 3, 4, 7, 9, 10}
 # Classes evaluated by the cooperative Rys-quadrature kernels (eri_rys.h), with
 # the kets of a batch: 16 where the one-dimensional integrals of 16 kets fit in
-# LDS beside the bra rows at 1,216 basis functions, else 8.
+# LDS beside whole bra rows of 1,216 functions, else 8 (larger molecules: windows).
 RYS_CLASSES = {14: 16, 17: 16, 18: 16, 19: 8, 20: 8}
 # Classes that mixed builds evaluate in FP64 too (a d-d bra and a d-d or d-p ket).
 FP64_ONLY = {19, 20}

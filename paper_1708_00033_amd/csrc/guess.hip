@@ -660,7 +660,7 @@ __global__ __launch_bounds__(NET_WG, 4) void k_net(const NetArgs a) {
 // contracted rows split over chunks of row blocks (blockIdx.x), within a chunk
 // over the workgroup's four waves.  A tile's chain over 8192 rows on one
 // workgroup left 16 workgroups at work for over a millisecond a layer; eight
-// chunks are 544 workgroups, 15 us, and 0.8 MB of partial sums each.  All
+// chunks are 544 workgroups, 15 us, and 0.96 MB of partial sums each.  All
 // fragments are whole, so loads need no bounds.
 constexpr int GTILES = 3 * 16 - 4 + 16 + 4 + 4;   // W3, W2 (16 each), W1 (12), H0 (16), H1, H2 (4 each)
 
@@ -1223,8 +1223,9 @@ extern "C" hfx_status hfx_guess_grad_dev(hfx_guess* g, const float* dX, const in
     if (s != HFX_OK) return s;
     const int nblk = a.blk0[NTYPE];
     // Chunks in eights: the workgroups of a chunk, eight apart in launch order,
-    // then share an XCD, whose L2 holds the chunk's fragments (30 KB a row
-    // block).  At most 32: the partial sums stay below 25 MB for any batch.
+    // then share an XCD, whose 4 MB L2 holds the chunk's fragments (124 KB a row
+    // block; up to 32 blocks, 4 MB, to 1024 blocks in all).  At most 32 chunks: the
+    // partial sums stay below 31 MB for any batch.
     const int want = nblk <= 16 ? 1 : 8 * std::min(4, (nblk + 255) / 256);
     const int chunk = std::max(1, (nblk + want - 1) / want), nchunk = nblk <= 16 ? 1 : want;
     s = ensure_cap(g, nblk, nchunk);

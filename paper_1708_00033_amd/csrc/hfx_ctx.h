@@ -107,8 +107,8 @@ struct hfx_ctx {
     int* d_mboff = nullptr;
     // Per ket list, groups of kets sharing (molecule, column window of shell c,
     // column window of shell d), Q descending within a group: group starts
-    // (ngroup + 1), each molecule's first group (nmol + 1), window code per
-    // group (wc | wd << 16).  Without windows a group is a molecule.
+    // (ngroup + 1), each molecule's first group (nmol + 1), task code per group
+    // (hfx_task_code).  Without windows a group is a molecule.
     std::vector<std::vector<int>> kgroup, kmolg, kwcode;
     // the ket lists come in up to three sets that differ in how they are grouped
     // for the LDS rows of the bras (load_batch): per quartet class its set; per

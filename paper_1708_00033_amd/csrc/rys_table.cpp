@@ -6,11 +6,11 @@
 // every polynomial P of degree below 2n, so that sum_r w_r x_r^m = F_m(T).
 // For each T the recurrence coefficients of the orthogonal polynomials come
 // from the Stieltjes procedure on a 48-point Gauss-Legendre discretisation of
-// the weight (exact to rounding for T <= RYS_TMAX), the roots from bisection
+// the weight (exact to rounding for T <= RYS_NT), the roots from bisection
 // and secant steps between the roots of the next lower polynomial, and the weights from the
 // Christoffel sums, all in long double.  Roots and weights are then
 // interpolated in T by one polynomial of degree RYS_NC - 1 per unit interval
-// (Chebyshev nodes).  Above RYS_TMAX the upper limit of the integral may be
+// (Chebyshev nodes), stored as powers.  Above RYS_NT the upper limit of the integral may be
 // moved to infinity (the tail is below 1.4e-17 of F_8 there): x_r = h_r / T
 // and w_r = v_r / sqrt(T) with the half-range Gauss-Hermite nodes h_r = s_r^2
 // and weights v_r, which the same procedure gives from the discretised weight
